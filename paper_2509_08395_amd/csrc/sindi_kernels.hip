@@ -41,6 +41,8 @@ constexpr int kWave = 64;
 constexpr int kRerankPerWave = 4;  // pool entries one rerank wave scores at a time
 constexpr int kRerankGroups = 4;   // such groups per wave (one query table per workgroup)
 constexpr int kMaxSeg = kQueryHash / 2 / kWave;  // 64-term segments of the longest query
+constexpr int kPrepWaves = 8;      // query rows per prep workgroup, one wave each
+constexpr int kPrepRow = 512;      // longest query row a prep wave holds in registers and LDS
 
 __device__ __forceinline__ uint32_t ord_f32(float f)
 {
@@ -195,27 +197,170 @@ __device__ K block_select(int64_t n, int64_t r, Load load, uint32_t *hist, int *
 }
 
 // ------------------------------------------------------------------ queries
-// One wave per query row.  Flags malformed rows (err[0] bits: 1 row pointers,
-// 2 term id out of range, 4 ids not strictly ascending, 8 non-finite value,
-// 16 more than kQueryHash / 2 entries), keeps the longest row in err[1],
-// and writes the coarse terms: the non-zero entries, cut to the beta-mass
-// subvector when beta < 1 (entries ranked by |q| descending, ties by id;
-// FP64 prefix sums in that order, the first prefix reaching beta * mass),
-// with weights pre-multiplied by the query's fixed-point scale.
-__global__ __launch_bounds__(256) void k_query_prep(DevQueries q, int64_t n_cols, double beta,
-                                                    DevCoarse c, const float *term_max,
-                                                    double *sabs, int32_t *err)
+// Orders a wave's LDS accesses against each other (one wave's DS operations execute in order;
+// this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// LDS of one prep wave: the row's ranking keys, later its kept entries.
+struct PrepRow {
+    union {
+        uint64_t key[kPrepRow];
+        struct {
+            int32_t id[kPrepRow];
+            float w[kPrepRow];
+        };
+    };
+    float abs[kPrepRow];  // |x| by rank
+};
+
+// Entries of a row of n <= 64 J held J per lane (entry 64 j + lane in slot j; id, v; absent and
+// zero entries have key 0): bit j of the result is set for the slots Def. 6's prefix keeps.
+template <int J>
+__device__ __forceinline__ uint32_t beta_mass_keep(const uint64_t (&key)[J], int32_t n, double beta,
+                                                   PrepRow &r)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x / kWave);
-    if (row >= q.n_rows) return;
-    int64_t a = q.indptr[row], b = q.indptr[row + 1];
+    int32_t rank[J], nz = 0;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        r.key[j * kWave + lane] = key[j];
+        rank[j] = 0;
+        nz += (int32_t)__popcll(__ballot(key[j] != 0));
+    }
+    wave_lds_sync();
+    // rank of every entry in pi order: the keys above its own (zero keys are above none)
+    for (int32_t f = 0; f < n; f += 8) {  // past n: zero keys
+        uint64_t k[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) k[i] = r.key[f + i];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int j = 0; j < J; ++j) rank[j] += k[i] > key[j] ? 1 : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+        if (key[j]) r.abs[rank[j]] = __uint_as_float((uint32_t)(key[j] >> 32));
+    wave_lds_sync();
+    // FP64 prefix sums in rank order, one addition after another; lane l keeps the sums of
+    // ranks l, l + 64, ...  The last one is the mass.
+    double run = 0.0, pre[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        pre[j] = 0.0;
+        const int32_t m = min(kWave, nz - j * kWave);
+        const int av = __float_as_int(r.abs[j * kWave + lane]);  // past nz: not read below
+        for (int32_t t = 0; t < m; ++t) {
+            run += (double)__int_as_float(__builtin_amdgcn_readlane(av, t));
+            pre[j] = lane == t ? run : pre[j];
+        }
+    }
+    const double thr = beta * run;
+    int32_t kept = nz;
+#pragma unroll
+    for (int j = J - 1; j >= 0; --j) {
+        const uint64_t m = __ballot(j * kWave + lane < nz && pre[j] >= thr);
+        if (m) kept = j * kWave + (int32_t)__ffsll((unsigned long long)m);
+    }
+    uint32_t bits = 0;
+#pragma unroll
+    for (int j = 0; j < J; ++j) bits |= (key[j] && rank[j] < kept) ? 1u << j : 0u;
+    return bits;
+}
+
+// The fixed-point exponent of a query whose coarse sums are bounded by `bound`: the largest
+// power of two keeping every partial sum within 2^30 in magnitude.
+__device__ __forceinline__ int scale_exponent(float bound)
+{
+    int ex = 0;
+    if (bound > 0.0f) {
+        (void)frexpf(bound, &ex);  // bound < 2^ex
+        ex = 30 - ex;
+        ex = ex > 100 ? 100 : (ex < -100 ? -100 : ex);
+    }
+    return ex;
+}
+
+// A row of n <= 64 J entries at a: check, prune, scale and write its coarse terms.  Returns the
+// malformed-row bits (nothing is written then).
+template <int J>
+__device__ __forceinline__ int prep_row(const DevQueries &q, int64_t n_cols, double beta,
+                                        const DevCoarse &c, const float *term_max, int64_t row,
+                                        int64_t a, int32_t n, PrepRow &r)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    int32_t id[J];
+    float v[J];
+    uint64_t key[J];
     int bad = 0;
-    if (a < 0 || b < a || b > q.nnz || (row == 0 && a != 0) || (row == q.n_rows - 1 && b != q.nnz))
-        bad |= 1;
-    a = a < 0 ? 0 : (a > q.nnz ? q.nnz : a);
-    b = b < a ? a : (b > q.nnz ? q.nnz : b);
-    if (b - a > kQueryHash / 2) bad |= 16;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int32_t e = j * kWave + lane;
+        id[j] = 0;
+        v[j] = 0.0f;
+        key[j] = 0;
+        if (e < n) {
+            id[j] = q.indices[a + e];
+            v[j] = q.values[a + e];
+            if (id[j] < 0 || id[j] >= n_cols) bad |= 2;
+            if (e + 1 < n && q.indices[a + e + 1] <= id[j]) bad |= 4;
+            if (!isfinite(v[j])) bad |= 8;
+            if (v[j] != 0.0f)
+                key[j] = ((uint64_t)__float_as_uint(fabsf(v[j])) << 32) | (0xFFFFFFFFu - (uint32_t)id[j]);
+        }
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) bad |= __shfl_xor(bad, m, kWave);
+    if (bad) return bad;
+    uint32_t keep = 0;
+    if (beta < 1.0) {
+        keep = beta_mass_keep<J>(key, n, beta, r);
+        wave_lds_sync();  // the keys give way to the kept entries
+    } else {
+#pragma unroll
+        for (int j = 0; j < J; ++j) keep |= key[j] ? 1u << j : 0u;
+    }
+    // ordered compaction of the kept entries (ascending term id preserved)
+    int32_t base = 0;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const bool k = (keep >> j) & 1u;
+        const uint64_t m = __ballot(k);
+        if (k) {
+            const int32_t p = base + (int32_t)lanes_below(m);
+            r.id[p] = id[j];
+            r.w[p] = v[j];
+        }
+        base += (int32_t)__popcll(m);
+    }
+    wave_lds_sync();
+    float bound = 0.0f;
+    for (int32_t i = lane; i < base; i += kWave) bound += fabsf(r.w[i]) * term_max[r.id[i]];
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) bound += __shfl_xor(bound, m, kWave);
+    const int ex = scale_exponent(bound);
+    const float scale = ldexpf(1.0f, ex);
+    for (int32_t i = lane; i < base; i += kWave) {
+        c.ct[a + i] = r.id[i];
+        c.cw[a + i] = r.w[i] * scale;
+    }
+    if (lane == 0) {
+        c.cn[row] = base;
+        c.qinv[row] = ldexpf(1.0f, -ex);
+    }
+    return 0;
+}
+
+// The malformed-row bits of the entries [a, b).
+__device__ int scan_row(const DevQueries &q, int64_t n_cols, int64_t a, int64_t b)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    int bad = 0;
     for (int64_t e = a + lane; e < b; e += kWave) {
         int32_t id = q.indices[e];
         float v = q.values[e];
@@ -225,15 +370,15 @@ __global__ __launch_bounds__(256) void k_query_prep(DevQueries q, int64_t n_cols
     }
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) bad |= __shfl_xor(bad, m, kWave);
-    if (bad) {
-        if (lane == 0) {
-            atomicOr(err, bad);
-            c.cn[row] = 0;
-            c.qinv[row] = 1.0f;
-        }
-        return;
-    }
-    if (lane == 0) atomicMax(err + 1, (int32_t)(b - a));  // longest row: rerank table size
+    return bad;
+}
+
+// A row [a, b) of more than kPrepRow entries, through global memory (sabs: FP64 scratch).
+__device__ int prep_long_row(const DevQueries &q, int64_t n_cols, double beta, const DevCoarse &c,
+                             const float *term_max, double *sabs, int64_t row, int64_t a, int64_t b)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    if (const int bad = scan_row(q, n_cols, a, b)) return bad;
     int32_t r_keep = 0x7FFFFFFF;  // rank bound of kept entries
     if (beta < 1.0) {
         // rank of every non-zero entry in pi order; |x| placed at its rank
@@ -271,7 +416,6 @@ __global__ __launch_bounds__(256) void k_query_prep(DevQueries q, int64_t n_cols
         }
         r_keep = __shfl(r, 0, kWave);
     }
-    // ordered compaction of the kept entries (ascending term id preserved)
     int32_t base = 0;
     for (int64_t e0 = a; e0 < b; e0 += kWave) {
         int64_t e = e0 + lane;
@@ -302,25 +446,84 @@ __global__ __launch_bounds__(256) void k_query_prep(DevQueries q, int64_t n_cols
         }
         base += __popcll(m);
     }
-    // fixed-point scale: the largest power of two keeping every partial
-    // coarse sum of this query within 2^30 in magnitude
     float bound = 0.0f;
     for (int32_t i = lane; i < base; i += kWave)
         bound += fabsf(c.cw[a + i]) * term_max[c.ct[a + i]];
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) bound += __shfl_xor(bound, m, kWave);
-    int ex = 0;
-    if (bound > 0.0f) {
-        (void)frexpf(bound, &ex);  // bound < 2^ex
-        ex = 30 - ex;
-        ex = ex > 100 ? 100 : (ex < -100 ? -100 : ex);
-    }
+    const int ex = scale_exponent(bound);
     const float scale = ldexpf(1.0f, ex);
     for (int32_t i = lane; i < base; i += kWave) c.cw[a + i] *= scale;
     if (lane == 0) {
         c.cn[row] = base;
         c.qinv[row] = ldexpf(1.0f, -ex);
     }
+    return 0;
+}
+
+// One wave per query row.  Flags malformed rows (err[0] bits: 1 row pointers,
+// 2 term id out of range, 4 ids not strictly ascending, 8 non-finite value,
+// 16 more than kQueryHash / 2 entries), keeps the longest row in err[1],
+// and writes the coarse terms: the non-zero entries, cut to the beta-mass
+// subvector when beta < 1 (entries ranked by |q| descending, ties by id;
+// FP64 prefix sums in that order, the first prefix reaching beta * mass),
+// with weights pre-multiplied by the query's fixed-point scale.
+//
+// Bound by latency: the row's entries are read once, one to eight per lane, and ranked, summed
+// and compacted in the wave's registers and LDS.  At beta 0.8, 37 rows of 5 to 123 entries take
+// 12 us and 7,000 rows of 35 take 19 us; ranking through global memory, summing on one lane and
+// an atomic per row for the longest row took 93 and 242 us (86 us at beta 1, all of it atomics).
+__global__ __launch_bounds__(kPrepWaves * kWave) void k_query_prep(DevQueries q, int64_t n_cols,
+                                                                   double beta, DevCoarse c,
+                                                                   const float *term_max,
+                                                                   double *sabs, int32_t *err)
+{
+    __shared__ PrepRow s_row[kPrepWaves];
+    __shared__ int32_t s_longest;
+    if (threadIdx.x == 0) s_longest = 0;
+    __syncthreads();
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = (int)uni((uint32_t)threadIdx.x / kWave);
+    const int64_t row = (int64_t)blockIdx.x * kPrepWaves + wave;
+    const bool live = row < q.n_rows;
+    int64_t a = live ? q.indptr[row] : 0, b = live ? q.indptr[row + 1] : 0;
+    int bad = 0;
+    if (live && (a < 0 || b < a || b > q.nnz || (row == 0 && a != 0) ||
+                 (row == q.n_rows - 1 && b != q.nnz)))
+        bad |= 1;
+    a = a < 0 ? 0 : (a > q.nnz ? q.nnz : a);
+    b = b < a ? a : (b > q.nnz ? q.nnz : b);
+    if (b - a > kQueryHash / 2) bad |= 16;
+    PrepRow &r = s_row[wave];
+    if (!live)
+        ;
+    else if (bad)
+        bad |= scan_row(q, n_cols, a, b);
+    else if (b - a <= kWave)
+        bad = prep_row<1>(q, n_cols, beta, c, term_max, row, a, (int32_t)(b - a), r);
+    else if (b - a <= 2 * kWave)
+        bad = prep_row<2>(q, n_cols, beta, c, term_max, row, a, (int32_t)(b - a), r);
+    else if (b - a <= 4 * kWave)
+        bad = prep_row<4>(q, n_cols, beta, c, term_max, row, a, (int32_t)(b - a), r);
+    else if (b - a <= kPrepRow)
+        bad = prep_row<kPrepRow / kWave>(q, n_cols, beta, c, term_max, row, a, (int32_t)(b - a), r);
+    else
+        bad = prep_long_row(q, n_cols, beta, c, term_max, sabs, row, a, b);
+    if (live && lane == 0) {
+        if (bad) {
+            atomicOr(err, bad);
+            c.cn[row] = 0;
+            c.qinv[row] = 1.0f;
+        } else {
+            atomicMax(&s_longest, (int32_t)(b - a));
+        }
+    }
+    // the longest row (sizes the rerank table): one device atomic per workgroup, and none where
+    // the value is already reached (an atomic of every row on one word cost 12 ns each)
+    __syncthreads();
+    if (threadIdx.x == 0 &&
+        __hip_atomic_load(err + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < s_longest)
+        atomicMax(err + 1, s_longest);
 }
 
 // ------------------------------------------------------------------ accumulate
@@ -1764,8 +1967,8 @@ hipError_t launch_query_prep(const DevQueries &q, int64_t n_cols, double beta, D
                              hipStream_t s)
 {
     if (q.n_rows == 0) return hipSuccess;
-    dim3 grid((unsigned)((q.n_rows + 3) / 4));
-    hipLaunchKernelGGL(k_query_prep, grid, dim3(256), 0, s, q, n_cols, beta, c, term_max,
+    dim3 grid((unsigned)((q.n_rows + kPrepWaves - 1) / kPrepWaves));
+    hipLaunchKernelGGL(k_query_prep, grid, dim3(kPrepWaves * kWave), 0, s, q, n_cols, beta, c, term_max,
                        scratch_abs, err_flag);
     return hipGetLastError();
 }

@@ -1,0 +1,52 @@
+"""GPU kernels at the sizes where their splits change: edges of registers, waves and tables."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def sindi():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2509_08395_amd as s
+    s._lib.load()
+    return s
+
+
+def _np(t):
+    return t.detach().cpu().numpy()
+
+
+def _rows(rng, lens, vocab, ties=False):
+    """Signed rows of exactly these lengths; with ties every |value| is one of four, zero too."""
+    indptr = np.zeros(len(lens) + 1, np.int64)
+    np.cumsum(lens, out=indptr[1:])
+    ids = np.concatenate([np.sort(rng.choice(vocab, n, replace=False)) for n in lens] or [[]])
+    val = (rng.choice([0.0, 0.5, 1.0, 2.0], indptr[-1]) if ties else rng.lognormal(0, 0.8, indptr[-1]))
+    val = val * rng.choice([-1.0, 1.0], indptr[-1])
+    return synth.Csr(indptr, ids.astype(np.int32), val.astype(np.float32), vocab)
+
+
+# ------------------------------------------------------------------ query preparation
+@pytest.mark.parametrize("ties", [False, True])
+@pytest.mark.parametrize("beta", [0.8, 0.3, 1.0])
+def test_query_prep_row_lengths(sindi, beta, ties):
+    """beta-mass rows on both sides of every register split: the same coarse results, bit for
+    bit, as the rows the oracle pruned (the coarse weights are then the same numbers)."""
+    rng = np.random.default_rng(5)
+    vocab = 3_000
+    corpus = synth.random_csr(rng, 3_000, vocab, 60, signed=True)
+    lens = [0, 1, 2, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 512, 513, 700]
+    q = _rows(rng, lens, vocab, ties)
+    idx = sindi.Index(corpus, alpha=1.0, window=1_000, value_dtype="f32")
+    got = idx.search_coarse(sindi.DeviceCsr.from_host(q), 40, beta=beta)
+    cut = oracle.apply_mask(q, oracle.mass_prune(q, beta))
+    ref = idx.search_coarse(sindi.DeviceCsr.from_host(cut), 40)
+    assert np.array_equal(_np(got[0]), _np(ref[0]))
+    assert np.array_equal(_np(got[1]).view(np.uint32), _np(ref[1]).view(np.uint32))
