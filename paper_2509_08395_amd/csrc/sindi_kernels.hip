@@ -39,7 +39,8 @@ namespace {
 
 constexpr int kWave = 64;
 constexpr int kRerankPerWave = 4;  // pool entries one rerank wave scores at a time
-constexpr int kRerankGroups = 4;   // such groups per wave (one query table per workgroup)
+constexpr int kRerankGroups = 4;   // most such groups per wave (one query table per workgroup)
+constexpr int64_t kRerankFill = 2048;  // rerank workgroups that fill the chip
 constexpr int kMaxSeg = kQueryHash / 2 / kWave;  // 64-term segments of the longest query
 constexpr int kPrepWaves = 8;      // query rows per prep workgroup, one wave each
 constexpr int kPrepRow = 512;      // longest query row a prep wave holds in registers and LDS
@@ -73,6 +74,10 @@ __device__ __forceinline__ int4 fresh_zero4()
 
 // Wave-uniform copy of a value (scalar register).
 __device__ __forceinline__ uint32_t uni(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ int64_t uni64(int64_t x)
+{
+    return (int64_t)(((uint64_t)uni((uint32_t)((uint64_t)x >> 32)) << 32) | uni((uint32_t)x));
+}
 // A wave-uniform pointer to global memory, held in scalar registers, and
 // loads of 8 or 16 bytes at a 32-bit byte offset from it (the scalar base +
 // vector offset form of the global load).
@@ -1491,8 +1496,100 @@ __device__ __forceinline__ float wave_dot(const DevIndex &ix, const QueryHash &h
     return wave_sum(acc);
 }
 
+// The full (unpruned) query row in LDS: 2^lg buckets of two entries {term, term, value, value},
+// empty terms -1.  A term sits in its home bucket or, where that is full, in the next one with
+// room; `spill` says whether any term did that.  With eight buckets per term few tables spill
+// (n^3 / 6 B^2: 3% at 35 terms and 512 buckets), and a lookup is then one 16-byte LDS read and
+// two compares with no loop: an open-addressing table of half the size ran its probe loop about
+// three times per 64 lanes, which is what bounded the rerank (see k_rerank).
+struct QueryTable {
+    int4 *b;
+    int32_t lg;
+    uint32_t spill;
+};
+constexpr int kTableLgMax = 12;  // 64 KB; holds the longest row (kQueryHash / 2 terms)
+
+__host__ __device__ __forceinline__ int table_lg(int64_t n)
+{
+    int lg = 6;
+    while (lg < kTableLgMax && (1ll << lg) < 8 * n) ++lg;
+    return lg;
+}
+
+// Byte offset of a term's home bucket (Fibonacci hashing of the term's low 24 bits).
+__device__ __forceinline__ uint32_t home_bucket(int32_t id, int lg)
+{
+    return (__umul24((uint32_t)id, 0x9E3779u) >> (20 - lg)) & (((1u << lg) - 1u) << 4);
+}
+
+// Fill the table from the query row [a, b): every thread of the workgroup, two barriers.
+// s_spill: a word of LDS.
+__device__ __forceinline__ void build_table(const DevQueries &q, int64_t a, int64_t b,
+                                            QueryTable &t, uint32_t *s_spill)
+{
+    const int B = 1 << t.lg;
+    for (int i = threadIdx.x; i < B; i += blockDim.x) t.b[i] = make_int4(-1, -1, 0, 0);
+    if (threadIdx.x == 0) *s_spill = 0u;
+    __syncthreads();
+    for (int64_t e = a + threadIdx.x; e < b; e += blockDim.x) {
+        const int32_t id = q.indices[e];
+        const float v = q.values[e];
+        const uint32_t home = home_bucket(id, t.lg) >> 4;
+        for (uint32_t i = home;; i = (i + 1) & (uint32_t)(B - 1)) {
+            int32_t *k = reinterpret_cast<int32_t *>(t.b + i);
+            const int s = atomicCAS(k, -1, id) == -1 ? 0 : (atomicCAS(k + 1, -1, id) == -1 ? 1 : 2);
+            if (s < 2) {
+                k[2 + s] = __float_as_int(v);
+                if (i != home) *s_spill = 1u;
+                break;
+            }
+        }
+    }
+    __syncthreads();
+    t.spill = uni(*s_spill);
+}
+
+// The query's value of a term; false where it has none.  id -2 is no term.
+__device__ __forceinline__ bool table_get(const QueryTable &t, int32_t id, float &v)
+{
+    uint32_t off = home_bucket(id, t.lg);
+    int4 k = *reinterpret_cast<const int4 *>(reinterpret_cast<const unsigned char *>(t.b) + off);
+    if (t.spill) {  // uniform: some term of this query is not in its home bucket
+        while (k.x != id && k.y != id && k.y != -1) {
+            off = (off + 16) & (((1u << t.lg) - 1u) << 4);
+            k = *reinterpret_cast<const int4 *>(reinterpret_cast<const unsigned char *>(t.b) + off);
+        }
+    }
+    v = __int_as_float(k.x == id ? k.z : k.w);
+    return k.x == id || k.y == id;
+}
+
+// The wave-wide sums of four values at once, each in the pairing of a butterfly over lane
+// distances 32, 16, 8, 4, 2, 1: lane l gets the sum of value (l >> 5) + 2 ((l >> 4) & 1).  The
+// halves and rows of two values are swapped into one register, so a stage adds two values' halves
+// with one instruction.
+__device__ __forceinline__ float wave_sum4(float a, float b, float c, float d)
+{
+    auto swap32 = [](float x, float y) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    };
+    auto swap16 = [](float x, float y) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    };
+    float s = swap16(swap32(a, b), swap32(c, d));
+    // rotations within rows of 16 lanes: after the stage at distance d the values repeat every d
+    // lanes, so a rotation by d / 2 reads the partner
+    s += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x128, 0xF, 0xF, false));
+    s += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x124, 0xF, 0xF, false));
+    s += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x122, 0xF, 0xF, false));
+    s += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x121, 0xF, 0xF, false));
+    return s;
+}
+
 // LDS sizes: P = the power of two at or above need keys, a rerank table of
-// 2^hlg slots, hlg = hash_lg of the longest query row of the launch.
+// 2^tlg buckets, tlg = table_lg of the longest query row of the launch.
 __host__ __device__ inline int32_t pow2_at_least(int32_t n)
 {
     int32_t p = 1;
@@ -1667,31 +1764,37 @@ __global__ __launch_bounds__(kFinThreads) void k_finalize(
 }
 
 // Exact rerank (Alg. 4): each wave scores kRerankPerWave pool entries at a
-// time, kRerankGroups times, NW waves per workgroup, grid (slot, entry block);
-// each workgroup builds the query's hash in LDS (2^hlg slots) once for its
-// kRerankGroups x NW x kRerankPerWave entries.  The entry's key becomes (FP32
+// time, `groups` times, NW waves per workgroup, grid (slot, entry block);
+// each workgroup builds the query's table in LDS (2^tlg buckets) once for its
+// groups x NW x kRerankPerWave entries.  The entry's key becomes (FP32
 // inner product of the unpruned row with the full query, then inverted id).
 // Slots not finalized are skipped.
+//
+// Bound by HBM where the queries are many: 7,000 queries' 500 rows of ~125 entries (3.5 GB) take
+// 0.56 ms, 6.3 TB/s; with an open-addressing table probed in a loop, butterfly sums and vector row
+// addresses the instructions bound it (1.37 ms).  A call of few queries is bound by the chain of
+// key, row bounds and row loads, so it takes one group per wave: one query 8.3 us, 41 us with four
+// groups on eight workgroups.
 __global__ __launch_bounds__(kFinThreads) void k_rerank(DevIndex ix, DevQueries q,
                                                         const int32_t *slot_q, int32_t need,
-                                                        int32_t hlg, uint64_t *pool,
+                                                        int32_t tlg, int32_t groups, uint64_t *pool,
                                                         int32_t *status)
 {
     constexpr int NW = kFinThreads / kWave, EPW = kRerankPerWave;
+    static_assert(EPW == 4, "wave_sum4");
     extern __shared__ __align__(16) unsigned char smem[];
-    int32_t *hid = reinterpret_cast<int32_t *>(smem);          // [2^hlg]
-    float *hval = reinterpret_cast<float *>(hid + (1 << hlg));  // [2^hlg]
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    __shared__ uint32_t s_spill;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = (int)uni((uint32_t)threadIdx.x / kWave);
     const int32_t slot = blockIdx.x;
     const int32_t row = slot_q ? slot_q[slot] : slot;
     if (status[row] != kSlotOk) return;
     const int64_t qa = q.indptr[row], qb = q.indptr[row + 1];
-    const int lg = hash_lg(qb - qa);
-    if (lg > hlg) {  // the launch was sized for shorter rows
+    QueryTable tb{reinterpret_cast<int4 *>(smem), table_lg(qb - qa), 0u};
+    if (tb.lg > tlg) {  // the launch was sized for shorter rows
         if (threadIdx.x == 0 && blockIdx.y == 0) status[row] = kSlotRetry;
         return;
     }
-    const QueryHash h{hid, hval, nullptr, lg};
     uint64_t *e = pool + (size_t)slot * (size_t)need;
     uint32_t lo[EPW];
     int64_t ra[EPW], rb[EPW];
@@ -1713,45 +1816,55 @@ __global__ __launch_bounds__(kFinThreads) void k_rerank(DevIndex ix, DevQueries 
     // The first group's keys and row bounds are loaded before the query table is
     // built, and the first two 64-entry rounds of every row of a group are loaded
     // together, so the entries' memory latencies overlap.
-    const int32_t first = (int32_t)blockIdx.y * kRerankGroups * NW;
+    const int32_t first = (int32_t)blockIdx.y * groups * NW;
     bounds((first + wave) * EPW);
-    build_query_hash(q, qa, qb, h);
-    for (int g = 0; g < kRerankGroups; ++g) {
+    build_table(q, qa, qb, tb, &s_spill);
+    for (int g = 0; g < groups; ++g) {
         const int32_t c0 = (first + g * NW + wave) * EPW;
         if (c0 >= need) break;  // wave-uniform; no barrier follows
-        if (g > 0) bounds(c0);
         int32_t id[EPW][2];
         float xv[EPW][2];
-#pragma unroll
-        for (int j = 0; j < EPW; ++j)
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const int64_t p = ra[j] + r * kWave + lane;
-                id[j][r] = -1;
-                xv[j][r] = 0.0f;
-                if (p < rb[j]) {
-                    id[j][r] = ix.indices[p];
-                    xv[j][r] = ix.values[p];
-                }
-            }
-        // delta(q, x_doc) in FP32, each lane over entries lane, lane + 64, ... of the
-        // row in order, then summed across the wave
+        int64_t pa[EPW];
+        int32_t pn[EPW];
+        uint32_t plo[EPW];
 #pragma unroll
         for (int j = 0; j < EPW; ++j) {
-            float acc = 0.0f;
+            pa[j] = uni64(ra[j]);
+            pn[j] = (int32_t)uni((uint32_t)(rb[j] - ra[j]));
+            plo[j] = uni(lo[j]);
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
-                if (id[j][r] < 0) continue;
-                const int sl = probe(h, id[j][r]);
-                if (sl >= 0) acc = fmaf(h.val[sl], xv[j][r], acc);
+                id[j][r] = -2;
+                xv[j][r] = 0.0f;
+                if (r * kWave + lane < pn[j]) {
+                    id[j][r] = (ix.indices + pa[j])[r * kWave + lane];
+                    xv[j][r] = (ix.values + pa[j])[r * kWave + lane];
+                }
             }
-            for (int64_t p = ra[j] + 2 * kWave + lane; p < rb[j]; p += kWave) {
-                const int sl = probe(h, ix.indices[p]);
-                if (sl >= 0) acc = fmaf(h.val[sl], ix.values[p], acc);
-            }
-            const float sc = wave_sum(acc);
-            if (c0 + j < need && lane == 0) e[c0 + j] = ((uint64_t)ord_f32(sc) << 32) | lo[j];
         }
+        // the next group's keys and bounds arrive while this one's rows are looked up
+        if (g + 1 < groups) bounds(c0 + NW * EPW);
+        // delta(q, x_doc) in FP32, each lane over entries lane, lane + 64, ... of the
+        // row in order, then summed across the wave
+        float acc[EPW];
+#pragma unroll
+        for (int j = 0; j < EPW; ++j) {
+            acc[j] = 0.0f;
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                float v;
+                if (table_get(tb, id[j][r], v)) acc[j] = fmaf(v, xv[j][r], acc[j]);
+            }
+            for (int32_t p = 2 * kWave + lane; p < pn[j]; p += kWave) {
+                float v;
+                if (table_get(tb, (ix.indices + pa[j])[p], v))
+                    acc[j] = fmaf(v, (ix.values + pa[j])[p], acc[j]);
+            }
+        }
+        const float sc = wave_sum4(acc[0], acc[1], acc[2], acc[3]);
+        const int j = (lane >> 5) + 2 * ((lane >> 4) & 1);  // the entry whose sum the lane has
+        const uint32_t l = j == 0 ? plo[0] : (j == 1 ? plo[1] : (j == 2 ? plo[2] : plo[3]));
+        if ((lane & 15) == 0 && c0 + j < need) e[c0 + j] = ((uint64_t)ord_f32(sc) << 32) | l;
     }
 }
 
@@ -2062,13 +2175,18 @@ hipError_t launch_finalize(const DevIndex &ix, const DevQueries &q, const int32_
                        slot_q, count, cand, theta, cap, need, k, (int32_t)bm, pool, out_ids,
                        out_scores, status);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    const int32_t hlg = hash_lg(max_qnnz > 0 ? max_qnnz : 1);
-    const size_t lds_h = ((size_t)1 << hlg) * 8;
-    e = set_lds(k_rerank, lds_h);
+    const int32_t tlg = table_lg(max_qnnz > 0 ? max_qnnz : 1);
+    const size_t lds_t = (size_t)16 << tlg;
+    e = set_lds(k_rerank, lds_t);
     if (e != hipSuccess) return e;
-    constexpr int PER_WG = kFinThreads / kWave * kRerankPerWave * kRerankGroups;
-    hipLaunchKernelGGL(k_rerank, dim3((unsigned)n_slots, (unsigned)((need + PER_WG - 1) / PER_WG)),
-                       dim3(kFinThreads), lds_h, s, ix, q, slot_q, need, hlg, pool, status);
+    // few queries: fewer entries per workgroup, so that more of them share the work
+    constexpr int kPerGroup = kFinThreads / kWave * kRerankPerWave;
+    int32_t groups = kRerankGroups;
+    while (groups > 1 && (int64_t)n_slots * ((need + kPerGroup * groups - 1) / (kPerGroup * groups)) < kRerankFill)
+        groups >>= 1;
+    const unsigned blocks = (unsigned)((need + kPerGroup * groups - 1) / (kPerGroup * groups));
+    hipLaunchKernelGGL(k_rerank, dim3((unsigned)n_slots, blocks), dim3(kFinThreads), lds_t, s, ix,
+                       q, slot_q, need, tlg, groups, pool, status);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     e = set_lds(k_topk, keys);
     if (e != hipSuccess) return e;

@@ -50,3 +50,24 @@ def test_query_prep_row_lengths(sindi, beta, ties):
     ref = idx.search_coarse(sindi.DeviceCsr.from_host(cut), 40)
     assert np.array_equal(_np(got[0]), _np(ref[0]))
     assert np.array_equal(_np(got[1]).view(np.uint32), _np(ref[1]).view(np.uint32))
+
+
+# ------------------------------------------------------------------ rerank
+def test_rerank_table_sizes(sindi):
+    """Query rows around every table size (full and spilling tables among them) against document
+    rows around every 64-entry round: FP32 inner products within the rounding of their sums."""
+    rng = np.random.default_rng(6)
+    vocab, nd = 5_000, 210
+    corpus = _rows(rng, [0, 1, 2, 63, 64, 65, 127, 128, 129, 130, 192, 193, 300] * 16 + [0, 77], vocab)
+    q = _rows(rng, [0, 1, 7, 8, 9, 16, 17, 32, 33, 64, 65, 128, 129, 256, 257, 512, 513, 1500, 4096], vocab)
+    idx = sindi.Index(corpus, alpha=0.5, window=100, value_dtype="f32")
+    for rows in (np.arange(q.n_rows), np.array([9]), np.array([18])):  # many and few workgroups
+        sub = q.take_rows(rows)
+        ids, sc = (_np(t) for t in idx.search(sindi.DeviceCsr.from_host(sub), nd, gamma=nd))
+        assert all(sorted(r) == list(range(nd)) for r in ids.tolist())
+        qi = np.repeat(np.arange(sub.n_rows), nd)
+        ref = oracle.pair_scores(corpus, sub, qi, ids.reshape(-1))
+        mag = lambda m: synth.Csr(m.indptr, m.indices, np.abs(m.values), m.n_cols)
+        # at most 5 additions on a lane and 6 across the wave, each within 2^-24 of the partial sums
+        tol = 11 * 2.0 ** -24 * oracle.pair_scores(mag(corpus), mag(sub), qi, ids.reshape(-1))
+        assert (np.abs(sc.reshape(-1) - ref) <= tol + 1e-30).all()
