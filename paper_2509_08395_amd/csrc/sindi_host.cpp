@@ -980,8 +980,11 @@ sindi_status search_impl(sindi_index *ix, const sindi_csr *qc, int32_t k,
                       grow_workspace, &ws);
 }
 
-sindi_status check_dev_queries(sindi_index *ix, const sindi_csr *qc, const char *fn, hipStream_t s)
+// Waits for the stream; *longest: the longest query row.
+sindi_status check_dev_queries(sindi_index *ix, const sindi_csr *qc, const char *fn, hipStream_t s,
+                               int32_t *longest)
 {
+    *longest = 0;
     if (!qc->on_device) return fail(SINDI_E_INVALID, "%s: queries must be device memory", fn);
     if (qc->n_cols != ix->n_cols) return fail(SINDI_E_INVALID, "%s: column count mismatch", fn);
     if (qc->n_rows < 0 || qc->nnz < 0) return fail(SINDI_E_INVALID, "%s: bad query shape", fn);
@@ -996,10 +999,11 @@ sindi_status check_dev_queries(sindi_index *ix, const sindi_csr *qc, const char 
     HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t *>(sc.err), 2, 0u, s));
     DevCoarse dc{sc.ct, sc.cw, sc.cn, sc.qinv};
     HIP_TRY(launch_query_prep(dq, ix->n_cols, 1.0, dc, ix->term_max.as<float>(), nullptr, sc.err, s));
-    int32_t qerr = 0;
-    HIP_TRY(hipMemcpyAsync(&qerr, sc.err, 4, hipMemcpyDeviceToHost, s));
+    int32_t qerr[2] = {0, 0};
+    HIP_TRY(hipMemcpyAsync(qerr, sc.err, 8, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    if (qerr) return fail(SINDI_E_INVALID, "%s: malformed query rows (flags 0x%x)", fn, qerr);
+    if (qerr[0]) return fail(SINDI_E_INVALID, "%s: malformed query rows (flags 0x%x)", fn, qerr[0]);
+    *longest = qerr[1];
     return SINDI_OK;
 }
 
@@ -1124,12 +1128,13 @@ sindi_status sindi_score_forward(const sindi_index *idx, const sindi_csr *querie
     sindi_index *ix = const_cast<sindi_index *>(idx);
     std::lock_guard<std::mutex> lock(ix->mu);
     hipStream_t s = (hipStream_t)stream;
-    sindi_status st = check_dev_queries(ix, queries, "sindi_score_forward", s);
+    int32_t longest = 0;
+    sindi_status st = check_dev_queries(ix, queries, "sindi_score_forward", s, &longest);
     if (st != SINDI_OK) return st;
     DevQueries dq{queries->n_rows, queries->nnz, queries->indptr, queries->indices, queries->values};
     DevIndex dix = ix->dev();
     if (doc_values) dix.values = doc_values;
-    HIP_TRY(launch_score_forward(dix, dq, cand_ids, n_cand, out_scores, s));
+    HIP_TRY(launch_score_forward(dix, dq, cand_ids, n_cand, longest, out_scores, s));
     return SINDI_OK;
 }
 
@@ -1144,13 +1149,14 @@ sindi_status sindi_score_backward(const sindi_index *idx, const sindi_csr *queri
     sindi_index *ix = const_cast<sindi_index *>(idx);
     std::lock_guard<std::mutex> lock(ix->mu);
     hipStream_t s = (hipStream_t)stream;
-    sindi_status st = check_dev_queries(ix, queries, "sindi_score_backward", s);
+    int32_t longest = 0;
+    sindi_status st = check_dev_queries(ix, queries, "sindi_score_backward", s, &longest);
     if (st != SINDI_OK) return st;
     DevQueries dq{queries->n_rows, queries->nnz, queries->indptr, queries->indices, queries->values};
     DevIndex dix = ix->dev();
     if (doc_values) dix.values = doc_values;
-    HIP_TRY(launch_score_backward(dix, dq, cand_ids, n_cand, grad_scores, grad_query_values,
-                                  grad_doc_values, s));
+    HIP_TRY(launch_score_backward(dix, dq, cand_ids, n_cand, longest, grad_scores,
+                                  grad_query_values, grad_doc_values, s));
     return SINDI_OK;
 }
 

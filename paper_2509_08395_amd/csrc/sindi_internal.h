@@ -180,11 +180,12 @@ hipError_t build_deal_chunks(const uint32_t *goff, const int64_t *tile_post, int
                              int64_t n_cols, int32_t vbytes, uint16_t *post_doc, void *post_val,
                              hipStream_t s);
 
+// Pair scores and their gradients; max_qnnz: the longest query row (sizes the query tables).
 hipError_t launch_score_forward(const DevIndex &ix, const DevQueries &q, const int64_t *cand,
-                                int32_t n_cand, float *out, hipStream_t s);
+                                int32_t n_cand, int32_t max_qnnz, float *out, hipStream_t s);
 
 hipError_t launch_score_backward(const DevIndex &ix, const DevQueries &q, const int64_t *cand,
-                                 int32_t n_cand, const float *grad, float *gq, float *gx,
-                                 hipStream_t s);
+                                 int32_t n_cand, int32_t max_qnnz, const float *grad, float *gq,
+                                 float *gx, hipStream_t s);
 
 }  // namespace sindi

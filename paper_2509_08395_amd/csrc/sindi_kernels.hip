@@ -116,18 +116,6 @@ __device__ __forceinline__ void lds_add_i32(int32_t *p, int32_t v)
                            __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-__device__ __forceinline__ float wave_sum(float v)
-{
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, kWave);
-    return v;
-}
-
-__device__ __forceinline__ uint32_t hash_slot(int32_t id, int lg)
-{
-    return ((uint32_t)id * 0x9E3779B1u) >> (32 - lg);
-}
-
 // Exclusive scan of one value per thread over the block; `total` = sum.
 template <int NT>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *wsum, uint32_t &total)
@@ -1441,61 +1429,6 @@ __global__ __launch_bounds__(1024) void k_collect_failed(const int32_t *status,
 }
 
 // ------------------------------------------------------------------ finalize
-struct QueryHash {
-    int32_t *id;
-    float *val;
-    int32_t *pos;
-    int lg;
-};
-
-// Full (unpruned) query row into an open-addressing LDS table.
-__device__ void build_query_hash(const DevQueries &q, int64_t a, int64_t b, QueryHash h)
-{
-    const int H = 1 << h.lg;
-    for (int i = threadIdx.x; i < H; i += blockDim.x) h.id[i] = -1;
-    __syncthreads();
-    for (int64_t e = a + threadIdx.x; e < b; e += blockDim.x) {
-        const int32_t id = q.indices[e];
-        uint32_t s = hash_slot(id, h.lg);
-        while (atomicCAS(&h.id[s], -1, id) != -1) s = (s + 1) & (uint32_t)(H - 1);
-        h.val[s] = q.values[e];
-        if (h.pos) h.pos[s] = (int32_t)(e - a);
-    }
-    __syncthreads();
-}
-
-__device__ __forceinline__ int probe(const QueryHash &h, int32_t id)
-{
-    const uint32_t mask = (1u << h.lg) - 1u;
-    uint32_t s = hash_slot(id, h.lg);
-    for (;;) {
-        const int32_t k = h.id[s];
-        if (k == id) return (int)s;
-        if (k == -1) return -1;
-        s = (s + 1) & mask;
-    }
-}
-
-__host__ __device__ __forceinline__ int hash_lg(int64_t n)
-{
-    int lg = 6;
-    while ((1ll << lg) < 2 * n) ++lg;
-    return lg;
-}
-
-// delta(q, x_doc) in FP32 by one wave over the document's row.
-__device__ __forceinline__ float wave_dot(const DevIndex &ix, const QueryHash &h, uint32_t doc)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t ra = ix.indptr[doc], rb = ix.indptr[doc + 1];
-    float acc = 0.0f;
-    for (int64_t e = ra + lane; e < rb; e += kWave) {
-        const int s = probe(h, ix.indices[e]);
-        if (s >= 0) acc = fmaf(h.val[s], ix.values[e], acc);
-    }
-    return wave_sum(acc);
-}
-
 // The full (unpruned) query row in LDS: 2^lg buckets of two entries {term, term, value, value},
 // empty terms -1.  A term sits in its home bucket or, where that is full, in the next one with
 // room; `spill` says whether any term did that.  With eight buckets per term few tables spill
@@ -1523,7 +1456,9 @@ __device__ __forceinline__ uint32_t home_bucket(int32_t id, int lg)
 }
 
 // Fill the table from the query row [a, b): every thread of the workgroup, two barriers.
-// s_spill: a word of LDS.
+// s_spill: a word of LDS.  With POS the buckets hold the terms' positions in the row instead of
+// their values.
+template <bool POS>
 __device__ __forceinline__ void build_table(const DevQueries &q, int64_t a, int64_t b,
                                             QueryTable &t, uint32_t *s_spill)
 {
@@ -1533,13 +1468,13 @@ __device__ __forceinline__ void build_table(const DevQueries &q, int64_t a, int6
     __syncthreads();
     for (int64_t e = a + threadIdx.x; e < b; e += blockDim.x) {
         const int32_t id = q.indices[e];
-        const float v = q.values[e];
+        const int32_t v = POS ? (int32_t)(e - a) : __float_as_int(q.values[e]);
         const uint32_t home = home_bucket(id, t.lg) >> 4;
         for (uint32_t i = home;; i = (i + 1) & (uint32_t)(B - 1)) {
             int32_t *k = reinterpret_cast<int32_t *>(t.b + i);
             const int s = atomicCAS(k, -1, id) == -1 ? 0 : (atomicCAS(k + 1, -1, id) == -1 ? 1 : 2);
             if (s < 2) {
-                k[2 + s] = __float_as_int(v);
+                k[2 + s] = v;
                 if (i != home) *s_spill = 1u;
                 break;
             }
@@ -1586,6 +1521,62 @@ __device__ __forceinline__ float wave_sum4(float a, float b, float c, float d)
     s += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x122, 0xF, 0xF, false));
     s += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x121, 0xF, 0xF, false));
     return s;
+}
+
+// The bounds (uniform) and the first two 64-entry rounds of four corpus rows, all loads in
+// flight together; lanes past a row's end hold term -2.
+struct Rows4 {
+    int64_t at[4];
+    int32_t n[4];
+    int32_t id[4][2];
+    float x[4][2];
+    __device__ __forceinline__ void load(const DevIndex &ix, const int64_t (&ra)[4],
+                                         const int64_t (&rb)[4])
+    {
+        const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            at[j] = uni64(ra[j]);
+            n[j] = (int32_t)uni((uint32_t)(rb[j] - ra[j]));
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                id[j][r] = -2;
+                x[j][r] = 0.0f;
+                if (r * kWave + lane < n[j]) {
+                    id[j][r] = (ix.indices + at[j])[r * kWave + lane];
+                    x[j][r] = (ix.values + at[j])[r * kWave + lane];
+                }
+            }
+        }
+    }
+    // delta(q, x_j) in FP32 of the four rows: each lane over entries lane, lane + 64, ... of the
+    // row in order, then summed across the wave (as wave_sum4 leaves them)
+    __device__ __forceinline__ float dot(const DevIndex &ix, const QueryTable &tb) const
+    {
+        const int lane = threadIdx.x & (kWave - 1);
+        float acc[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            acc[j] = 0.0f;
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                float v;
+                if (table_get(tb, id[j][r], v)) acc[j] = fmaf(v, x[j][r], acc[j]);
+            }
+            for (int32_t p = 2 * kWave + lane; p < n[j]; p += kWave) {
+                float v;
+                if (table_get(tb, (ix.indices + at[j])[p], v))
+                    acc[j] = fmaf(v, (ix.values + at[j])[p], acc[j]);
+            }
+        }
+        return wave_sum4(acc[0], acc[1], acc[2], acc[3]);
+    }
+};
+// The row whose sum wave_sum4 leaves in this lane.
+__device__ __forceinline__ int sum4_row()
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    return (lane >> 5) + 2 * ((lane >> 4) & 1);
 }
 
 // LDS sizes: P = the power of two at or above need keys, a rerank table of
@@ -1781,7 +1772,7 @@ __global__ __launch_bounds__(kFinThreads) void k_rerank(DevIndex ix, DevQueries 
                                                         int32_t *status)
 {
     constexpr int NW = kFinThreads / kWave, EPW = kRerankPerWave;
-    static_assert(EPW == 4, "wave_sum4");
+    static_assert(EPW == 4, "Rows4");
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t s_spill;
     const int lane = threadIdx.x & (kWave - 1);
@@ -1818,52 +1809,18 @@ __global__ __launch_bounds__(kFinThreads) void k_rerank(DevIndex ix, DevQueries 
     // together, so the entries' memory latencies overlap.
     const int32_t first = (int32_t)blockIdx.y * groups * NW;
     bounds((first + wave) * EPW);
-    build_table(q, qa, qb, tb, &s_spill);
+    build_table<false>(q, qa, qb, tb, &s_spill);
     for (int g = 0; g < groups; ++g) {
         const int32_t c0 = (first + g * NW + wave) * EPW;
         if (c0 >= need) break;  // wave-uniform; no barrier follows
-        int32_t id[EPW][2];
-        float xv[EPW][2];
-        int64_t pa[EPW];
-        int32_t pn[EPW];
-        uint32_t plo[EPW];
-#pragma unroll
-        for (int j = 0; j < EPW; ++j) {
-            pa[j] = uni64(ra[j]);
-            pn[j] = (int32_t)uni((uint32_t)(rb[j] - ra[j]));
-            plo[j] = uni(lo[j]);
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                id[j][r] = -2;
-                xv[j][r] = 0.0f;
-                if (r * kWave + lane < pn[j]) {
-                    id[j][r] = (ix.indices + pa[j])[r * kWave + lane];
-                    xv[j][r] = (ix.values + pa[j])[r * kWave + lane];
-                }
-            }
-        }
+        Rows4 rows;
+        rows.load(ix, ra, rb);
+        const uint32_t l0 = lo[0], l1 = lo[1], l2 = lo[2], l3 = lo[3];
         // the next group's keys and bounds arrive while this one's rows are looked up
         if (g + 1 < groups) bounds(c0 + NW * EPW);
-        // delta(q, x_doc) in FP32, each lane over entries lane, lane + 64, ... of the
-        // row in order, then summed across the wave
-        float acc[EPW];
-#pragma unroll
-        for (int j = 0; j < EPW; ++j) {
-            acc[j] = 0.0f;
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                float v;
-                if (table_get(tb, id[j][r], v)) acc[j] = fmaf(v, xv[j][r], acc[j]);
-            }
-            for (int32_t p = 2 * kWave + lane; p < pn[j]; p += kWave) {
-                float v;
-                if (table_get(tb, (ix.indices + pa[j])[p], v))
-                    acc[j] = fmaf(v, (ix.values + pa[j])[p], acc[j]);
-            }
-        }
-        const float sc = wave_sum4(acc[0], acc[1], acc[2], acc[3]);
-        const int j = (lane >> 5) + 2 * ((lane >> 4) & 1);  // the entry whose sum the lane has
-        const uint32_t l = j == 0 ? plo[0] : (j == 1 ? plo[1] : (j == 2 ? plo[2] : plo[3]));
+        const float sc = rows.dot(ix, tb);
+        const int j = sum4_row();
+        const uint32_t l = j == 0 ? l0 : (j == 1 ? l1 : (j == 2 ? l2 : l3));
         if ((lane & 15) == 0 && c0 + j < need) e[c0 + j] = ((uint64_t)ord_f32(sc) << 32) | l;
     }
 }
@@ -1885,71 +1842,121 @@ __global__ __launch_bounds__(kFinThreads) void k_topk(const int32_t *slot_q, int
 }
 
 // ------------------------------------------------------------------ pair scores
+// Row bounds of the candidates [c0, c0 + 4) of query b; ids outside the corpus give empty rows.
+__device__ __forceinline__ void cand_bounds(const DevIndex &ix, const int64_t *cand, int64_t n_cand,
+                                            int64_t b, int64_t c0, int64_t (&ra)[4], int64_t (&rb)[4])
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        ra[j] = rb[j] = 0;
+        if (c0 + j < n_cand) {
+            const int64_t d = cand[b * n_cand + c0 + j];
+            if (d >= 0 && d < ix.n_docs) {
+                ra[j] = ix.indptr[d];
+                rb[j] = ix.indptr[d + 1];
+            }
+        }
+    }
+}
+
+// Scores of listed pairs: grid (query, candidate block), four candidates per wave at a time,
+// `groups` times, as k_rerank does.  Bound by the chain of id, row bounds and row loads, so the
+// candidates of a query are split over workgroups until the chip is full: 256 queries x 100
+// candidates of ~180 entries take 11 us (145 us with one workgroup per query).
 __global__ __launch_bounds__(kFinThreads) void k_score_forward(DevIndex ix, DevQueries q,
-                                                               const int64_t *cand,
-                                                               int32_t n_cand, float *out)
+                                                               const int64_t *cand, int32_t n_cand,
+                                                               int32_t tlg, int32_t groups, float *out)
 {
     constexpr int NW = kFinThreads / kWave;
     extern __shared__ __align__(16) unsigned char smem[];
-    int32_t *hid = reinterpret_cast<int32_t *>(smem);
-    float *hval = reinterpret_cast<float *>(hid + kQueryHash);
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    __shared__ uint32_t s_spill;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = (int)uni((uint32_t)threadIdx.x / kWave);
     const int64_t b = blockIdx.x;
-    const int64_t qa = q.indptr[b], qb = q.indptr[b + 1];
-    const QueryHash h{hid, hval, nullptr, hash_lg(qb - qa)};
-    build_query_hash(q, qa, qb, h);
-    for (int c = wave; c < n_cand; c += NW) {
-        const int64_t d = cand[b * n_cand + c];
-        float s = 0.0f;
-        if (d >= 0 && d < ix.n_docs) s = wave_dot(ix, h, (uint32_t)d);
-        if (lane == 0) out[b * n_cand + c] = s;
+    QueryTable tb{reinterpret_cast<int4 *>(smem), tlg, 0u};
+    const int64_t first = (int64_t)blockIdx.y * groups * NW;
+    int64_t ra[4], rb[4];
+    cand_bounds(ix, cand, n_cand, b, (first + wave) * 4, ra, rb);
+    build_table<false>(q, q.indptr[b], q.indptr[b + 1], tb, &s_spill);
+    for (int32_t g = 0; g < groups; ++g) {
+        const int64_t c0 = (first + (int64_t)g * NW + wave) * 4;
+        if (c0 >= n_cand) break;  // wave-uniform; no barrier follows
+        Rows4 rows;
+        rows.load(ix, ra, rb);
+        if (g + 1 < groups) cand_bounds(ix, cand, n_cand, b, c0 + NW * 4, ra, rb);
+        const float s = rows.dot(ix, tb);
+        const int j = sum4_row();
+        if ((lane & 15) == 0 && c0 + j < n_cand) out[b * n_cand + c0 + j] = s;
     }
 }
 
 // Gradients of s[b][c] = delta(q_b, x_c): every common dimension t adds
 // G[b][c] * x_c[t] to the query entry and G[b][c] * q_b[t] to the document
-// entry.  Query-side sums stay in LDS (one workgroup per query); document
-// entries can be shared by several queries, so they take global atomics.
+// entry.  Grid and row loads as in k_score_forward.  A workgroup sums its candidates' query side
+// in LDS and adds it to the query's gradient; queries' workgroups and document entries shared by
+// several queries meet in global atomics.  256 x 100 candidates: 28 us (164 us with one workgroup
+// per query).
 __global__ __launch_bounds__(kFinThreads) void k_score_backward(
-    DevIndex ix, DevQueries q, const int64_t *cand, int32_t n_cand, const float *grad, float *gq,
-    float *gx)
+    DevIndex ix, DevQueries q, const int64_t *cand, int32_t n_cand, int32_t tlg, int32_t groups,
+    const float *grad, float *gq, float *gx)
 {
     constexpr int NW = kFinThreads / kWave;
     extern __shared__ __align__(16) unsigned char smem[];
-    int32_t *hid = reinterpret_cast<int32_t *>(smem);
-    float *hval = reinterpret_cast<float *>(hid + kQueryHash);
-    int32_t *hpos = reinterpret_cast<int32_t *>(hval + kQueryHash);
-    float *gacc = reinterpret_cast<float *>(hpos + kQueryHash);
-    uint32_t *gtouch = reinterpret_cast<uint32_t *>(gacc + kQueryHash / 2);
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    __shared__ uint32_t s_spill;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = (int)uni((uint32_t)threadIdx.x / kWave);
     const int64_t b = blockIdx.x;
     const int64_t qa = q.indptr[b], qb = q.indptr[b + 1];
     const int n = (int)(qb - qa);
-    const QueryHash h{hid, hval, hpos, hash_lg(n)};
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    QueryTable tb{reinterpret_cast<int4 *>(smem), tlg, 0u};
+    float *qv = reinterpret_cast<float *>(tb.b + (1 << tlg));  // [n] the query's values
+    float *gacc = qv + n;                                      // [n] its gradient's sums
+    uint32_t *gtouch = reinterpret_cast<uint32_t *>(gacc + n); // [n] entries that got any
+    const int64_t first = (int64_t)blockIdx.y * groups * NW;
+    int64_t ra[4], rb[4];
+    cand_bounds(ix, cand, n_cand, b, (first + wave) * 4, ra, rb);
+    for (int i = threadIdx.x; i < n; i += kFinThreads) {
+        qv[i] = q.values[qa + i];
         gacc[i] = 0.0f;
         gtouch[i] = 0u;
     }
-    build_query_hash(q, qa, qb, h);
-    for (int c = wave; c < n_cand; c += NW) {
-        const int64_t d = cand[b * n_cand + c];
-        if (d < 0 || d >= ix.n_docs) continue;
-        const float g = grad[b * n_cand + c];
-        const int64_t ra = ix.indptr[d], rb = ix.indptr[d + 1];
-        for (int64_t e = ra + lane; e < rb; e += kWave) {
-            const int s = probe(h, ix.indices[e]);
-            if (s < 0) continue;
+    build_table<true>(q, qa, qb, tb, &s_spill);
+    for (int32_t g = 0; g < groups; ++g) {
+        const int64_t c0 = (first + (int64_t)g * NW + wave) * 4;
+        if (c0 >= n_cand) break;  // wave-uniform
+        Rows4 rows;
+        rows.load(ix, ra, rb);
+        float gr[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) gr[j] = c0 + j < n_cand ? grad[b * n_cand + c0 + j] : 0.0f;
+        if (g + 1 < groups) cand_bounds(ix, cand, n_cand, b, c0 + NW * 4, ra, rb);
+        auto entry = [&](int j, int32_t id, float x, int32_t p) {
+            float at;
+            if (!table_get(tb, id, at)) return;
+            const int i = __float_as_int(at);
             if (gq) {
-                lds_add(&gacc[hpos[s]], g * ix.values[e]);
-                gtouch[hpos[s]] = 1u;
+                lds_add(&gacc[i], gr[j] * x);
+                gtouch[i] = 1u;
             }
-            if (gx) atomicAdd(&gx[e], g * hval[s]);
+            if (gx) atomicAdd(&gx[rows.at[j] + p], gr[j] * qv[i]);
+        };
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+#pragma unroll
+            for (int r = 0; r < 2; ++r) entry(j, rows.id[j][r], rows.x[j][r], r * kWave + lane);
+            for (int32_t p = 2 * kWave + lane; p < rows.n[j]; p += kWave)
+                entry(j, (ix.indices + rows.at[j])[p], (ix.values + rows.at[j])[p], p);
         }
     }
+    if (!gq) return;
     __syncthreads();
-    if (gq)
-        for (int i = threadIdx.x; i < n; i += blockDim.x)
-            if (gtouch[i]) gq[qa + i] += gacc[i];
+    for (int i = threadIdx.x; i < n; i += kFinThreads)
+        if (gtouch[i]) {
+            if (gridDim.y == 1)
+                gq[qa + i] += gacc[i];
+            else
+                atomicAdd(&gq[qa + i], gacc[i]);
+        }
 }
 
 template <typename F>
@@ -2195,28 +2202,48 @@ hipError_t launch_finalize(const DevIndex &ix, const DevQueries &q, const int32_
     return hipGetLastError();
 }
 
+namespace {
+// Row groups per wave of a pair-score launch: fewer where the workgroups would not fill the
+// chip, more where the grid's second dimension would not hold them.
+int32_t score_groups(int64_t n_rows, int64_t n_cand)
+{
+    constexpr int64_t kPer = kFinThreads / kWave * 4;
+    int64_t g = kRerankGroups;
+    while (g > 1 && n_rows * ((n_cand + kPer * g - 1) / (kPer * g)) < kRerankFill) g >>= 1;
+    while ((n_cand + kPer * g - 1) / (kPer * g) > 65535) g <<= 1;
+    return (int32_t)g;
+}
+dim3 score_grid(int64_t n_rows, int64_t n_cand, int32_t groups)
+{
+    const int64_t per = (int64_t)(kFinThreads / kWave) * 4 * groups;
+    return dim3((unsigned)n_rows, (unsigned)((n_cand + per - 1) / per));
+}
+}  // namespace
+
 hipError_t launch_score_forward(const DevIndex &ix, const DevQueries &q, const int64_t *cand,
-                                int32_t n_cand, float *out, hipStream_t s)
+                                int32_t n_cand, int32_t max_qnnz, float *out, hipStream_t s)
 {
     if (q.n_rows == 0 || n_cand == 0) return hipSuccess;
-    const size_t lds = (size_t)kQueryHash * 8;
+    const int32_t tlg = table_lg(max_qnnz), groups = score_groups(q.n_rows, n_cand);
+    const size_t lds = (size_t)16 << tlg;
     hipError_t e = set_lds(k_score_forward, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_score_forward, dim3((unsigned)q.n_rows), dim3(kFinThreads), lds, s, ix,
-                       q, cand, n_cand, out);
+    hipLaunchKernelGGL(k_score_forward, score_grid(q.n_rows, n_cand, groups), dim3(kFinThreads),
+                       lds, s, ix, q, cand, n_cand, tlg, groups, out);
     return hipGetLastError();
 }
 
 hipError_t launch_score_backward(const DevIndex &ix, const DevQueries &q, const int64_t *cand,
-                                 int32_t n_cand, const float *grad, float *gq, float *gx,
-                                 hipStream_t s)
+                                 int32_t n_cand, int32_t max_qnnz, const float *grad, float *gq,
+                                 float *gx, hipStream_t s)
 {
-    if (q.n_rows == 0 || n_cand == 0) return hipSuccess;
-    const size_t lds = (size_t)kQueryHash * 12 + (size_t)(kQueryHash / 2) * 8;
+    if (q.n_rows == 0 || n_cand == 0 || (!gq && !gx)) return hipSuccess;
+    const int32_t tlg = table_lg(max_qnnz), groups = score_groups(q.n_rows, n_cand);
+    const size_t lds = ((size_t)16 << tlg) + (size_t)max_qnnz * 12;
     hipError_t e = set_lds(k_score_backward, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_score_backward, dim3((unsigned)q.n_rows), dim3(kFinThreads), lds, s, ix,
-                       q, cand, n_cand, grad, gq, gx);
+    hipLaunchKernelGGL(k_score_backward, score_grid(q.n_rows, n_cand, groups), dim3(kFinThreads),
+                       lds, s, ix, q, cand, n_cand, tlg, groups, grad, gq, gx);
     return hipGetLastError();
 }
 

@@ -71,3 +71,36 @@ def test_rerank_table_sizes(sindi):
         # at most 5 additions on a lane and 6 across the wave, each within 2^-24 of the partial sums
         tol = 11 * 2.0 ** -24 * oracle.pair_scores(mag(corpus), mag(sub), qi, ids.reshape(-1))
         assert (np.abs(sc.reshape(-1) - ref) <= tol + 1e-30).all()
+
+
+# ------------------------------------------------------------------ pair scores
+@pytest.mark.parametrize("n_cand", [1, 3, 16, 17, 130])
+@pytest.mark.parametrize("lens", [[0, 1, 8, 9, 64, 65, 129], [512, 513], [4096], [12] * 700])
+def test_pair_scores_and_gradients_at_split_edges(sindi, n_cand, lens):
+    """Scores and gradients against the FP64 oracle, each within the rounding of its additions:
+    one to many workgroups per query, every table size, rows around every 64-entry round, ids
+    outside the corpus and candidates shared by several queries."""
+    rng = np.random.default_rng(7)
+    vocab, u = 5_000, 2.0 ** -24
+    corpus = _rows(rng, [0, 1, 63, 64, 65, 127, 128, 129, 192, 300] * 9, vocab)
+    q = _rows(rng, lens, vocab)
+    nq, nd = q.n_rows, corpus.n_rows
+    cand = rng.integers(-1, nd, (nq, n_cand))
+    g = rng.standard_normal((nq, n_cand)).astype(np.float32)
+    idx = sindi.Index(corpus, alpha=0.5, window=100)
+    dq, tc = sindi.DeviceCsr.from_host(q), torch.from_numpy(cand).cuda()
+    xv = torch.from_numpy(corpus.values).cuda()
+    s = _np(idx.score(dq, tc, doc_values=xv))
+    mag = lambda m: synth.Csr(m.indptr, m.indices, np.abs(m.values), m.n_cols)
+    qi = np.repeat(np.arange(nq), n_cand)
+    ok = cand.reshape(-1) >= 0
+    ref = np.where(ok, oracle.pair_scores(corpus, q, qi, np.maximum(cand, 0).reshape(-1)), 0.0)
+    size = oracle.pair_scores(mag(corpus), mag(q), qi, np.maximum(cand, 0).reshape(-1))
+    assert (np.abs(s.reshape(-1) - ref) <= 11 * u * size + 1e-30).all()
+    gq, gx = torch.zeros_like(dq.values), torch.zeros_like(xv)
+    idx.score_backward(dq, tc, torch.from_numpy(g).cuda(), gq, gx, doc_values=xv)
+    rq, rx = oracle.score_grad(corpus, q, cand, g.astype(np.float64))
+    sq, sx = oracle.score_grad(mag(corpus), mag(q), cand, np.abs(g).astype(np.float64))
+    m = np.bincount(cand.reshape(-1)[ok], minlength=1).max() if ok.any() else 0
+    assert (np.abs(_np(gq) - rq) <= (n_cand + 3) * u * sq + 1e-30).all()
+    assert (np.abs(_np(gx) - rx) <= (m + 2) * u * sx + 1e-30).all()
