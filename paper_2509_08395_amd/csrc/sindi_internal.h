@@ -56,8 +56,7 @@ struct DevCoarse {
 };
 
 constexpr int kAccThreads = 512;       // accumulate kernel workgroup
-constexpr int kFinThreads = 256;       // finalize, rerank and top-k kernels
-constexpr int kThetaThreads = 1024;    // threshold kernel (one radix select per query)
+constexpr int kFinThreads = 256;       // rerank, top-k and pair-score kernels
 constexpr int kGammaMax = 4096;        // largest reorder pool
 constexpr int kQueryHash = 8192;       // rerank hash slots (query nnz <= kQueryHash / 2)
 constexpr int kEntryBlock = 512;       // (query, term) entries merged per pass in the accumulate kernel

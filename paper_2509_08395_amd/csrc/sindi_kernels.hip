@@ -40,6 +40,8 @@ namespace {
 constexpr int kWave = 64;
 constexpr int kRerankPerWave = 4;  // pool entries one rerank wave scores at a time
 constexpr int kRerankGroups = 4;   // most such groups per wave (one query table per workgroup)
+constexpr int kRankSort = 256;     // most keys put in order by counting the larger ones
+constexpr int kTopkRegs = 8;       // pool keys per thread of a selecting k_topk
 constexpr int64_t kRerankFill = 2048;  // rerank workgroups that fill the chip
 constexpr int kMaxSeg = kQueryHash / 2 / kWave;  // 64-term segments of the longest query
 constexpr int kPrepWaves = 8;      // query rows per prep workgroup, one wave each
@@ -141,51 +143,91 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *wsum, 
     return off + x - v;
 }
 
-// r-th largest (1-based) of n keys, by most-significant-digit radix select:
-// one 256-bin histogram per byte of the key, restricted to the keys that
-// share the digits chosen so far.  Requires 1 <= r <= n.
-template <typename K, typename Load>
-__device__ K block_select(int64_t n, int64_t r, Load load, uint32_t *hist, int *s_digit,
-                          int64_t *s_need)
+// Inclusive prefix sum over the wave in lane order: within each row of 16
+// lanes by four shifted adds (DPP row_shr 1, 2, 4, 8; lanes shifted in from
+// outside the row read 0), then each row adds the totals of the rows below.
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
 {
-    K prefix = 0, mask = 0;
-    int64_t need = r;
-    for (int shift = (int)sizeof(K) * 8 - 8; shift >= 0; shift -= 8) {
-        for (int i = threadIdx.x; i < 256; i += blockDim.x) hist[i] = 0u;
+    const int lane = threadIdx.x & (kWave - 1);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);
+    const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)x, 15);
+    const uint32_t r1 = (uint32_t)__builtin_amdgcn_readlane((int)x, 31);
+    const uint32_t r2 = (uint32_t)__builtin_amdgcn_readlane((int)x, 47);
+    return x + (lane >= 16 ? r0 : 0u) + (lane >= 32 ? r1 : 0u) + (lane >= 48 ? r2 : 0u);
+}
+
+// LDS of a block_select.
+struct SelectLds {
+    uint32_t hist[2][256];
+    uint64_t differ[16];  // per wave: the bits in which its keys differ from the first key
+    uint32_t digit, need, count;
+};
+
+// Radix select over the workgroup's keys: each(f) calls f on every key the calling thread owns,
+// `any` is one of the keys (the same on every thread), 1 <= r <= number of keys.  Returns a bound
+// t: the keys at or above t are the r largest (more only where keys tie at t, which is then the
+// r-th largest key itself).  *exact: t is that key.
+//
+// The digits start at the highest bit in which keys differ (scores share their upper bits) and
+// stop once the digits chosen so far hold just the keys still needed, so 64-bit keys take two or
+// three passes of 8 bits, not eight, each of two barriers.
+template <int NT, typename K, typename Each>
+__device__ __forceinline__ K block_select(K any, int64_t r, Each each, SelectLds &L, bool *exact)
+{
+    static_assert(NT / kWave <= 16 && NT >= 256, "SelectLds");
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    K x = 0;
+    each([&](K k) { x |= k ^ any; });
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) x |= __shfl_xor(x, m, kWave);
+    if (lane == 0) L.differ[tid / kWave] = (uint64_t)x;
+    if (tid < 256) L.hist[0][tid] = 0u;
+    __syncthreads();
+    uint64_t diff = 0;
+#pragma unroll
+    for (int i = 0; i < NT / kWave; ++i) diff |= L.differ[i];
+    int top = diff ? 64 - __clzll((long long)diff) : 0;  // bits still undecided
+    K mask = top >= (int)sizeof(K) * 8 ? (K)0 : (K)(~(K)0 << top);
+    K prefix = any & mask;
+    uint32_t need = (uint32_t)r;
+    bool whole = false;  // the digits so far hold just the keys still needed
+    for (int cur = 0; top > 0 && !whole; cur ^= 1) {
+        const int shift = max(0, top - 8);
+        const uint32_t dmask = (1u << (top - shift)) - 1u;
+        if (tid < 256) L.hist[cur ^ 1][tid] = 0u;
+        each([&](K k) {
+            if ((k & mask) == prefix) atomicAdd(&L.hist[cur][(uint32_t)(k >> shift) & dmask], 1u);
+        });
         __syncthreads();
-        for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-            K key = load(i);
-            if ((key & mask) == prefix) atomicAdd(&hist[(uint32_t)(key >> shift) & 255u], 1u);
-        }
-        __syncthreads();
-        if (threadIdx.x < kWave) {
+        if (tid < kWave) {
             // digit of the need-th key: lane l holds digits 255 - 4l .. 252 - 4l; a prefix
             // sum over the lanes counts the keys with larger digits
-            const int l = threadIdx.x;
             uint32_t h[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) h[u] = hist[255 - 4 * l - u];
+            for (int u = 0; u < 4; ++u) h[u] = L.hist[cur][255 - 4 * tid - u];
             const uint32_t tot = h[0] + h[1] + h[2] + h[3];
-            uint32_t incl = tot;
-#pragma unroll
-            for (int d = 1; d < kWave; d <<= 1) {
-                const uint32_t y = __shfl_up(incl, d, kWave);
-                if (l >= d) incl += y;
-            }
-            int64_t acc = (int64_t)(incl - tot);
-            if (acc < need && (int64_t)incl >= need) {
+            const uint32_t incl = wave_incl_scan(tot);
+            uint32_t acc = incl - tot;
+            if (acc < need && incl >= need) {
                 int u = 0;
-                while (u < 3 && acc + (int64_t)h[u] < need) acc += h[u++];
-                *s_digit = 255 - 4 * l - u;
-                *s_need = need - acc;
+                while (u < 3 && acc + h[u] < need) acc += h[u++];
+                L.digit = (uint32_t)(255 - 4 * tid - u);
+                L.need = need - acc;
+                L.count = h[u];
             }
         }
         __syncthreads();
-        prefix |= (K)(*s_digit) << shift;
-        mask |= (K)0xFF << shift;
-        need = *s_need;
-        __syncthreads();
+        prefix |= (K)L.digit << shift;
+        mask |= (K)dmask << shift;
+        need = L.need;
+        whole = L.count == need;
+        top = shift;
     }
+    if (exact) *exact = top == 0;
+    __syncthreads();  // L may be used again
     return prefix;
 }
 
@@ -1036,22 +1078,6 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))
     }
 }
 
-// Inclusive prefix sum over the wave in lane order: within each row of 16
-// lanes by four shifted adds (DPP row_shr 1, 2, 4, 8; lanes shifted in from
-// outside the row read 0), then each row adds the totals of the rows below.
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);
-    const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)x, 15);
-    const uint32_t r1 = (uint32_t)__builtin_amdgcn_readlane((int)x, 31);
-    const uint32_t r2 = (uint32_t)__builtin_amdgcn_readlane((int)x, 47);
-    return x + (lane >= 16 ? r0 : 0u) + (lane >= 32 ? r1 : 0u) + (lane >= 48 ? r2 : 0u);
-}
-
 // The single-query form of k_accumulate (same grid, same scores, same
 // read-out).  Every wave lays out the tile's chunks itself: the query's terms
 // are taken 64 at a time (a segment, one list per lane), and a wave-wide
@@ -1371,16 +1397,46 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))
 // produce bitwise identical scores (integer sums), so every sampled document
 // at or above theta is kept again by the scoring pass.  The finalize kernel
 // verifies the result (at least gamma candidates kept).
-__global__ __launch_bounds__(kThetaThreads) void k_theta(const float *maxima, int64_t n_m,
-                                                       int64_t rank, float *theta)
+//
+// Bound by the barriers of its select; a thread keeps up to R maxima in registers.  One query
+// (4,096 maxima): 4.7 us; 7,000 queries: 40 us (7.8 and 150 us with four fixed digits from memory).
+template <int NT, int R>
+__global__ __launch_bounds__(NT) void k_theta(const float *maxima, int64_t n_m, int64_t rank,
+                                              float *theta)
 {
-    __shared__ uint32_t hist[256];
-    __shared__ int s_digit;
-    __shared__ int64_t s_need;
+    __shared__ SelectLds L;
+    __shared__ uint32_t s_min;
     const float *mx = maxima + (size_t)blockIdx.x * (size_t)n_m;
-    const uint32_t key = block_select<uint32_t>(
-        n_m, rank, [&](int64_t i) { return ord_f32(mx[i]); }, hist, &s_digit, &s_need);
-    if (threadIdx.x == 0) {
+    const int tid = threadIdx.x;
+    if (tid == 0) s_min = 0xFFFFFFFFu;
+    auto select = [&](auto each) {
+        bool exact;
+        const uint32_t t = block_select<NT, uint32_t>(ord_f32(mx[0]), rank, each, L, &exact);
+        if (exact) return t;
+        uint32_t mn = 0xFFFFFFFFu;  // the least key at or above the bound is the rank-th largest
+        each([&](uint32_t k) { mn = k >= t ? min(mn, k) : mn; });
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) mn = min(mn, (uint32_t)__shfl_xor(mn, m, kWave));
+        if ((tid & (kWave - 1)) == 0) atomicMin(&s_min, mn);
+        __syncthreads();
+        return s_min;
+    };
+    uint32_t key;
+    if (n_m <= NT * R) {
+        uint32_t k[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) k[j] = j * NT + tid < n_m ? ord_f32(mx[j * NT + tid]) : 0u;
+        key = select([&](auto f) {
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+                if (j * NT + tid < n_m) f(k[j]);
+        });
+    } else {
+        key = select([&](auto f) {
+            for (int64_t i = tid; i < n_m; i += NT) f(ord_f32(mx[i]));
+        });
+    }
+    if (tid == 0) {
         const float th = unord_f32(key);
         theta[blockIdx.x] = th > -INFINITY ? th : -INFINITY;
     }
@@ -1588,15 +1644,36 @@ __host__ __device__ inline int32_t pow2_at_least(int32_t n)
     return p;
 }
 
-// Sort need keys (score bits, then inverted id) in LDS descending and write
-// the first k as (id, score) to the query's output row, padded with (-1, -inf).
-__device__ void sort_and_write(uint64_t *keys, int32_t need, int32_t k, int32_t row,
+// The m keys (distinct) in LDS, descending, as (id, score) into the first k places of the query's
+// output row, padded with (-1, -inf).  Up to kRankSort keys each find their place by counting the
+// larger ones, with no further barrier; more are sorted (bitonic; keys has pow2_at_least(m) words).
+template <int NT>
+__device__ void sort_and_write(uint64_t *keys, int32_t m, int32_t k, int32_t row,
                                int64_t *out_ids, float *out_scores)
 {
-    constexpr int NT = kFinThreads;
     const int tid = threadIdx.x;
-    const int32_t P = pow2_at_least(need);
-    for (int i = need + tid; i < P; i += NT) keys[i] = 0ull;
+    int64_t *ids = out_ids + (size_t)row * (size_t)k;
+    float *sc = out_scores + (size_t)row * (size_t)k;
+    for (int r = m + tid; r < k; r += NT) {
+        ids[r] = -1;
+        sc[r] = -INFINITY;
+    }
+    if (m <= kRankSort) {
+        __syncthreads();
+        for (int i = tid; i < m; i += NT) {
+            const uint64_t key = keys[i];
+            int32_t rank = 0;
+#pragma unroll 4
+            for (int j = 0; j < m; ++j) rank += keys[j] > key ? 1 : 0;
+            if (rank < k) {
+                ids[rank] = (int64_t)key_doc(key);
+                sc[rank] = key_score(key);
+            }
+        }
+        return;
+    }
+    const int32_t P = pow2_at_least(m);
+    for (int i = m + tid; i < P; i += NT) keys[i] = 0ull;
     __syncthreads();
     for (int kk = 2; kk <= P; kk <<= 1) {
         for (int j = kk >> 1; j > 0; j >>= 1) {
@@ -1614,37 +1691,45 @@ __device__ void sort_and_write(uint64_t *keys, int32_t need, int32_t k, int32_t 
             __syncthreads();
         }
     }
-    for (int r = tid; r < k; r += NT) {
-        const size_t o = (size_t)row * (size_t)k + r;
-        if (r < need) {
-            out_ids[o] = (int64_t)key_doc(keys[r]);
-            out_scores[o] = key_score(keys[r]);
-        } else {
-            out_ids[o] = -1;
-            out_scores[o] = -INFINITY;
-        }
+    for (int r = tid; r < min(m, k); r += NT) {
+        ids[r] = (int64_t)key_doc(keys[r]);
+        sc[r] = key_score(keys[r]);
     }
+}
+
+// The next place in an LDS list for every lane with `take`: one atomic per wave.
+__device__ __forceinline__ uint32_t wave_place(uint32_t *n, bool take)
+{
+    const uint64_t m = __ballot(take);
+    uint32_t base = 0;
+    if (m == 0) return 0;
+    const int first = __ffsll((unsigned long long)m) - 1;
+    if ((int)(threadIdx.x & (kWave - 1)) == first) base = atomicAdd(n, (uint32_t)__popcll(m));
+    return (uint32_t)__builtin_amdgcn_readlane((int)base, first) + lanes_below(m);
 }
 
 // One workgroup per query slot: the exact top-need of its coarse candidates
 // (with the zero-score documents the scoring pass left implicit).  Without a
 // rerank it sorts them and writes the top k; with a rerank it writes them to
 // pool[slot][need] for k_rerank and k_topk.
-template <bool RERANK>
-__global__ __launch_bounds__(kFinThreads) void k_finalize(
+//
+// Bound by latency: the candidates' load and the barriers of the select.  Up to NT R candidates
+// stay in registers over its passes.  One query (about 1,500 candidates): 5.9 us; 10,000
+// candidates (every document of a small index) 8.3 us; 7,000 queries 45 us (14.8, 60 and 124 us
+// with eight fixed digits from memory).
+template <bool RERANK, int NT, int R>
+__global__ __launch_bounds__(NT) void k_finalize(
     DevIndex ix, const int32_t *slot_q, const uint32_t *count, const uint64_t *cand,
     const float *theta, int64_t cap, int32_t need, int32_t k, int32_t bm_words, uint64_t *pool,
     int64_t *out_ids, float *out_scores, int32_t *status)
 {
-    constexpr int NT = kFinThreads, NW = NT / kWave;
+    constexpr int NW = NT / kWave;
     extern __shared__ __align__(16) unsigned char smem[];
     const int32_t P = pow2_at_least(need);
     uint64_t *keys = reinterpret_cast<uint64_t *>(smem);                   // [P]
     uint32_t *bm = reinterpret_cast<uint32_t *>(keys + P);                  // [bm_words]
-    __shared__ uint32_t hist[256];
+    __shared__ SelectLds L;
     __shared__ uint32_t s_n, s_wsum[NW];
-    __shared__ int s_digit;
-    __shared__ int64_t s_need;
     const int tid = threadIdx.x;
     const int32_t slot = blockIdx.x;
     const int32_t row = slot_q ? slot_q[slot] : slot;
@@ -1659,27 +1744,28 @@ __global__ __launch_bounds__(kFinThreads) void k_finalize(
     }
     const uint64_t *cs = cand + (size_t)slot * (size_t)cap;
     constexpr uint32_t kZeroOrd = 0x80000000u;  // ord_f32(0.0f)
-    uint32_t n_pos = (uint32_t)cnt;
-    if (imp) {
-        uint32_t mine = 0;
-        for (int64_t i = tid; i < cnt; i += NT) mine += (uint32_t)(cs[i] >> 32) > kZeroOrd ? 1u : 0u;
-        (void)block_excl_scan<NT>(mine, s_wsum, n_pos);
-    }
     if (tid == 0) s_n = 0;
-    if (!imp || (int64_t)n_pos >= (int64_t)need) {
-        // the first need candidates (all positive when zeros are implicit)
-        const uint64_t kth = block_select<uint64_t>(
-            cnt, need, [&](int64_t i) { return cs[i]; }, hist, &s_digit, &s_need);
-        __syncthreads();
-        for (int64_t i = tid; i < cnt; i += NT) {
-            const uint64_t key = cs[i];
-            if (key >= kth) {
-                const uint32_t p = atomicAdd(&s_n, 1u);
-                if (p < (uint32_t)P) keys[p] = key;
-            }
+    // the pool into keys; false: the slot needs a retry.  each(f): f on every candidate of the thread
+    auto select = [&](auto each) -> bool {
+        uint32_t n_pos = cnt;
+        if (imp) {
+            uint32_t mine = 0;
+            each([&](uint64_t key) { mine += (uint32_t)(key >> 32) > kZeroOrd ? 1u : 0u; });
+            (void)block_excl_scan<NT>(mine, s_wsum, n_pos);
         }
-        __syncthreads();
-    } else {
+        if (!imp || (int64_t)n_pos >= (int64_t)need) {
+            // the first need candidates (all positive when zeros are implicit)
+            const uint64_t bound = (int64_t)cnt == need ? 0ull
+                : block_select<NT, uint64_t>(cs[0], need, each, L, nullptr);
+            __syncthreads();
+            each([&](uint64_t key) {
+                const bool take = key >= bound;
+                const uint32_t p = wave_place(&s_n, take);
+                if (take && p < (uint32_t)P) keys[p] = key;
+            });
+            __syncthreads();
+            return true;
+        }
         // every positive candidate, then the lowest-id zero-score documents, then (only if
         // the zeros run out) the best emitted negatives
         const int64_t zeros_avail = ix.n_docs - (int64_t)cnt;
@@ -1687,21 +1773,17 @@ __global__ __launch_bounds__(kFinThreads) void k_finalize(
         const int64_t nt = (int64_t)need - n_pos - zt;
         const int64_t bound = min(ix.n_docs, zt + (int64_t)cnt);  // the zt-th zero id is below
         const int32_t words = (int32_t)((bound + 31) / 32);
-        if (nt > (int64_t)cnt - n_pos || words > bm_words) {
-            if (tid == 0) status[row] = kSlotRetry;
-            return;
-        }
+        if (nt > (int64_t)cnt - n_pos || words > bm_words) return false;
         __syncthreads();
-        for (int64_t i = tid; i < cnt; i += NT) {
-            const uint64_t key = cs[i];
+        each([&](uint64_t key) {
             if ((uint32_t)(key >> 32) > kZeroOrd) keys[atomicAdd(&s_n, 1u)] = key;
-        }
+        });
         for (int w = tid; w < words; w += NT) bm[w] = 0u;
         __syncthreads();
-        for (int64_t i = tid; i < cnt; i += NT) {
-            const uint32_t d = key_doc(cs[i]);
+        each([&](uint64_t key) {
+            const uint32_t d = key_doc(key);
             if ((int64_t)d < bound) atomicOr(&bm[d >> 5], 1u << (d & 31));
-        }
+        });
         __syncthreads();
         // zero bits in order: each thread owns a run of words
         const int32_t per = (words + NT - 1) / NT;
@@ -1727,31 +1809,42 @@ __global__ __launch_bounds__(kFinThreads) void k_finalize(
         }
         if (nt > 0) {
             // the nt best negatives: non-negative keys map to 0 and rank below them
-            const uint64_t kthn = block_select<uint64_t>(
-                cnt, nt,
-                [&](int64_t i) {
-                    const uint64_t key = cs[i];
-                    return (uint32_t)(key >> 32) < kZeroOrd ? key : 0ull;
-                },
-                hist, &s_digit, &s_need);
+            auto neg = [&](auto f) {
+                each([&](uint64_t key) { f((uint32_t)(key >> 32) < kZeroOrd ? key : 0ull); });
+            };
+            const uint64_t first = (uint32_t)(cs[0] >> 32) < kZeroOrd ? cs[0] : 0ull;
+            const uint64_t kthn = block_select<NT, uint64_t>(first, nt, neg, L, nullptr);
             if (tid == 0) s_n = 0;
             __syncthreads();
-            for (int64_t i = tid; i < cnt; i += NT) {
-                const uint64_t key = cs[i];
-                if ((uint32_t)(key >> 32) < kZeroOrd && key >= kthn)
-                    keys[n_pos + zt + atomicAdd(&s_n, 1u)] = key;
-            }
+            neg([&](uint64_t key) {
+                if (key && key >= kthn) keys[n_pos + zt + atomicAdd(&s_n, 1u)] = key;
+            });
         }
         __syncthreads();
+        return true;
+    };
+    bool ok;
+    if (cnt <= (uint32_t)(NT * R)) {
+        uint64_t key[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) key[j] = (uint32_t)(j * NT + tid) < cnt ? cs[j * NT + tid] : 0ull;
+        ok = select([&](auto f) {
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+                if ((uint32_t)(j * NT + tid) < cnt) f(key[j]);
+        });
+    } else {
+        ok = select([&](auto f) {
+            for (int64_t i = tid; i < cnt; i += NT) f(cs[i]);
+        });
     }
-
+    if (tid == 0) status[row] = ok ? kSlotOk : kSlotRetry;
+    if (!ok) return;
     if (RERANK) {
         for (int i = tid; i < need; i += NT) pool[(size_t)slot * (size_t)need + i] = keys[i];
-        if (tid == 0) status[row] = kSlotOk;
         return;
     }
-    sort_and_write(keys, need, k, row, out_ids, out_scores);
-    if (tid == 0) status[row] = kSlotOk;
+    sort_and_write<NT>(keys, need, k, row, out_ids, out_scores);
 }
 
 // Exact rerank (Alg. 4): each wave scores kRerankPerWave pool entries at a
@@ -1825,20 +1918,49 @@ __global__ __launch_bounds__(kFinThreads) void k_rerank(DevIndex ix, DevQueries 
     }
 }
 
-// One workgroup per slot: sort the reranked pool and write the top k.
+// One workgroup per slot: the top k of the reranked pool, in order.  A short result (k up to
+// kRankSort of a pool of up to kTopkRegs per thread) is selected first, so that only k keys are
+// put in order: one query (50 of 500) 5.0 us, 7,000 queries 21 us where sorting the
+// pool (a barrier for each of 45 exchange steps) took 18.4 and 96 us.
+template <bool SELECT>
 __global__ __launch_bounds__(kFinThreads) void k_topk(const int32_t *slot_q, int32_t need,
                                                       int32_t k, const uint64_t *pool,
                                                       int64_t *out_ids, float *out_scores,
                                                       const int32_t *status)
 {
+    constexpr int NT = kFinThreads;
     extern __shared__ __align__(16) unsigned char smem[];
-    uint64_t *keys = reinterpret_cast<uint64_t *>(smem);  // [pow2_at_least(need)]
+    uint64_t *keys = reinterpret_cast<uint64_t *>(smem);  // [pow2_at_least(SELECT ? k : need)]
+    const int tid = threadIdx.x;
     const int32_t slot = blockIdx.x;
     const int32_t row = slot_q ? slot_q[slot] : slot;
-    if (status[row] != kSlotOk) return;
-    for (int i = threadIdx.x; i < need; i += kFinThreads)
-        keys[i] = pool[(size_t)slot * (size_t)need + i];
-    sort_and_write(keys, need, k, row, out_ids, out_scores);
+    const uint64_t *e = pool + (size_t)slot * (size_t)need;
+    if constexpr (SELECT) {
+        __shared__ SelectLds L;
+        __shared__ uint32_t s_n;
+        uint64_t key[kTopkRegs];
+#pragma unroll
+        for (int j = 0; j < kTopkRegs; ++j) key[j] = j * NT + tid < need ? e[j * NT + tid] : 0ull;
+        const uint64_t any = e[0];
+        if (status[row] != kSlotOk) return;
+        if (tid == 0) s_n = 0;
+        auto each = [&](auto f) {
+#pragma unroll
+            for (int j = 0; j < kTopkRegs; ++j)
+                if (j * NT + tid < need) f(key[j]);
+        };
+        const uint64_t bound = block_select<NT, uint64_t>(any, k, each, L, nullptr);
+        each([&](uint64_t x) {
+            const bool take = x >= bound;
+            const uint32_t p = wave_place(&s_n, take);
+            if (take && p < (uint32_t)k) keys[p] = x;  // keys are distinct: exactly k
+        });
+        sort_and_write<NT>(keys, k, k, row, out_ids, out_scores);
+    } else {
+        if (status[row] != kSlotOk) return;
+        for (int i = tid; i < need; i += NT) keys[i] = e[i];
+        sort_and_write<NT>(keys, need, k, row, out_ids, out_scores);
+    }
 }
 
 // ------------------------------------------------------------------ pair scores
@@ -2111,12 +2233,21 @@ hipError_t launch_accumulate(const DevIndex &ix, const DevQueries &q, const DevC
     return dispatch_b<2, false>(batch, ix, q, c, slot_q, n_slots, n_sample_tiles, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
 }
 
+// Selecting kernels (k_theta, k_finalize): large workgroups while they all run at once, small ones
+// beyond (kFewSlots = two 1,024-thread workgroups per CU).  Threshold of one query: 4.7 us with
+// 1,024 threads, 8.7 with 256; of 1,000 queries: 12.4 and 11.2 us.
+constexpr int32_t kFewSlots = 512;
+
 hipError_t launch_theta(const float *maxima, int64_t n_maxima, int64_t rank, int32_t n_slots,
                         float *theta, hipStream_t s)
 {
     if (n_slots == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_theta, dim3((unsigned)n_slots), dim3(kThetaThreads), 0, s, maxima,
-                       n_maxima, rank, theta);
+    if (n_slots <= kFewSlots)
+        hipLaunchKernelGGL((k_theta<1024, 4>), dim3((unsigned)n_slots), dim3(1024), 0, s, maxima,
+                           n_maxima, rank, theta);
+    else
+        hipLaunchKernelGGL((k_theta<256, 16>), dim3((unsigned)n_slots), dim3(256), 0, s, maxima,
+                           n_maxima, rank, theta);
     return hipGetLastError();
 }
 
@@ -2166,22 +2297,23 @@ hipError_t launch_finalize(const DevIndex &ix, const DevQueries &q, const int32_
     if (bm > (int64_t)1 << 20) return hipErrorInvalidValue;
     const size_t keys = (size_t)pow2_at_least(need) * 8;
     const size_t lds = keys + (size_t)bm * 4;
+    if (rerank && !pool) return hipErrorInvalidValue;
     hipError_t e;
-    if (!rerank) {
-        e = set_lds(k_finalize<false>, lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_finalize<false>, dim3((unsigned)n_slots), dim3(kFinThreads), lds, s,
-                           ix, slot_q, count, cand, theta, cap, need, k, (int32_t)bm, nullptr,
-                           out_ids, out_scores, status);
+    auto finalize = [&](auto kernel, int nt) -> hipError_t {
+        hipError_t r = set_lds(kernel, lds);
+        if (r != hipSuccess) return r;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)n_slots), dim3(nt), lds, s, ix, slot_q, count,
+                           cand, theta, cap, need, k, (int32_t)bm, pool, out_ids, out_scores, status);
         return hipGetLastError();
-    }
-    if (!pool) return hipErrorInvalidValue;
-    e = set_lds(k_finalize<true>, lds);
+    };
+    // 1,024 threads where every document is a candidate (10,000 of them: 8.3 us, 20 us with 256
+    // threads); a threshold leaves one or two thousand, which 256 threads select sooner (one query
+    // 5.9 against 6.4 us, 37 queries 7.8 against 9.6)
+    const bool wide = n_slots <= kFewSlots && !theta;
+    if (!rerank)
+        return wide ? finalize(k_finalize<false, 1024, 8>, 1024) : finalize(k_finalize<false, 256, 8>, 256);
+    e = wide ? finalize(k_finalize<true, 1024, 8>, 1024) : finalize(k_finalize<true, 256, 8>, 256);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_finalize<true>, dim3((unsigned)n_slots), dim3(kFinThreads), lds, s, ix,
-                       slot_q, count, cand, theta, cap, need, k, (int32_t)bm, pool, out_ids,
-                       out_scores, status);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
     const int32_t tlg = table_lg(max_qnnz > 0 ? max_qnnz : 1);
     const size_t lds_t = (size_t)16 << tlg;
     e = set_lds(k_rerank, lds_t);
@@ -2195,11 +2327,16 @@ hipError_t launch_finalize(const DevIndex &ix, const DevQueries &q, const int32_
     hipLaunchKernelGGL(k_rerank, dim3((unsigned)n_slots, blocks), dim3(kFinThreads), lds_t, s, ix,
                        q, slot_q, need, tlg, groups, pool, status);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    e = set_lds(k_topk, keys);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_topk, dim3((unsigned)n_slots), dim3(kFinThreads), keys, s, slot_q, need,
-                       k, pool, out_ids, out_scores, status);
-    return hipGetLastError();
+    auto topk = [&](auto kernel, size_t bytes) -> hipError_t {
+        hipError_t r = set_lds(kernel, bytes);
+        if (r != hipSuccess) return r;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)n_slots), dim3(kFinThreads), bytes, s, slot_q,
+                           need, k, pool, out_ids, out_scores, status);
+        return hipGetLastError();
+    };
+    if (k < need && k <= kRankSort && need > kRankSort && need <= kFinThreads * kTopkRegs)
+        return topk(k_topk<true>, (size_t)pow2_at_least(k) * 8);
+    return topk(k_topk<false>, keys);
 }
 
 namespace {

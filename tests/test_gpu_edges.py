@@ -104,3 +104,45 @@ def test_pair_scores_and_gradients_at_split_edges(sindi, n_cand, lens):
     m = np.bincount(cand.reshape(-1)[ok], minlength=1).max() if ok.any() else 0
     assert (np.abs(_np(gq) - rq) <= (n_cand + 3) * u * sq + 1e-30).all()
     assert (np.abs(_np(gx) - rx) <= (m + 2) * u * sx + 1e-30).all()
+
+
+# ------------------------------------------------------------------ selection
+def _int_setup(nd, nq, signed, seed=8):
+    """Small integer values: every product and sum is exact, and most scores tie."""
+    rng = np.random.default_rng(seed)
+    vocab = 60
+    corpus = synth.random_csr(rng, nd, vocab, 6)
+    q = synth.random_csr(rng, nq, vocab, 5, min_nnz=1)
+    draw = [-2.0, -1.0, 1.0, 2.0] if signed else [1.0, 2.0]
+    corpus = synth.Csr(corpus.indptr, corpus.indices, rng.choice(draw, corpus.nnz).astype(np.float32), vocab)
+    q = synth.Csr(q.indptr, q.indices, np.ones(q.nnz, np.float32), vocab)
+    dense = np.zeros((nd, vocab))
+    dense[np.repeat(np.arange(nd), np.diff(corpus.indptr)), corpus.indices] = corpus.values
+    qd = np.zeros((nq, vocab))
+    qd[np.repeat(np.arange(nq), np.diff(q.indptr)), q.indices] = q.values
+    return corpus, q, qd @ dense.T
+
+
+def _ranked(scores, k):
+    """The first k of every row, score descending, equal scores by ascending id."""
+    ids = np.argsort(-scores, axis=1, kind="stable")[:, :k]
+    return ids, np.take_along_axis(scores, ids, 1)
+
+
+@pytest.mark.parametrize("signed", [False, True])
+@pytest.mark.parametrize("nd, cand_cap", [(1, 0), (255, 0), (2047, 0), (2049, 0), (8193, 0), (9001, 2500)])
+@pytest.mark.parametrize("nq", [3, 520])
+def test_selection_with_ties(sindi, nd, cand_cap, nq, signed):
+    """Top-k of scores that mostly tie, over every workgroup size, register and memory path,
+    with every document a candidate and with a candidate threshold: exactly the ranking order."""
+    corpus, q, scores = _int_setup(nd, nq, signed)
+    idx = sindi.Index(corpus, alpha=1.0, window=4_000, tile=1_000)
+    dq = sindi.DeviceCsr.from_host(q)
+    for k, gamma in ((1, 0), (50, 500), (256, 300), (257, 600), (1, 2049), (600, 2100)):
+        ref = _ranked(scores, k)
+        n = ref[0].shape[1]
+        for got in (idx.search_coarse(dq, k, cand_cap=cand_cap),
+                    idx.search(dq, k, gamma=gamma, cand_cap=cand_cap)):
+            ids, sc = _np(got[0]), _np(got[1])
+            assert np.array_equal(ids[:, :n], ref[0]) and np.array_equal(sc[:, :n], ref[1])
+            assert (ids[:, n:] == -1).all() and np.isneginf(sc[:, n:]).all()
