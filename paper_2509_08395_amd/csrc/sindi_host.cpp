@@ -145,6 +145,9 @@ constexpr int32_t kDefaultSampleTiles = 8;
 // with one workgroup per (query, tile run); 79.0 against 80.5 ms on the serving mix)
 constexpr int32_t kDefaultSchedule = 2;
 constexpr int32_t kDefaultGamma = 500;
+// Device queries of so few entries are searched without waiting for their check (one query, or
+// several whose rerank tables, sized for all entries, stay at 16 KB of LDS).
+constexpr int64_t kUncheckedOne = 512, kUncheckedNnz = 128;
 constexpr size_t kCandBudget = size_t(4) << 30;  // candidate buffer bytes per pass
 
 }  // namespace
@@ -444,6 +447,7 @@ sindi_status build_impl(const sindi_csr *c, const sindi_build_params *p, hipStre
     int lds = 0;
     HIP_TRY(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, ix->device));
     ix->max_lds = lds;
+    if (ix->stage.alloc() != hipSuccess) return fail(SINDI_E_OOM, "sindi_build: pinned host allocation failed");
     const int64_t nd = c->n_rows, nc = c->n_cols;
     ix->n_docs = nd;
     ix->n_cols = nc;
@@ -715,7 +719,7 @@ size_t scratch_row_bytes(const Plan &pl, int64_t nq, int64_t nnz)
 {
     const size_t e = (size_t)std::max<int64_t>(nnz, 1), q = (size_t)std::max<int64_t>(nq, 1);
     return 2 * align256(e * 4) + align256(pl.beta < 1.0 ? e * 8 : 8) + 5 * align256(q * 4) +
-           2 * align256(8);
+           align256(16);
 }
 
 Scratch carve_rows(unsigned char *p, const Plan &pl, int64_t nq, int64_t nnz)
@@ -735,8 +739,8 @@ Scratch carve_rows(unsigned char *p, const Plan &pl, int64_t nq, int64_t nnz)
     sc.status = reinterpret_cast<int32_t *>(take(q * 4));
     sc.rows = reinterpret_cast<int32_t *>(take(q * 4));
     sc.rows2 = reinterpret_cast<int32_t *>(take(q * 4));
-    sc.err = reinterpret_cast<int32_t *>(take(8));
-    sc.n_rows = reinterpret_cast<uint32_t *>(take(8));
+    sc.err = reinterpret_cast<int32_t *>(take(16));
+    sc.n_rows = reinterpret_cast<uint32_t *>(sc.err + 2);
     return sc;
 }
 
@@ -764,7 +768,7 @@ PassShape pass_shape(const sindi_index *ix, const Plan &pl, PassKind kind)
 size_t pass_bytes(const PassShape &sh, const Plan &pl, int64_t g)
 {
     const size_t n = (size_t)g;
-    return 2 * align256(n * 4) + align256(16 + n * 4) + align256(n * (size_t)sh.n_max * 4) +
+    return align256(16 + n * 4) + align256(n * 4) + align256(n * (size_t)sh.n_max * 4) +
            align256(n * (size_t)sh.cap * 8) + (pl.rerank ? align256(n * (size_t)pl.need * 8) : 0);
 }
 
@@ -772,7 +776,7 @@ int64_t pass_group(const PassShape &sh, const Plan &pl, size_t bytes)
 {
     // pass_bytes(g) >= g * per (alignment only adds, at most 255 bytes per array), so
     // bytes / per bounds g from above and few steps down reach the largest fit
-    const size_t per = 12 + (size_t)sh.n_max * 4 + (size_t)sh.cap * 8 + (pl.rerank ? (size_t)pl.need * 8 : 0);
+    const size_t per = 8 + (size_t)sh.n_max * 4 + (size_t)sh.cap * 8 + (pl.rerank ? (size_t)pl.need * 8 : 0);
     int64_t g = (int64_t)(bytes / per);
     while (g > 0 && pass_bytes(sh, pl, g) > bytes) --g;
     return g;
@@ -781,25 +785,29 @@ int64_t pass_group(const PassShape &sh, const Plan &pl, size_t bytes)
 sindi_status enqueue_prep(const sindi_index *ix, const Scratch &sc, const Plan &pl,
                           const DevQueries &dq, hipStream_t s)
 {
-    HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t *>(sc.err), 2, 0u, s));
+    // the arena starts with the queue counters and candidate counts of a group's slots
+    const PassShape sh = pass_shape(ix, pl, kPassSampled);
+    const int64_t g = std::min<int64_t>(pass_group(sh, pl, sc.arena_bytes), dq.n_rows);
     DevCoarse dc{sc.ct, sc.cw, sc.cn, sc.qinv};
     HIP_TRY(timed(kProfPrep, s, [&] {
         return launch_query_prep(dq, ix->n_cols, pl.beta, dc, ix->term_max.as<float>(), sc.sabs,
-                                 sc.err, s);
+                                 sc.err, reinterpret_cast<uint32_t *>(sc.arena), g > 0 ? 4 + g : 0, s);
     }));
     return SINDI_OK;
 }
 
 sindi_status enqueue_passes(const sindi_index *ix, const Scratch &sc, const Plan &pl,
                             PassKind kind, const DevQueries &dq, const int32_t *rows, int64_t n,
+                            int32_t *out_rows, uint32_t *out_count, bool unchecked,
                             int64_t *out_ids, float *out_scores, hipStream_t s)
 {
     if (n <= 0) return SINDI_OK;
+    const DevRetry retry{sc.err, sc.status, out_rows, out_count, sc.report, unchecked};
     if (ix->n_docs == 0) {  // every query row: k paddings
-        if (rows) return fail(SINDI_E_INTERNAL, "search: a retry over an empty index");
+        if (rows || unchecked) return fail(SINDI_E_INTERNAL, "search: an empty index");
         HIP_TRY(launch_fill_f32(out_scores, n * pl.k, -INFINITY, s));
         HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t *>(out_ids), 2 * n * pl.k, 0xFFFFFFFFu, s));
-        HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t *>(sc.status), n, (uint32_t)kSlotOk, s));
+        HIP_TRY(launch_report(retry, s));
         return SINDI_OK;
     }
     const PassShape sh = pass_shape(ix, pl, kind);
@@ -813,29 +821,29 @@ sindi_status enqueue_passes(const sindi_index *ix, const Scratch &sc, const Plan
         p += align256(bytes);
         return r;
     };
-    int32_t *slot_q = reinterpret_cast<int32_t *>(take((size_t)g * 4));
     // the work-queue counters of the persistent scoring launches (sample, score), then the
-    // per-slot candidate counts: one fill clears both
+    // per-slot candidate counts: one fill clears both (for the sampled pass's first group the
+    // preparation has cleared them)
     unsigned long long *queue = reinterpret_cast<unsigned long long *>(take(16 + (size_t)g * 4));
     uint32_t *count = reinterpret_cast<uint32_t *>(queue + 2);
     float *theta = reinterpret_cast<float *>(take((size_t)g * 4));
     float *maxima = reinterpret_cast<float *>(take((size_t)g * sh.n_max * 4));
     uint64_t *cand = reinterpret_cast<uint64_t *>(take((size_t)g * sh.cap * 8));
     uint64_t *pool = pl.rerank ? reinterpret_cast<uint64_t *>(take((size_t)g * pl.need * 8)) : nullptr;
+    const float *th = sh.keep_all ? nullptr : theta;
     const DevIndex dix = ix->dev();
     const DevCoarse dc{sc.ct, sc.cw, sc.cn, sc.qinv};
     // retried rows are few: one query per workgroup
     const int batch = kind == kPassSampled ? pl.batch : 1;
+    if (rows) HIP_TRY(launch_fill_u32(out_count, 1, 0u, s));
     for (int64_t g0 = 0; g0 < n; g0 += g) {
         const int32_t ns = (int32_t)std::min<int64_t>(g, n - g0);
-        const int32_t *sq = rows ? rows + g0 : slot_q;
-        if (!rows) HIP_TRY(launch_iota(slot_q, ns, (int32_t)g0, s));
-        HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t *>(queue), 4 + (int64_t)ns, 0u, s));
-        if (sh.keep_all) {
-            HIP_TRY(launch_fill_f32(theta, ns, -INFINITY, s));
-        } else {
+        const DevSlots slots{rows ? rows + g0 : nullptr, (int32_t)g0, ns};
+        if (rows || g0 > 0)
+            HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t *>(queue), 4 + (int64_t)ns, 0u, s));
+        if (!sh.keep_all) {
             HIP_TRY(timed(kProfSample, s, [&] {
-                return launch_accumulate(dix, dq, dc, batch, true, sq, ns, sh.n_sample, maxima,
+                return launch_accumulate(dix, dq, dc, batch, true, slots, sh.n_sample, maxima,
                                          nullptr, nullptr, nullptr, 0, pl.tile_run, pl.max_qnnz,
                                          pl.queue ? queue : nullptr, s);
             }));
@@ -844,24 +852,16 @@ sindi_status enqueue_passes(const sindi_index *ix, const Scratch &sc, const Plan
             }));
         }
         HIP_TRY(timed(kProfScore, s, [&] {
-            return launch_accumulate(dix, dq, dc, batch, false, sq, ns, 0, nullptr, theta, count,
+            return launch_accumulate(dix, dq, dc, batch, false, slots, 0, nullptr, th, count,
                                      cand, sh.cap, pl.tile_run, pl.max_qnnz,
                                      pl.queue ? queue + 1 : nullptr, s);
         }));
         // without a threshold no sum is left implicit
         HIP_TRY(timed(kProfFinal, s, [&] {
-            return launch_finalize(dix, dq, sq, ns, count, cand, sh.keep_all ? nullptr : theta,
-                                   sh.cap, pl.need, pl.k, pl.rerank, pl.max_qnnz, pool, out_ids,
-                                   out_scores, sc.status, s);
+            return launch_finalize(dix, dq, slots, count, cand, th, sh.cap, pl.need, pl.k, pl.rerank,
+                                   pl.max_qnnz, pool, out_ids, out_scores, retry, s);
         }));
     }
-    return SINDI_OK;
-}
-
-sindi_status enqueue_collect_failed(const Scratch &sc, const int32_t *in_rows, int64_t n,
-                                    int32_t *out_rows, uint32_t *count, hipStream_t s)
-{
-    HIP_TRY(launch_collect_failed(sc.status, in_rows, (int32_t)n, out_rows, count, s));
     return SINDI_OK;
 }
 
@@ -874,26 +874,35 @@ sindi_status run_search(const sindi_index *ix, Scratch &sc, const Plan &plan, co
     const int64_t nq = dq.n_rows;
     sindi_status st = enqueue_prep(ix, sc, pl, dq, s);
     if (st != SINDI_OK) return st;
-    int32_t e2[2] = {0, 0};
-    if (device_queries) {
-        // validate before anything reaches the caller's outputs
+    auto malformed = [&](uint32_t flags) {
+        return fail(SINDI_E_INVALID,
+                    "%s: malformed query rows (flags 0x%x: 1 row pointers, 2 term id range, "
+                    "4 order, 8 non-finite, 16 more than %d entries)",
+                    fn, flags, kQueryHash / 2);
+    };
+    // Device queries are validated before anything reaches the caller's outputs.  A call of few
+    // entries does not wait for that: the entries bound its longest row, and its kernels write
+    // nothing where the flags are set.
+    const bool unchecked = device_queries && ix->n_docs > 0 &&
+                           dq.nnz <= (nq == 1 ? kUncheckedOne : kUncheckedNnz);
+    if (device_queries && !unchecked) {
+        int32_t e2[2] = {0, 0};
         HIP_TRY(hipMemcpyAsync(e2, sc.err, 8, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
-        if (e2[0])
-            return fail(SINDI_E_INVALID,
-                        "%s: malformed query rows (flags 0x%x: 1 row pointers, 2 term id range, "
-                        "4 order, 8 non-finite, 16 more than %d entries)",
-                        fn, e2[0], kQueryHash / 2);
+        if (e2[0]) return malformed((uint32_t)e2[0]);
         pl.max_qnnz = e2[1];
+    } else if (unchecked) {
+        pl.max_qnnz = (int32_t)dq.nnz;
     }
-    if ((st = enqueue_passes(ix, sc, pl, kPassSampled, dq, nullptr, nq, out_ids, out_scores, s)) != SINDI_OK)
+    if ((st = enqueue_passes(ix, sc, pl, kPassSampled, dq, nullptr, nq, sc.rows, sc.n_rows, unchecked,
+                             out_ids, out_scores, s)) != SINDI_OK)
         return st;
-    if ((st = enqueue_collect_failed(sc, nullptr, nq, sc.rows, sc.n_rows, s)) != SINDI_OK) return st;
-    uint32_t n_fail = 0;
-    HIP_TRY(hipMemcpyAsync(&n_fail, sc.n_rows, 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(e2, sc.err, 4, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    if (e2[0]) return fail(SINDI_E_INTERNAL, "%s: validated host queries flagged 0x%x", fn, e2[0]);
+    if (sc.report[1]) {
+        if (device_queries) return malformed(sc.report[1]);
+        return fail(SINDI_E_INTERNAL, "%s: validated host queries flagged 0x%x", fn, sc.report[1]);
+    }
+    uint32_t n_fail = sc.report[0];
     // rows whose sampled threshold missed: a threshold over every tile, then no threshold
     const PassKind retry[2] = {kPassFullSample, kPassKeepAll};
     int32_t *lists[3] = {sc.rows, sc.rows2, sc.rows};
@@ -903,13 +912,11 @@ sindi_status run_search(const sindi_index *ix, Scratch &sc, const Plan &plan, co
             if (!grow) return fail(SINDI_E_INTERNAL, "%s: scratch too small for a retry", fn);
             if ((st = grow(grow_ctx, need, sc)) != SINDI_OK) return st;
         }
-        if ((st = enqueue_passes(ix, sc, pl, retry[r], dq, lists[r], n_fail, out_ids, out_scores,
-                                 s)) != SINDI_OK)
+        if ((st = enqueue_passes(ix, sc, pl, retry[r], dq, lists[r], n_fail, lists[r + 1],
+                                 sc.n_rows + 1, false, out_ids, out_scores, s)) != SINDI_OK)
             return st;
-        if ((st = enqueue_collect_failed(sc, lists[r], n_fail, lists[r + 1], sc.n_rows + 1, s)) != SINDI_OK)
-            return st;
-        HIP_TRY(hipMemcpyAsync(&n_fail, sc.n_rows + 1, 4, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
+        n_fail = sc.report[0];
     }
     if (n_fail) return fail(SINDI_E_INTERNAL, "%s: %u queries unresolved", fn, n_fail);
     return SINDI_OK;
@@ -961,30 +968,44 @@ sindi_status search_impl(sindi_index *ix, const sindi_csr *qc, int32_t k,
     HIP_TRY(ws.arena.ensure(pass_bytes(sh, pl, g)));
     sc.arena = ws.arena.as<unsigned char>();
     sc.arena_bytes = ws.arena.bytes;
+    sc.report = ix->stage.report();
 
     DevQueries dq{nq, qc->nnz, qc->indptr, qc->indices, qc->values};
     if (!qc->on_device) {
-        HIP_TRY(ws.q_ptr.ensure((size_t)(nq + 1) * 8));
-        HIP_TRY(ws.q_idx.ensure((size_t)qc->nnz * 4 + 4));
-        HIP_TRY(ws.q_val.ensure((size_t)qc->nnz * 4 + 4));
-        HIP_TRY(hipMemcpyAsync(ws.q_ptr.p, qc->indptr, (size_t)(nq + 1) * 8, hipMemcpyHostToDevice, s));
-        if (qc->nnz) {
-            HIP_TRY(hipMemcpyAsync(ws.q_idx.p, qc->indices, (size_t)qc->nnz * 4, hipMemcpyHostToDevice, s));
-            HIP_TRY(hipMemcpyAsync(ws.q_val.p, qc->values, (size_t)qc->nnz * 4, hipMemcpyHostToDevice, s));
+        const size_t np = (size_t)(nq + 1) * 8, ne = (size_t)qc->nnz * 4;
+        HIP_TRY(ws.q_all.ensure(np + 2 * ne + 8));
+        unsigned char *d = ws.q_all.as<unsigned char>();
+        if (np + 2 * ne <= HostStage::kBytes) {  // packed in pinned memory: one upload
+            unsigned char *h = ix->stage.p;
+            memcpy(h, qc->indptr, np);
+            if (ne) {
+                memcpy(h + np, qc->indices, ne);
+                memcpy(h + np + ne, qc->values, ne);
+            }
+            HIP_TRY(hipMemcpyAsync(d, h, np + 2 * ne, hipMemcpyHostToDevice, s));
+        } else {
+            HIP_TRY(hipMemcpyAsync(d, qc->indptr, np, hipMemcpyHostToDevice, s));
+            if (ne) {
+                HIP_TRY(hipMemcpyAsync(d + np, qc->indices, ne, hipMemcpyHostToDevice, s));
+                HIP_TRY(hipMemcpyAsync(d + np + ne, qc->values, ne, hipMemcpyHostToDevice, s));
+            }
         }
-        dq.indptr = ws.q_ptr.as<int64_t>();
-        dq.indices = ws.q_idx.as<int32_t>();
-        dq.values = ws.q_val.as<float>();
+        dq.indptr = reinterpret_cast<const int64_t *>(d);
+        dq.indices = reinterpret_cast<const int32_t *>(d + np);
+        dq.values = reinterpret_cast<const float *>(d + np + ne);
     }
     return run_search(ix, sc, pl, dq, qc->on_device != 0, out_ids, out_scores, s, fn,
                       grow_workspace, &ws);
 }
 
-// Waits for the stream; *longest: the longest query row.
-sindi_status check_dev_queries(sindi_index *ix, const sindi_csr *qc, const char *fn, hipStream_t s,
-                               int32_t *longest)
+// Check the queries of a pair-score call on the device and run launch(err, bound on the rows).
+// The launch is enqueued behind the check, for rows up to twice the mean, and does nothing where
+// the flags are set or a row is longer; then the flags are read (waiting for the stream), and it
+// is launched again where a row was longer.
+template <typename Launch>
+sindi_status checked_score(sindi_index *ix, const sindi_csr *qc, const char *fn, hipStream_t s,
+                           Launch launch)
 {
-    *longest = 0;
     if (!qc->on_device) return fail(SINDI_E_INVALID, "%s: queries must be device memory", fn);
     if (qc->n_cols != ix->n_cols) return fail(SINDI_E_INVALID, "%s: column count mismatch", fn);
     if (qc->n_rows < 0 || qc->nnz < 0) return fail(SINDI_E_INVALID, "%s: bad query shape", fn);
@@ -996,14 +1017,17 @@ sindi_status check_dev_queries(sindi_index *ix, const sindi_csr *qc, const char 
     HIP_TRY(ws.row_part.ensure(scratch_row_bytes(pl, qc->n_rows, qc->nnz)));
     const Scratch sc = carve_rows(ws.row_part.as<unsigned char>(), pl, qc->n_rows, qc->nnz);
     DevQueries dq{qc->n_rows, qc->nnz, qc->indptr, qc->indices, qc->values};
-    HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t *>(sc.err), 2, 0u, s));
     DevCoarse dc{sc.ct, sc.cw, sc.cn, sc.qinv};
-    HIP_TRY(launch_query_prep(dq, ix->n_cols, 1.0, dc, ix->term_max.as<float>(), nullptr, sc.err, s));
-    int32_t qerr[2] = {0, 0};
-    HIP_TRY(hipMemcpyAsync(qerr, sc.err, 8, hipMemcpyDeviceToHost, s));
+    HIP_TRY(launch_query_prep(dq, ix->n_cols, 1.0, dc, ix->term_max.as<float>(), nullptr, sc.err,
+                              nullptr, 0, s));
+    const int64_t mean = (qc->nnz + qc->n_rows - 1) / qc->n_rows;
+    const int32_t bound = (int32_t)std::min<int64_t>(std::max<int64_t>(2 * mean, 32), kQueryHash / 2);
+    HIP_TRY(launch(dq, sc.err, bound));
+    uint32_t *report = ix->stage.report();
+    HIP_TRY(launch_report(DevRetry{sc.err, nullptr, nullptr, sc.n_rows, report, false}, s));
     HIP_TRY(hipStreamSynchronize(s));
-    if (qerr[0]) return fail(SINDI_E_INVALID, "%s: malformed query rows (flags 0x%x)", fn, qerr[0]);
-    *longest = qerr[1];
+    if (report[1]) return fail(SINDI_E_INVALID, "%s: malformed query rows (flags 0x%x)", fn, report[1]);
+    if ((int32_t)report[2] > bound) HIP_TRY(launch(dq, sc.err, (int32_t)report[2]));
     return SINDI_OK;
 }
 
@@ -1128,14 +1152,12 @@ sindi_status sindi_score_forward(const sindi_index *idx, const sindi_csr *querie
     sindi_index *ix = const_cast<sindi_index *>(idx);
     std::lock_guard<std::mutex> lock(ix->mu);
     hipStream_t s = (hipStream_t)stream;
-    int32_t longest = 0;
-    sindi_status st = check_dev_queries(ix, queries, "sindi_score_forward", s, &longest);
-    if (st != SINDI_OK) return st;
-    DevQueries dq{queries->n_rows, queries->nnz, queries->indptr, queries->indices, queries->values};
     DevIndex dix = ix->dev();
     if (doc_values) dix.values = doc_values;
-    HIP_TRY(launch_score_forward(dix, dq, cand_ids, n_cand, longest, out_scores, s));
-    return SINDI_OK;
+    return checked_score(ix, queries, "sindi_score_forward", s,
+                         [&](const DevQueries &q, const int32_t *err, int32_t bound) {
+                             return launch_score_forward(dix, q, cand_ids, n_cand, err, bound, out_scores, s);
+                         });
 }
 
 sindi_status sindi_score_backward(const sindi_index *idx, const sindi_csr *queries,
@@ -1149,15 +1171,13 @@ sindi_status sindi_score_backward(const sindi_index *idx, const sindi_csr *queri
     sindi_index *ix = const_cast<sindi_index *>(idx);
     std::lock_guard<std::mutex> lock(ix->mu);
     hipStream_t s = (hipStream_t)stream;
-    int32_t longest = 0;
-    sindi_status st = check_dev_queries(ix, queries, "sindi_score_backward", s, &longest);
-    if (st != SINDI_OK) return st;
-    DevQueries dq{queries->n_rows, queries->nnz, queries->indptr, queries->indices, queries->values};
     DevIndex dix = ix->dev();
     if (doc_values) dix.values = doc_values;
-    HIP_TRY(launch_score_backward(dix, dq, cand_ids, n_cand, longest, grad_scores,
-                                  grad_query_values, grad_doc_values, s));
-    return SINDI_OK;
+    return checked_score(ix, queries, "sindi_score_backward", s,
+                         [&](const DevQueries &q, const int32_t *err, int32_t bound) {
+                             return launch_score_backward(dix, q, cand_ids, n_cand, err, bound, grad_scores,
+                                                   grad_query_values, grad_doc_values, s);
+                         });
 }
 
 sindi_status sindi_profile_enable(int32_t enable) { return profile_enable(enable); }

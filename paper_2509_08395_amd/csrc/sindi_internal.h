@@ -97,8 +97,26 @@ inline int entry_block(int batch, int64_t max_terms)
     return eb;
 }
 
-// Status codes written per query slot by the finalize kernel.
+// Status codes written per query row by the finalizing kernels.
 enum SlotStatus : int32_t { kSlotOk = 0, kSlotRetry = 1 };
+
+// The query rows of a launch's n slots: rows[slot], or row0 + slot where rows is null.
+struct DevSlots {
+    const int32_t *rows;
+    int32_t row0, n;
+    __device__ __forceinline__ int32_t row(int32_t slot) const { return rows ? rows[slot] : row0 + slot; }
+};
+
+// Where a pass leaves its outcome: each row's status, the rows left to a retry (their number in
+// *count, zero when the pass starts), and, written by the pass's last kernel, report (pinned host
+// memory): {*count, err[0], err[1]}.  unchecked: the host has not seen the query flags err yet, so
+// a flagged call must write no output.
+struct DevRetry {
+    const int32_t *err;
+    int32_t *status, *rows;
+    uint32_t *count, *report;
+    bool unchecked;
+};
 
 // Lets `kernel` take up to the device's per-workgroup LDS (less its static
 // LDS) as dynamic LDS, set once per device and kernel, so launches of any size
@@ -107,17 +125,17 @@ enum SlotStatus : int32_t { kSlotOk = 0, kSlotRetry = 1 };
 hipError_t allow_lds(const void *kernel, size_t bytes);
 
 // Kernel launchers (sindi_kernels.hip).  All return hipGetLastError().
-// err_flag[0]: malformed-row bits, err_flag[1]: longest well-formed row (both
-// must be zero on entry).
+// err_flag[0]: malformed-row bits, err_flag[1]: longest well-formed row,
+// err_flag[2], [3]: cleared (the retry counts); zero[0, n_zero) is cleared too.
 hipError_t launch_query_prep(const DevQueries &q, int64_t n_cols, double beta, DevCoarse c,
                              const float *term_max, double *scratch_abs, int32_t *err_flag,
-                             hipStream_t s);
+                             uint32_t *zero, int64_t n_zero, hipStream_t s);
 
-// queue: null launches one workgroup per (slot, tile run); otherwise (one query per
+// theta: null keeps every document.  queue: null launches one workgroup per (slot, tile run); otherwise (one query per
 // workgroup only) one persistent launch of the device's resident workgroups takes the items
 // from the 8-byte counter *queue, which must be zero when the launch starts.
 hipError_t launch_accumulate(const DevIndex &ix, const DevQueries &q, const DevCoarse &c,
-                             int batch, bool sample, const int32_t *slot_q, int32_t n_slots,
+                             int batch, bool sample, const DevSlots &slots,
                              int32_t n_sample_tiles, float *maxima, const float *theta,
                              uint32_t *count, uint64_t *cand, int64_t cap, int32_t tiles_per_wg,
                              int32_t max_terms, unsigned long long *queue, hipStream_t s);
@@ -127,13 +145,8 @@ hipError_t launch_theta(const float *maxima, int64_t n_maxima, int64_t rank, int
 
 hipError_t launch_fill_f32(float *p, int64_t n, float v, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t s);
-// p[i] = first + i for i in [0, n).
-hipError_t launch_iota(int32_t *p, int32_t n, int32_t first, hipStream_t s);
-
-// Rows whose status is not kSlotOk (of [0, n), or of in_rows[0, n)) into
-// out_rows in order; their number into *count.
-hipError_t launch_collect_failed(const int32_t *status, const int32_t *in_rows, int32_t n,
-                                 int32_t *out_rows, uint32_t *count, hipStream_t s);
+// Write the report of a pass whose last kernel does not.
+hipError_t launch_report(const DevRetry &r, hipStream_t s);
 
 // max_qnnz: bound on the length of every finalized query row (sizes the
 // rerank table; a longer row gets status kSlotRetry).  theta: the thresholds
@@ -141,11 +154,11 @@ hipError_t launch_collect_failed(const int32_t *status, const int32_t *in_rows, 
 // threshold <= 0 means the zero sums were left out and are supplied here.
 // With rerank, pool is scratch of n_slots * need keys (select, then rerank
 // with one wave per entry, then sort).
-hipError_t launch_finalize(const DevIndex &ix, const DevQueries &q, const int32_t *slot_q,
-                           int32_t n_slots, const uint32_t *count, const uint64_t *cand,
+hipError_t launch_finalize(const DevIndex &ix, const DevQueries &q, const DevSlots &slots,
+                           const uint32_t *count, const uint64_t *cand,
                            const float *theta, int64_t cap, int32_t need, int32_t k, bool rerank,
                            int32_t max_qnnz, uint64_t *pool, int64_t *out_ids, float *out_scores,
-                           int32_t *status, hipStream_t s);
+                           const DevRetry &retry, hipStream_t s);
 
 // Device index build (sindi_build.hip); err bits: 1 row pointers, 2 term id
 // range, 4 ids not ascending, 8 non-finite, 16 a tile of more than kTileGroupsMax groups,
@@ -179,12 +192,15 @@ hipError_t build_deal_chunks(const uint32_t *goff, const int64_t *tile_post, int
                              int64_t n_cols, int32_t vbytes, uint16_t *post_doc, void *post_val,
                              hipStream_t s);
 
-// Pair scores and their gradients; max_qnnz: the longest query row (sizes the query tables).
+// Pair scores and their gradients; max_qnnz: bound on the query rows (sizes the query tables).
+// err: k_query_prep's flags; a launch whose rows are flagged, or whose longest row is beyond the
+// bound, does nothing.
 hipError_t launch_score_forward(const DevIndex &ix, const DevQueries &q, const int64_t *cand,
-                                int32_t n_cand, int32_t max_qnnz, float *out, hipStream_t s);
+                                int32_t n_cand, const int32_t *err, int32_t max_qnnz, float *out,
+                                hipStream_t s);
 
 hipError_t launch_score_backward(const DevIndex &ix, const DevQueries &q, const int64_t *cand,
-                                 int32_t n_cand, int32_t max_qnnz, const float *grad, float *gq,
-                                 float *gx, hipStream_t s);
+                                 int32_t n_cand, const int32_t *err, int32_t max_qnnz,
+                                 const float *grad, float *gq, float *gx, hipStream_t s);
 
 }  // namespace sindi

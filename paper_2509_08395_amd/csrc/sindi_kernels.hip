@@ -498,8 +498,9 @@ __device__ int prep_long_row(const DevQueries &q, int64_t n_cols, double beta, c
 
 // One wave per query row.  Flags malformed rows (err[0] bits: 1 row pointers,
 // 2 term id out of range, 4 ids not strictly ascending, 8 non-finite value,
-// 16 more than kQueryHash / 2 entries), keeps the longest row in err[1],
-// and writes the coarse terms: the non-zero entries, cut to the beta-mass
+// 16 more than kQueryHash / 2 entries), keeps the longest row in err[1]
+// (err[0..3] must be zero where the grid has several workgroups), clears
+// zero[0, n_zero) for the kernels that follow, and writes the coarse terms: the non-zero entries, cut to the beta-mass
 // subvector when beta < 1 (entries ranked by |q| descending, ties by id;
 // FP64 prefix sums in that order, the first prefix reaching beta * mass),
 // with weights pre-multiplied by the query's fixed-point scale.
@@ -511,12 +512,16 @@ __device__ int prep_long_row(const DevQueries &q, int64_t n_cols, double beta, c
 __global__ __launch_bounds__(kPrepWaves * kWave) void k_query_prep(DevQueries q, int64_t n_cols,
                                                                    double beta, DevCoarse c,
                                                                    const float *term_max,
-                                                                   double *sabs, int32_t *err)
+                                                                   double *sabs, int32_t *err,
+                                                                   uint32_t *zero, int64_t n_zero)
 {
     __shared__ PrepRow s_row[kPrepWaves];
-    __shared__ int32_t s_longest;
-    if (threadIdx.x == 0) s_longest = 0;
+    __shared__ int32_t s_longest, s_bad;
+    if (threadIdx.x == 0) s_longest = s_bad = 0;
     __syncthreads();
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_zero;
+         i += (int64_t)gridDim.x * blockDim.x)
+        zero[i] = 0u;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = (int)uni((uint32_t)threadIdx.x / kWave);
     const int64_t row = (int64_t)blockIdx.x * kPrepWaves + wave;
@@ -546,18 +551,26 @@ __global__ __launch_bounds__(kPrepWaves * kWave) void k_query_prep(DevQueries q,
         bad = prep_long_row(q, n_cols, beta, c, term_max, sabs, row, a, b);
     if (live && lane == 0) {
         if (bad) {
-            atomicOr(err, bad);
+            atomicOr(&s_bad, bad);
             c.cn[row] = 0;
             c.qinv[row] = 1.0f;
         } else {
             atomicMax(&s_longest, (int32_t)(b - a));
         }
     }
-    // the longest row (sizes the rerank table): one device atomic per workgroup, and none where
-    // the value is already reached (an atomic of every row on one word cost 12 ns each)
+    // flags and the longest row (sizes the rerank table): a lone workgroup writes them (and the
+    // two retry counts behind them); else one device atomic per workgroup, and none where the value
+    // is already reached (an atomic of every row on one word cost 12 ns each)
     __syncthreads();
-    if (threadIdx.x == 0 &&
-        __hip_atomic_load(err + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < s_longest)
+    if (threadIdx.x != 0) return;
+    if (gridDim.x == 1) {
+        err[0] = s_bad;
+        err[1] = s_longest;
+        err[2] = err[3] = 0;
+        return;
+    }
+    if (s_bad) atomicOr(err, s_bad);
+    if (__hip_atomic_load(err + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < s_longest)
         atomicMax(err + 1, s_longest);
 }
 
@@ -712,11 +725,12 @@ __device__ __forceinline__ void unpack_pair(uint32_t wlo, uint32_t whi, int32_t 
 // its candidate list.
 template <int VT, int B, bool SAMPLE>
 __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_accumulate(
-    DevIndex ix, DevQueries q, DevCoarse c, const int32_t *slot_q, int32_t n_slots,
+    DevIndex ix, DevQueries q, DevCoarse c, DevSlots slots,
     int32_t n_sample, float *maxima, const float *theta, uint32_t *count, uint64_t *cand,
     int64_t cap, int32_t tiles_per_wg, int32_t eb)
 {
     constexpr int NT = kAccThreads, NW = NT / kWave;
+    const int32_t n_slots = slots.n;
     const int EB = eb;  // entries merged per pass: a power of two, at most NT
     constexpr int NP = B / 2;            // score words per document
     constexpr int KU = VT == 0 ? 4 : 8;  // chunks in flight per wave
@@ -758,7 +772,7 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))
             int64_t qa = 0;
             float qinv = 1.0f;
             if (s < n_slots) {
-                const int32_t row = slot_q[s];
+                const int32_t row = slots.row(s);
                 qa = q.indptr[row];
                 n = c.cn[row];
                 qinv = c.qinv[row];
@@ -773,11 +787,11 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))
     }
     if (!SAMPLE && tid < B) {
         const int32_t s2 = batch * B + tid;
-        const int64_t a = s2 < n_slots ? sum_threshold(theta[s2], c.qinv[slot_q[s2]])
+        const int64_t a = s2 < n_slots ? sum_threshold(theta ? theta[s2] : -INFINITY, c.qinv[slots.row(s2)])
                                        : (int64_t)INT32_MAX + 1;
         s_none[tid] = a > INT32_MAX;
         s_thr[tid] = a > INT32_MAX ? INT32_MAX : (int32_t)a;
-        const float th = s2 < n_slots ? theta[s2] : 1.0f;
+        const float th = s2 < n_slots ? (theta ? theta[s2] : -INFINITY) : 1.0f;
         s_imp[tid] = th <= 0.0f && th != -INFINITY;
     }
     __syncthreads();
@@ -1098,7 +1112,7 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))
 // the tile's adds touched, so it is all zero again on return).
 template <int VT, bool SAMPLE>
 __device__ __forceinline__ void accumulate1_item(
-    const DevIndex &ix, const DevQueries &q, const DevCoarse &c, const int32_t *slot_q,
+    const DevIndex &ix, const DevQueries &q, const DevCoarse &c, const DevSlots &slots,
     int32_t n_sample, float *maxima, const float *theta, uint32_t *count, uint64_t *cand,
     int64_t cap, int32_t tiles_per_wg, int32_t slot, int64_t run, bool clear_row)
 {
@@ -1108,17 +1122,17 @@ __device__ __forceinline__ void accumulate1_item(
     int32_t *A32 = reinterpret_cast<int32_t *>(smem);  // the query's score row [tile_stride]
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = (int)uni((uint32_t)tid / kWave);
-    const int32_t row = slot_q[slot];
+    const int32_t row = slots.row(slot);
     const int64_t qa = q.indptr[row];
     const int32_t n = c.cn[row];
     const float qinv = c.qinv[row];
     int32_t th = 0;
     bool none = false, imp = false;
     if (!SAMPLE) {
-        const int64_t a = sum_threshold(theta[slot], qinv);
+        const float tv = theta ? theta[slot] : -INFINITY;
+        const int64_t a = sum_threshold(tv, qinv);
         none = a > INT32_MAX;
         th = none ? INT32_MAX : (int32_t)a;
-        const float tv = theta[slot];
         imp = tv <= 0.0f && tv != -INFINITY;
     }
     const int32_t nseg = (n + kWave - 1) / kWave;
@@ -1357,12 +1371,11 @@ __device__ __forceinline__ void accumulate1_item(
 // workgroups resident together score the same tiles.
 template <int VT, bool SAMPLE>
 __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_accumulate1(
-    DevIndex ix, DevQueries q, DevCoarse c, const int32_t *slot_q, int32_t n_slots,
+    DevIndex ix, DevQueries q, DevCoarse c, DevSlots slots,
     int32_t n_sample, float *maxima, const float *theta, uint32_t *count, uint64_t *cand,
     int64_t cap, int32_t tiles_per_wg)
 {
-    (void)n_slots;
-    accumulate1_item<VT, SAMPLE>(ix, q, c, slot_q, n_sample, maxima, theta, count, cand, cap,
+    accumulate1_item<VT, SAMPLE>(ix, q, c, slots, n_sample, maxima, theta, count, cand, cap,
                                  tiles_per_wg, (int32_t)blockIdx.x, (int64_t)blockIdx.y, true);
 }
 
@@ -1374,7 +1387,7 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))
 // once the counter passes the last item; *head must be 0 at launch.
 template <int VT, bool SAMPLE>
 __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_accumulate1_queue(
-    DevIndex ix, DevQueries q, DevCoarse c, const int32_t *slot_q, int32_t n_slots,
+    DevIndex ix, DevQueries q, DevCoarse c, DevSlots slots,
     int32_t n_sample, float *maxima, const float *theta, uint32_t *count, uint64_t *cand,
     int64_t cap, int32_t tiles_per_wg, int64_t n_items, unsigned long long *head)
 {
@@ -1386,8 +1399,8 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))
         const int64_t it = s_item;
         __syncthreads();  // every thread has the item before thread 0 takes the next
         if (it >= n_items) break;
-        accumulate1_item<VT, SAMPLE>(ix, q, c, slot_q, n_sample, maxima, theta, count, cand, cap,
-                                     tiles_per_wg, (int32_t)(it % n_slots), it / n_slots, first);
+        accumulate1_item<VT, SAMPLE>(ix, q, c, slots, n_sample, maxima, theta, count, cand, cap,
+                                     tiles_per_wg, (int32_t)(it % slots.n), it / slots.n, first);
         first = false;
     }
 }
@@ -1454,37 +1467,24 @@ __global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v)
          i += (int64_t)gridDim.x * blockDim.x)
         p[i] = v;
 }
-__global__ void k_iota_i32(int32_t *p, int32_t n, int32_t first)
+// What the host reads when a pass has ended: the rows that need a retry, the query flags and the
+// longest row, into pinned host memory.
+__device__ __forceinline__ void write_report(const DevRetry &r)
 {
-    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-        p[i] = first + i;
+    __hip_atomic_store(r.report, *r.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(r.report + 1, (uint32_t)r.err[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(r.report + 2, (uint32_t)r.err[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-
-// Rows whose status is not kSlotOk, in order: of rows [0, n) (in_rows null)
-// or of in_rows[0, n).  One workgroup; writes the count last.
-__global__ __launch_bounds__(1024) void k_collect_failed(const int32_t *status,
-                                                         const int32_t *in_rows, int32_t n,
-                                                         int32_t *out_rows, uint32_t *count)
-{
-    __shared__ uint32_t s_wsum[1024 / kWave];
-    uint32_t base = 0;
-    for (int32_t i0 = 0; i0 < n; i0 += 1024) {
-        const int32_t i = i0 + (int32_t)threadIdx.x;
-        int32_t row = 0;
-        uint32_t bad = 0;
-        if (i < n) {
-            row = in_rows ? in_rows[i] : i;
-            bad = status[row] != kSlotOk ? 1u : 0u;
-        }
-        uint32_t tot;
-        const uint32_t pos = block_excl_scan<1024>(bad, s_wsum, tot);
-        if (bad) out_rows[base + pos] = row;
-        base += tot;
-    }
-    if (threadIdx.x == 0) *count = base;
-}
+__global__ void k_report(DevRetry r) { write_report(r); }
 
 // ------------------------------------------------------------------ finalize
+// Leave a row to a retry pass (one thread, once per row).
+__device__ __forceinline__ void retry_row(const DevRetry &r, int32_t row)
+{
+    r.status[row] = kSlotRetry;
+    r.rows[atomicAdd(r.count, 1u)] = row;
+}
+
 // The full (unpruned) query row in LDS: 2^lg buckets of two entries {term, term, value, value},
 // empty terms -1.  A term sits in its home bucket or, where that is full, in the next one with
 // room; `spill` says whether any term did that.  With eight buckets per term few tables spill
@@ -1719,9 +1719,9 @@ __device__ __forceinline__ uint32_t wave_place(uint32_t *n, bool take)
 // with eight fixed digits from memory).
 template <bool RERANK, int NT, int R>
 __global__ __launch_bounds__(NT) void k_finalize(
-    DevIndex ix, const int32_t *slot_q, const uint32_t *count, const uint64_t *cand,
+    DevIndex ix, DevSlots slots, const uint32_t *count, const uint64_t *cand,
     const float *theta, int64_t cap, int32_t need, int32_t k, int32_t bm_words, uint64_t *pool,
-    int64_t *out_ids, float *out_scores, int32_t *status)
+    int64_t *out_ids, float *out_scores, DevRetry retry)
 {
     constexpr int NW = NT / kWave;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1732,14 +1732,15 @@ __global__ __launch_bounds__(NT) void k_finalize(
     __shared__ uint32_t s_n, s_wsum[NW];
     const int tid = threadIdx.x;
     const int32_t slot = blockIdx.x;
-    const int32_t row = slot_q ? slot_q[slot] : slot;
+    if (retry.unchecked && retry.err[0]) return;  // malformed queries: no output is written
+    const int32_t row = slots.row(slot);
     const uint32_t cnt = count[slot];
     const float th = theta ? theta[slot] : -INFINITY;
     // threshold <= 0: the scoring pass emitted only nonzero sums; every document it did
     // not emit scores exactly 0
     const bool imp = th <= 0.0f && th != -INFINITY;
     if ((int64_t)cnt > cap || (!imp && (int64_t)cnt < (int64_t)need)) {
-        if (tid == 0) status[row] = kSlotRetry;
+        if (tid == 0) retry_row(retry, row);
         return;
     }
     const uint64_t *cs = cand + (size_t)slot * (size_t)cap;
@@ -1838,7 +1839,12 @@ __global__ __launch_bounds__(NT) void k_finalize(
             for (int64_t i = tid; i < cnt; i += NT) f(cs[i]);
         });
     }
-    if (tid == 0) status[row] = ok ? kSlotOk : kSlotRetry;
+    if (tid == 0) {
+        if (ok)
+            retry.status[row] = kSlotOk;
+        else
+            retry_row(retry, row);
+    }
     if (!ok) return;
     if (RERANK) {
         for (int i = tid; i < need; i += NT) pool[(size_t)slot * (size_t)need + i] = keys[i];
@@ -1860,9 +1866,9 @@ __global__ __launch_bounds__(NT) void k_finalize(
 // key, row bounds and row loads, so it takes one group per wave: one query 8.3 us, 41 us with four
 // groups on eight workgroups.
 __global__ __launch_bounds__(kFinThreads) void k_rerank(DevIndex ix, DevQueries q,
-                                                        const int32_t *slot_q, int32_t need,
+                                                        DevSlots slots, int32_t need,
                                                         int32_t tlg, int32_t groups, uint64_t *pool,
-                                                        int32_t *status)
+                                                        DevRetry retry)
 {
     constexpr int NW = kFinThreads / kWave, EPW = kRerankPerWave;
     static_assert(EPW == 4, "Rows4");
@@ -1871,12 +1877,13 @@ __global__ __launch_bounds__(kFinThreads) void k_rerank(DevIndex ix, DevQueries 
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = (int)uni((uint32_t)threadIdx.x / kWave);
     const int32_t slot = blockIdx.x;
-    const int32_t row = slot_q ? slot_q[slot] : slot;
-    if (status[row] != kSlotOk) return;
+    const int32_t row = slots.row(slot);
+    // (with malformed queries the row bounds mean nothing and the statuses were not written)
+    if ((retry.unchecked && retry.err[0]) || retry.status[row] != kSlotOk) return;
     const int64_t qa = q.indptr[row], qb = q.indptr[row + 1];
     QueryTable tb{reinterpret_cast<int4 *>(smem), table_lg(qb - qa), 0u};
     if (tb.lg > tlg) {  // the launch was sized for shorter rows
-        if (threadIdx.x == 0 && blockIdx.y == 0) status[row] = kSlotRetry;
+        if (threadIdx.x == 0 && blockIdx.y == 0) retry_row(retry, row);
         return;
     }
     uint64_t *e = pool + (size_t)slot * (size_t)need;
@@ -1923,17 +1930,18 @@ __global__ __launch_bounds__(kFinThreads) void k_rerank(DevIndex ix, DevQueries 
 // put in order: one query (50 of 500) 5.0 us, 7,000 queries 21 us where sorting the
 // pool (a barrier for each of 45 exchange steps) took 18.4 and 96 us.
 template <bool SELECT>
-__global__ __launch_bounds__(kFinThreads) void k_topk(const int32_t *slot_q, int32_t need,
-                                                      int32_t k, const uint64_t *pool,
-                                                      int64_t *out_ids, float *out_scores,
-                                                      const int32_t *status)
+__global__ __launch_bounds__(kFinThreads) void k_topk(DevSlots slots, int32_t need, int32_t k,
+                                                      const uint64_t *pool, int64_t *out_ids,
+                                                      float *out_scores, DevRetry retry)
 {
     constexpr int NT = kFinThreads;
     extern __shared__ __align__(16) unsigned char smem[];
     uint64_t *keys = reinterpret_cast<uint64_t *>(smem);  // [pow2_at_least(SELECT ? k : need)]
     const int tid = threadIdx.x;
     const int32_t slot = blockIdx.x;
-    const int32_t row = slot_q ? slot_q[slot] : slot;
+    const int32_t row = slots.row(slot);
+    if (slot == 0 && tid == 0) write_report(retry);  // the pass's last kernel
+    if (retry.unchecked && retry.err[0]) return;
     const uint64_t *e = pool + (size_t)slot * (size_t)need;
     if constexpr (SELECT) {
         __shared__ SelectLds L;
@@ -1942,7 +1950,7 @@ __global__ __launch_bounds__(kFinThreads) void k_topk(const int32_t *slot_q, int
 #pragma unroll
         for (int j = 0; j < kTopkRegs; ++j) key[j] = j * NT + tid < need ? e[j * NT + tid] : 0ull;
         const uint64_t any = e[0];
-        if (status[row] != kSlotOk) return;
+        if (retry.status[row] != kSlotOk) return;
         if (tid == 0) s_n = 0;
         auto each = [&](auto f) {
 #pragma unroll
@@ -1957,7 +1965,7 @@ __global__ __launch_bounds__(kFinThreads) void k_topk(const int32_t *slot_q, int
         });
         sort_and_write<NT>(keys, k, k, row, out_ids, out_scores);
     } else {
-        if (status[row] != kSlotOk) return;
+        if (retry.status[row] != kSlotOk) return;
         for (int i = tid; i < need; i += NT) keys[i] = e[i];
         sort_and_write<NT>(keys, need, k, row, out_ids, out_scores);
     }
@@ -1987,13 +1995,16 @@ __device__ __forceinline__ void cand_bounds(const DevIndex &ix, const int64_t *c
 // candidates of ~180 entries take 11 us (145 us with one workgroup per query).
 __global__ __launch_bounds__(kFinThreads) void k_score_forward(DevIndex ix, DevQueries q,
                                                                const int64_t *cand, int32_t n_cand,
-                                                               int32_t tlg, int32_t groups, float *out)
+                                                               int32_t tlg, int32_t groups,
+                                                               const int32_t *err, int32_t max_qnnz,
+                                                               float *out)
 {
     constexpr int NW = kFinThreads / kWave;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t s_spill;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = (int)uni((uint32_t)threadIdx.x / kWave);
+    if (err[0] || err[1] > max_qnnz) return;  // malformed, or longer rows than the launch is for
     const int64_t b = blockIdx.x;
     QueryTable tb{reinterpret_cast<int4 *>(smem), tlg, 0u};
     const int64_t first = (int64_t)blockIdx.y * groups * NW;
@@ -2020,13 +2031,14 @@ __global__ __launch_bounds__(kFinThreads) void k_score_forward(DevIndex ix, DevQ
 // per query).
 __global__ __launch_bounds__(kFinThreads) void k_score_backward(
     DevIndex ix, DevQueries q, const int64_t *cand, int32_t n_cand, int32_t tlg, int32_t groups,
-    const float *grad, float *gq, float *gx)
+    const int32_t *err, int32_t max_qnnz, const float *grad, float *gq, float *gx)
 {
     constexpr int NW = kFinThreads / kWave;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t s_spill;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = (int)uni((uint32_t)threadIdx.x / kWave);
+    if (err[0] || err[1] > max_qnnz) return;  // as in k_score_forward
     const int64_t b = blockIdx.x;
     const int64_t qa = q.indptr[b], qb = q.indptr[b + 1];
     const int n = (int)(qb - qa);
@@ -2114,7 +2126,7 @@ hipError_t resident_workgroups(F *kernel, size_t lds, int64_t *out)
 
 template <int VT, int B, bool SAMPLE>
 hipError_t run_accumulate(const DevIndex &ix, const DevQueries &q, const DevCoarse &c,
-                          const int32_t *slot_q, int32_t n_slots, int32_t n_sample, float *maxima,
+                          const DevSlots &slots, int32_t n_sample, float *maxima,
                           const float *theta, uint32_t *count, uint64_t *cand, int64_t cap,
                           int32_t tiles_per_wg, int32_t max_terms, unsigned long long *queue,
                           hipStream_t s)
@@ -2127,7 +2139,7 @@ hipError_t run_accumulate(const DevIndex &ix, const DevQueries &q, const DevCoar
     else
         e = set_lds(k_accumulate<VT, B, SAMPLE>, lds);
     if (e != hipSuccess) return e;
-    const int64_t n_batches = (n_slots + B - 1) / B;
+    const int64_t n_batches = (slots.n + B - 1) / B;
     const int64_t n_iter = SAMPLE ? n_sample : ix.n_tiles;
     // Contiguous tile ranges per workgroup (see the kernel); the range length
     // keeps the grid at least a few times the chip's resident workgroups.
@@ -2148,15 +2160,15 @@ hipError_t run_accumulate(const DevIndex &ix, const DevQueries &q, const DevCoar
                 return e;
             const int64_t n_items = n_batches * groups;
             hipLaunchKernelGGL((k_accumulate1_queue<VT, SAMPLE>), dim3((unsigned)std::min(wgs, n_items)),
-                               dim3(kAccThreads), lds, s, ix, q, c, slot_q, n_slots, n_sample,
+                               dim3(kAccThreads), lds, s, ix, q, c, slots, n_sample,
                                maxima, theta, count, cand, cap, (int32_t)per, n_items, queue);
             return hipGetLastError();
         }
         hipLaunchKernelGGL((k_accumulate1<VT, SAMPLE>), grid, dim3(kAccThreads), lds, s, ix, q, c,
-                           slot_q, n_slots, n_sample, maxima, theta, count, cand, cap, (int32_t)per);
+                           slots, n_sample, maxima, theta, count, cand, cap, (int32_t)per);
     } else {
         hipLaunchKernelGGL((k_accumulate<VT, B, SAMPLE>), grid, dim3(kAccThreads), lds, s, ix, q, c,
-                           slot_q, n_slots, n_sample, maxima, theta, count, cand, cap, (int32_t)per,
+                           slots, n_sample, maxima, theta, count, cand, cap, (int32_t)per,
                            (int32_t)eb);
     }
     return hipGetLastError();
@@ -2164,16 +2176,16 @@ hipError_t run_accumulate(const DevIndex &ix, const DevQueries &q, const DevCoar
 
 template <int VT, bool SAMPLE>
 hipError_t dispatch_b(int batch, const DevIndex &ix, const DevQueries &q, const DevCoarse &c,
-                      const int32_t *slot_q, int32_t n_slots, int32_t n_sample, float *maxima,
+                      const DevSlots &slots, int32_t n_sample, float *maxima,
                       const float *theta, uint32_t *count, uint64_t *cand, int64_t cap,
                       int32_t tiles_per_wg, int32_t max_terms, unsigned long long *queue,
                       hipStream_t s)
 {
     switch (batch) {
-    case 1: return run_accumulate<VT, 1, SAMPLE>(ix, q, c, slot_q, n_slots, n_sample, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
-    case 2: return run_accumulate<VT, 2, SAMPLE>(ix, q, c, slot_q, n_slots, n_sample, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, nullptr, s);
-    case 4: return run_accumulate<VT, 4, SAMPLE>(ix, q, c, slot_q, n_slots, n_sample, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, nullptr, s);
-    case 8: return run_accumulate<VT, 8, SAMPLE>(ix, q, c, slot_q, n_slots, n_sample, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, nullptr, s);
+    case 1: return run_accumulate<VT, 1, SAMPLE>(ix, q, c, slots, n_sample, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
+    case 2: return run_accumulate<VT, 2, SAMPLE>(ix, q, c, slots, n_sample, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, nullptr, s);
+    case 4: return run_accumulate<VT, 4, SAMPLE>(ix, q, c, slots, n_sample, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, nullptr, s);
+    case 8: return run_accumulate<VT, 8, SAMPLE>(ix, q, c, slots, n_sample, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, nullptr, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -2206,31 +2218,35 @@ hipError_t allow_lds(const void *kernel, size_t bytes)
 
 hipError_t launch_query_prep(const DevQueries &q, int64_t n_cols, double beta, DevCoarse c,
                              const float *term_max, double *scratch_abs, int32_t *err_flag,
-                             hipStream_t s)
+                             uint32_t *zero, int64_t n_zero, hipStream_t s)
 {
     if (q.n_rows == 0) return hipSuccess;
     dim3 grid((unsigned)((q.n_rows + kPrepWaves - 1) / kPrepWaves));
+    if (grid.x > 1) {
+        const hipError_t e = launch_fill_u32(reinterpret_cast<uint32_t *>(err_flag), 4, 0u, s);
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(k_query_prep, grid, dim3(kPrepWaves * kWave), 0, s, q, n_cols, beta, c, term_max,
-                       scratch_abs, err_flag);
+                       scratch_abs, err_flag, zero, n_zero);
     return hipGetLastError();
 }
 
 hipError_t launch_accumulate(const DevIndex &ix, const DevQueries &q, const DevCoarse &c,
-                             int batch, bool sample, const int32_t *slot_q, int32_t n_slots,
+                             int batch, bool sample, const DevSlots &slots,
                              int32_t n_sample_tiles, float *maxima, const float *theta,
                              uint32_t *count, uint64_t *cand, int64_t cap, int32_t tiles_per_wg,
                              int32_t max_terms, unsigned long long *queue, hipStream_t s)
 {
-    if (n_slots == 0 || ix.n_tiles == 0) return hipSuccess;
+    if (slots.n == 0 || ix.n_tiles == 0) return hipSuccess;
     const int vt = ix.value_dtype;
     if (sample) {
-        if (vt == 0) return dispatch_b<0, true>(batch, ix, q, c, slot_q, n_slots, n_sample_tiles, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
-        if (vt == 1) return dispatch_b<1, true>(batch, ix, q, c, slot_q, n_slots, n_sample_tiles, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
-        return dispatch_b<2, true>(batch, ix, q, c, slot_q, n_slots, n_sample_tiles, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
+        if (vt == 0) return dispatch_b<0, true>(batch, ix, q, c, slots, n_sample_tiles, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
+        if (vt == 1) return dispatch_b<1, true>(batch, ix, q, c, slots, n_sample_tiles, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
+        return dispatch_b<2, true>(batch, ix, q, c, slots, n_sample_tiles, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
     }
-    if (vt == 0) return dispatch_b<0, false>(batch, ix, q, c, slot_q, n_slots, n_sample_tiles, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
-    if (vt == 1) return dispatch_b<1, false>(batch, ix, q, c, slot_q, n_slots, n_sample_tiles, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
-    return dispatch_b<2, false>(batch, ix, q, c, slot_q, n_slots, n_sample_tiles, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
+    if (vt == 0) return dispatch_b<0, false>(batch, ix, q, c, slots, n_sample_tiles, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
+    if (vt == 1) return dispatch_b<1, false>(batch, ix, q, c, slots, n_sample_tiles, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
+    return dispatch_b<2, false>(batch, ix, q, c, slots, n_sample_tiles, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
 }
 
 // Selecting kernels (k_theta, k_finalize): large workgroups while they all run at once, small ones
@@ -2268,29 +2284,19 @@ hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_iota(int32_t *p, int32_t n, int32_t first, hipStream_t s)
+hipError_t launch_report(const DevRetry &r, hipStream_t s)
 {
-    if (n <= 0) return hipSuccess;
-    int32_t blocks = (n + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(k_iota_i32, dim3((unsigned)blocks), dim3(256), 0, s, p, n, first);
+    hipLaunchKernelGGL(k_report, dim3(1), dim3(1), 0, s, r);
     return hipGetLastError();
 }
 
-hipError_t launch_collect_failed(const int32_t *status, const int32_t *in_rows, int32_t n,
-                                 int32_t *out_rows, uint32_t *count, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_collect_failed, dim3(1), dim3(1024), 0, s, status, in_rows, n, out_rows,
-                       count);
-    return hipGetLastError();
-}
-
-hipError_t launch_finalize(const DevIndex &ix, const DevQueries &q, const int32_t *slot_q,
-                           int32_t n_slots, const uint32_t *count, const uint64_t *cand,
+hipError_t launch_finalize(const DevIndex &ix, const DevQueries &q, const DevSlots &slots,
+                           const uint32_t *count, const uint64_t *cand,
                            const float *theta, int64_t cap, int32_t need, int32_t k, bool rerank,
                            int32_t max_qnnz, uint64_t *pool, int64_t *out_ids, float *out_scores,
-                           int32_t *status, hipStream_t s)
+                           const DevRetry &retry, hipStream_t s)
 {
+    const int32_t n_slots = slots.n;
     if (n_slots == 0) return hipSuccess;
     // bitmap of candidate ids below need + cap: zero-score documents in id order
     const int64_t bm = theta ? (need + cap + 31) / 32 : 0;
@@ -2302,16 +2308,18 @@ hipError_t launch_finalize(const DevIndex &ix, const DevQueries &q, const int32_
     auto finalize = [&](auto kernel, int nt) -> hipError_t {
         hipError_t r = set_lds(kernel, lds);
         if (r != hipSuccess) return r;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)n_slots), dim3(nt), lds, s, ix, slot_q, count,
-                           cand, theta, cap, need, k, (int32_t)bm, pool, out_ids, out_scores, status);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)n_slots), dim3(nt), lds, s, ix, slots, count,
+                           cand, theta, cap, need, k, (int32_t)bm, pool, out_ids, out_scores, retry);
         return hipGetLastError();
     };
     // 1,024 threads where every document is a candidate (10,000 of them: 8.3 us, 20 us with 256
     // threads); a threshold leaves one or two thousand, which 256 threads select sooner (one query
     // 5.9 against 6.4 us, 37 queries 7.8 against 9.6)
     const bool wide = n_slots <= kFewSlots && !theta;
-    if (!rerank)
-        return wide ? finalize(k_finalize<false, 1024, 8>, 1024) : finalize(k_finalize<false, 256, 8>, 256);
+    if (!rerank) {
+        e = wide ? finalize(k_finalize<false, 1024, 8>, 1024) : finalize(k_finalize<false, 256, 8>, 256);
+        return e != hipSuccess ? e : launch_report(retry, s);
+    }
     e = wide ? finalize(k_finalize<true, 1024, 8>, 1024) : finalize(k_finalize<true, 256, 8>, 256);
     if (e != hipSuccess) return e;
     const int32_t tlg = table_lg(max_qnnz > 0 ? max_qnnz : 1);
@@ -2325,13 +2333,13 @@ hipError_t launch_finalize(const DevIndex &ix, const DevQueries &q, const int32_
         groups >>= 1;
     const unsigned blocks = (unsigned)((need + kPerGroup * groups - 1) / (kPerGroup * groups));
     hipLaunchKernelGGL(k_rerank, dim3((unsigned)n_slots, blocks), dim3(kFinThreads), lds_t, s, ix,
-                       q, slot_q, need, tlg, groups, pool, status);
+                       q, slots, need, tlg, groups, pool, retry);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     auto topk = [&](auto kernel, size_t bytes) -> hipError_t {
         hipError_t r = set_lds(kernel, bytes);
         if (r != hipSuccess) return r;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)n_slots), dim3(kFinThreads), bytes, s, slot_q,
-                           need, k, pool, out_ids, out_scores, status);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)n_slots), dim3(kFinThreads), bytes, s, slots,
+                           need, k, pool, out_ids, out_scores, retry);
         return hipGetLastError();
     };
     if (k < need && k <= kRankSort && need > kRankSort && need <= kFinThreads * kTopkRegs)
@@ -2358,7 +2366,8 @@ dim3 score_grid(int64_t n_rows, int64_t n_cand, int32_t groups)
 }  // namespace
 
 hipError_t launch_score_forward(const DevIndex &ix, const DevQueries &q, const int64_t *cand,
-                                int32_t n_cand, int32_t max_qnnz, float *out, hipStream_t s)
+                                int32_t n_cand, const int32_t *err, int32_t max_qnnz, float *out,
+                                hipStream_t s)
 {
     if (q.n_rows == 0 || n_cand == 0) return hipSuccess;
     const int32_t tlg = table_lg(max_qnnz), groups = score_groups(q.n_rows, n_cand);
@@ -2366,13 +2375,13 @@ hipError_t launch_score_forward(const DevIndex &ix, const DevQueries &q, const i
     hipError_t e = set_lds(k_score_forward, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_score_forward, score_grid(q.n_rows, n_cand, groups), dim3(kFinThreads),
-                       lds, s, ix, q, cand, n_cand, tlg, groups, out);
+                       lds, s, ix, q, cand, n_cand, tlg, groups, err, max_qnnz, out);
     return hipGetLastError();
 }
 
 hipError_t launch_score_backward(const DevIndex &ix, const DevQueries &q, const int64_t *cand,
-                                 int32_t n_cand, int32_t max_qnnz, const float *grad, float *gq,
-                                 float *gx, hipStream_t s)
+                                 int32_t n_cand, const int32_t *err, int32_t max_qnnz,
+                                 const float *grad, float *gq, float *gx, hipStream_t s)
 {
     if (q.n_rows == 0 || n_cand == 0 || (!gq && !gx)) return hipSuccess;
     const int32_t tlg = table_lg(max_qnnz), groups = score_groups(q.n_rows, n_cand);
@@ -2380,7 +2389,7 @@ hipError_t launch_score_backward(const DevIndex &ix, const DevQueries &q, const 
     hipError_t e = set_lds(k_score_backward, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_score_backward, score_grid(q.n_rows, n_cand, groups), dim3(kFinThreads),
-                       lds, s, ix, q, cand, n_cand, tlg, groups, grad, gq, gx);
+                       lds, s, ix, q, cand, n_cand, tlg, groups, err, max_qnnz, grad, gq, gx);
     return hipGetLastError();
 }
 

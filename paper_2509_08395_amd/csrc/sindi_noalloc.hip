@@ -88,6 +88,7 @@ sindi_status noalloc_impl(const sindi_index *ix, const sindi_csr *qc, int32_t k,
     Scratch sc = carve_rows(base, pl, qc->n_rows, qc->nnz);
     sc.arena = base + rows;
     sc.arena_bytes = kScratchBytes - rows;
+    sc.report = ix->stage.report_noalloc();
     const DevQueries dq{qc->n_rows, qc->nnz, qc->indptr, qc->indices, qc->values};
     return run_search(ix, sc, pl, dq, true, out_ids, out_scores, s, fn, nullptr, nullptr);
 }

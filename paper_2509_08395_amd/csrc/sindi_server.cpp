@@ -135,8 +135,8 @@ struct Slot {
     size_t region_off = 0, region_bytes = 0;  // the batch's share of the arena (0: none)
     bool wants_retry_buffer = false;          // a retry waits for the server's retry buffer
     Pinned<int64_t> h_ptr, h_ids;
-    Pinned<int32_t> h_idx, h_err;
-    Pinned<uint32_t> h_fail;  // [2] failed-row counts of the stages
+    Pinned<int32_t> h_idx;
+    Pinned<uint32_t> h_report;  // [3] rows the last pass left, query flags, longest row
     Pinned<float> h_val, h_scores;
     std::vector<Request *> reqs;
     Plan pl;
@@ -189,7 +189,7 @@ struct sindi_server {
     void run();
     bool launch(Slot &s, std::vector<Request *> &batch);
     sindi_status enqueue_retry(Slot &s, PassKind kind, const int32_t *rows, uint32_t n,
-                               int32_t *out_rows, uint32_t *out_count, uint32_t *h_count);
+                               int32_t *out_rows, uint32_t *out_count);
     void complete(Slot &s);
     void start_retry(Slot &s);
     void finish(Slot &s, sindi_status st, const std::string &msg);
@@ -259,15 +259,11 @@ bool sindi_server::launch(Slot &s, std::vector<Request *> &batch)
         }
         sindi_status e = enqueue_prep(ix, s.sc, s.pl, s.dq, st);
         if (e != SINDI_OK) return e;
-        e = enqueue_passes(ix, s.sc, s.pl, kPassSampled, s.dq, nullptr, nb, s.d_ids.as<int64_t>(),
-                           s.d_scores.as<float>(), st);
-        if (e != SINDI_OK) return e;
-        e = enqueue_collect_failed(s.sc, nullptr, nb, s.sc.rows, s.sc.n_rows, st);
+        e = enqueue_passes(ix, s.sc, s.pl, kPassSampled, s.dq, nullptr, nb, s.sc.rows, s.sc.n_rows,
+                           false, s.d_ids.as<int64_t>(), s.d_scores.as<float>(), st);
         if (e != SINDI_OK) return e;
         HIP_TRY(hipMemcpyAsync(s.h_ids.p, s.d_ids.p, (size_t)nb * kb * 8, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipMemcpyAsync(s.h_scores.p, s.d_scores.p, (size_t)nb * kb * 4, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipMemcpyAsync(s.h_fail.p, s.sc.n_rows, 4, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipMemcpyAsync(s.h_err.p, s.sc.err, 4, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipEventRecord(s.done, st));
         return SINDI_OK;
     };
@@ -278,21 +274,18 @@ bool sindi_server::launch(Slot &s, std::vector<Request *> &batch)
 }
 
 // Enqueue a retry stage of a slot's batch over the n device-listed rows:
-// the pass, the rows it still leaves unresolved (into out_rows / out_count),
-// the results and that count back to the host, then the slot's event.
+// the pass, the rows it still leaves unresolved (into out_rows / out_count and
+// the slot's report), the results back to the host, then the slot's event.
 sindi_status sindi_server::enqueue_retry(Slot &s, PassKind kind, const int32_t *rows, uint32_t n,
-                                         int32_t *out_rows, uint32_t *out_count, uint32_t *h_count)
+                                         int32_t *out_rows, uint32_t *out_count)
 {
     const hipStream_t st = s.stream;
     const int32_t nb = (int32_t)s.reqs.size();
-    sindi_status e = enqueue_passes(ix, s.sc, s.pl, kind, s.dq, rows, n, s.d_ids.as<int64_t>(),
-                                    s.d_scores.as<float>(), st);
-    if (e != SINDI_OK) return e;
-    e = enqueue_collect_failed(s.sc, rows, n, out_rows, out_count, st);
+    sindi_status e = enqueue_passes(ix, s.sc, s.pl, kind, s.dq, rows, n, out_rows, out_count, false,
+                                    s.d_ids.as<int64_t>(), s.d_scores.as<float>(), st);
     if (e != SINDI_OK) return e;
     HIP_TRY(hipMemcpyAsync(s.h_ids.p, s.d_ids.p, (size_t)nb * s.kb * 8, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipMemcpyAsync(s.h_scores.p, s.d_scores.p, (size_t)nb * s.kb * 4, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipMemcpyAsync(h_count, out_count, 4, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipEventRecord(s.done, st));
     return SINDI_OK;
 }
@@ -347,13 +340,12 @@ void sindi_server::finish(Slot &s, sindi_status st, const std::string &msg)
 // when no row is left.
 void sindi_server::complete(Slot &s)
 {
-    if (s.stage == 0 && s.h_err.p[0] != 0) {
-        finish(s, fail(SINDI_E_INTERNAL, "sindi_server: validated queries flagged 0x%x", s.h_err.p[0]),
+    if (s.stage == 0 && s.h_report.p[1] != 0) {
+        finish(s, fail(SINDI_E_INTERNAL, "sindi_server: validated queries flagged 0x%x", s.h_report.p[1]),
                last_error());
         return;
     }
-    // stage 0 and 2 leave their count in h_fail[0] (rows), stage 1 in h_fail[1] (rows2)
-    const uint32_t left = s.h_fail.p[s.stage == 1 ? 1 : 0];
+    const uint32_t left = s.h_report.p[0];
     if (left == 0) {
         finish(s, SINDI_OK, std::string());
         return;
@@ -386,11 +378,9 @@ void sindi_server::start_retry(Slot &s)
     s.sc.arena_bytes = retry_buf.bytes;
     sindi_status e;
     if (s.stage == 0)
-        e = enqueue_retry(s, kPassFullSample, s.sc.rows, s.h_fail.p[0], s.sc.rows2, s.sc.n_rows + 1,
-                          s.h_fail.p + 1);
+        e = enqueue_retry(s, kPassFullSample, s.sc.rows, s.h_report.p[0], s.sc.rows2, s.sc.n_rows + 1);
     else
-        e = enqueue_retry(s, kPassKeepAll, s.sc.rows2, s.h_fail.p[1], s.sc.rows, s.sc.n_rows,
-                          s.h_fail.p);
+        e = enqueue_retry(s, kPassKeepAll, s.sc.rows2, s.h_report.p[0], s.sc.rows, s.sc.n_rows);
     s.stage += 1;
     if (e != SINDI_OK) {
         s.launch_st = e;  // the dispatcher drains the stream and publishes the error
@@ -535,8 +525,8 @@ sindi_status create_impl(const sindi_index *ix, const sindi_server_params *pp, s
             HIP_TRY(s.h_val.alloc(qn));
             HIP_TRY(s.h_ids.alloc(mb * kk));
             HIP_TRY(s.h_scores.alloc(mb * kk));
-            HIP_TRY(s.h_fail.alloc(2));
-            HIP_TRY(s.h_err.alloc(1));
+            HIP_TRY(s.h_report.alloc(3));
+            s.sc.report = s.h_report.p;
         }
         return SINDI_OK;
     };

@@ -99,7 +99,8 @@ struct Plan {
 struct Scratch {
     int32_t *ct = nullptr, *cn = nullptr, *err = nullptr, *status = nullptr;
     int32_t *rows = nullptr, *rows2 = nullptr;  // failed rows, two lists for two retries
-    uint32_t *n_rows = nullptr;                 // [2] lengths of rows / rows2
+    uint32_t *n_rows = nullptr;                 // [2] lengths of rows / rows2 (behind err[2])
+    uint32_t *report = nullptr;                 // [3] pinned host memory: DevRetry's report
     float *cw = nullptr, *qinv = nullptr;
     double *sabs = nullptr;
     unsigned char *arena = nullptr;
@@ -131,9 +132,27 @@ size_t pass_bytes(const PassShape &sh, const Plan &pl, int64_t g);
 // Most query slots of a pass that an arena of `bytes` holds (0 if not one).
 int64_t pass_group(const PassShape &sh, const Plan &pl, size_t bytes);
 
+// Pinned host memory of an index, allocated with it: what small host queries are packed into for
+// one upload, and the reports of its sindi_search / score calls (under mu) and of its
+// sindi_search_noalloc calls (under the device's lock).
+struct HostStage {
+    static constexpr size_t kBytes = 64 << 10;
+    unsigned char *p = nullptr;
+    HostStage() = default;
+    HostStage(const HostStage &) = delete;
+    HostStage &operator=(const HostStage &) = delete;
+    ~HostStage()
+    {
+        if (p) (void)hipHostFree(p);
+    }
+    hipError_t alloc() { return hipHostMalloc((void **)&p, kBytes + 256, hipHostMallocDefault); }
+    uint32_t *report() const { return reinterpret_cast<uint32_t *>(p + kBytes); }
+    uint32_t *report_noalloc() const { return reinterpret_cast<uint32_t *>(p + kBytes + 128); }
+};
+
 // Grow-only owner of a Scratch (sindi_search's, one per index).
 struct Workspace {
-    DBuf q_ptr, q_idx, q_val, row_part, arena;
+    DBuf q_all, row_part, arena;
     Scratch view;
 };
 
@@ -160,6 +179,7 @@ struct sindi_index {
     std::vector<int64_t> h_tile_doc;
     sindi::DBuf indptr, indices, values, tile_doc, tile_post, term_goff, post_doc, post_val,
         term_max;
+    sindi::HostStage stage;
     std::mutex mu;        // guards ws (the workspace of sindi_search calls)
     sindi::Workspace ws;
 
@@ -186,22 +206,23 @@ sindi_status validate_host_csr(const sindi_csr *m, const char *what, int64_t max
 // Enqueue on s the query preparation of rows [0, nq) of dq: beta-mass
 // coarse terms, fixed-point weights and device-side validation, whose flags
 // land in sc.err[0] (0: every row well formed), the longest row in sc.err[1].
+// Clears the retry counts and what the first group of the sampled pass needs
+// cleared in sc's arena.
 sindi_status enqueue_prep(const sindi_index *ix, const Scratch &sc, const Plan &pl,
                           const DevQueries &dq, hipStream_t s);
 
 // Enqueue on s, after enqueue_prep, passes of one kind over n query rows:
-// rows [0, n) of dq when rows is null, else the rows listed in device memory
-// rows[0, n).  Slots go in groups that fit sc's arena (at least one must).
-// Each row's status lands in sc.status; results in the row's output rows.
+// rows [0, n) of dq when rows is null (the sampled pass), else the rows listed
+// in device memory rows[0, n).  Slots go in groups that fit sc's arena (at
+// least one must).  Results land in the row's output rows; the rows still
+// unresolved in out_rows (not rows), their number in *out_count and, in pinned
+// host memory, sc.report.
+// unchecked: the query flags have not been read yet (the pass then writes no
+// output where they are set).
 sindi_status enqueue_passes(const sindi_index *ix, const Scratch &sc, const Plan &pl,
                             PassKind kind, const DevQueries &dq, const int32_t *rows, int64_t n,
+                            int32_t *out_rows, uint32_t *out_count, bool unchecked,
                             int64_t *out_ids, float *out_scores, hipStream_t s);
-
-// Enqueue the compaction of the rows whose status is not kSlotOk: of rows
-// [0, n) (in_rows null) or of in_rows[0, n), into out_rows, the count into
-// *count (device).
-sindi_status enqueue_collect_failed(const Scratch &sc, const int32_t *in_rows, int64_t n,
-                                    int32_t *out_rows, uint32_t *count, hipStream_t s);
 
 // Synchronous search of validated device queries dq with the scratch sc:
 // prep, sampled (or keep-all) passes, then for rows whose threshold missed a

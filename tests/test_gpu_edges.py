@@ -146,3 +146,51 @@ def test_selection_with_ties(sindi, nd, cand_cap, nq, signed):
             ids, sc = _np(got[0]), _np(got[1])
             assert np.array_equal(ids[:, :n], ref[0]) and np.array_equal(sc[:, :n], ref[1])
             assert (ids[:, n:] == -1).all() and np.isneginf(sc[:, n:]).all()
+
+
+# ------------------------------------------------------------------ calls of few entries
+@pytest.mark.parametrize("lens", [[35], [512], [513], [60, 68], [60, 69], [0], [0, 3]])
+def test_few_entries_malformed_device_queries_write_nothing(sindi, lens):
+    """Device queries on both sides of the sizes that are searched without waiting for their
+    check: each malformed form is refused with the outputs untouched, and the next call on the
+    same index is right."""
+    rng = np.random.default_rng(9)
+    vocab = 2_000
+    corpus = synth.random_csr(rng, 4_000, vocab, 40)
+    idx = sindi.Index(corpus, alpha=0.6, window=1_500)
+    q = _rows(rng, lens, vocab)
+    good = sindi.DeviceCsr.from_host(q)
+    host = idx.search(q, 7, gamma=90)  # checked on the host
+    nnz = q.nnz
+
+    def broken():
+        p, i, v = (t.clone() for t in (good.indptr, good.indices, good.values))
+        p[0] = 1
+        yield sindi.DeviceCsr(p, i, v, vocab)
+        p = good.indptr.clone()
+        p[-1] = nnz + 5
+        yield sindi.DeviceCsr(p, i, v, vocab)
+        p = good.indptr.clone()
+        p[-1] = -3
+        yield sindi.DeviceCsr(p, i, v, vocab)
+        if nnz > 1:
+            for bad in (vocab, -1, int(i[0])):
+                j = i.clone()
+                j[1] = bad
+                yield sindi.DeviceCsr(good.indptr, j, v, vocab)
+            w = v.clone()
+            w[nnz - 1] = float("nan")
+            yield sindi.DeviceCsr(good.indptr, i, w, vocab)
+
+    out = (torch.full((q.n_rows, 7), -7, dtype=torch.int64, device="cuda"),
+           torch.full((q.n_rows, 7), 7.0, device="cuda"))
+    for bad in broken():
+        for call in (lambda: idx.search(bad, 7, gamma=90, out=out),
+                     lambda: idx.search_coarse(bad, 7, out=out)):
+            with pytest.raises(sindi.SindiError, match="malformed"):
+                call()
+            assert (out[0] == -7).all() and (out[1] == 7.0).all()
+    got = idx.search(good, 7, gamma=90)
+    assert torch.equal(got[0], host[0]) and torch.equal(got[1], host[1])
+    with pytest.raises(sindi.SindiError, match="malformed"):
+        idx.score(next(broken()), torch.zeros((q.n_rows, 3), dtype=torch.int64, device="cuda"))
