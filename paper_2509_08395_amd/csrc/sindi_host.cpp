@@ -998,14 +998,26 @@ sindi_status search_impl(sindi_index *ix, const sindi_csr *qc, int32_t k,
                       grow_workspace, &ws);
 }
 
-// Check the queries of a pair-score call on the device and run launch(err, bound on the rows).
-// The launch is enqueued behind the check, for rows up to twice the mean, and does nothing where
-// the flags are set or a row is longer; then the flags are read (waiting for the stream), and it
-// is launched again where a row was longer.
-template <typename Launch>
-sindi_status checked_score(sindi_index *ix, const sindi_csr *qc, const char *fn, hipStream_t s,
-                           Launch launch)
+// Wait for the report of a launch_report on s (report[3] was 0 before it).
+sindi_status wait_report(uint32_t *report, hipStream_t s)
 {
+    for (;;) {
+        for (int i = 0; i < 2000; ++i)
+            if (__atomic_load_n(report + 3, __ATOMIC_ACQUIRE)) return SINDI_OK;
+        const hipError_t e = hipStreamQuery(s);  // a stream that failed never writes it
+        if (e == hipErrorNotReady) continue;
+        HIP_TRY(e);
+        if (!__atomic_load_n(report + 3, __ATOMIC_ACQUIRE))
+            return fail(SINDI_E_INTERNAL, "the query check left no report");
+    }
+}
+
+// Check the queries of a pair-score call on the device; *longest: the longest query row.  Waits
+// for the check's report.
+sindi_status check_dev_queries(sindi_index *ix, const sindi_csr *qc, const char *fn, hipStream_t s,
+                               int32_t *longest)
+{
+    *longest = 0;
     if (!qc->on_device) return fail(SINDI_E_INVALID, "%s: queries must be device memory", fn);
     if (qc->n_cols != ix->n_cols) return fail(SINDI_E_INVALID, "%s: column count mismatch", fn);
     if (qc->n_rows < 0 || qc->nnz < 0) return fail(SINDI_E_INVALID, "%s: bad query shape", fn);
@@ -1020,14 +1032,13 @@ sindi_status checked_score(sindi_index *ix, const sindi_csr *qc, const char *fn,
     DevCoarse dc{sc.ct, sc.cw, sc.cn, sc.qinv};
     HIP_TRY(launch_query_prep(dq, ix->n_cols, 1.0, dc, ix->term_max.as<float>(), nullptr, sc.err,
                               nullptr, 0, s));
-    const int64_t mean = (qc->nnz + qc->n_rows - 1) / qc->n_rows;
-    const int32_t bound = (int32_t)std::min<int64_t>(std::max<int64_t>(2 * mean, 32), kQueryHash / 2);
-    HIP_TRY(launch(dq, sc.err, bound));
     uint32_t *report = ix->stage.report();
+    __atomic_store_n(report + 3, 0u, __ATOMIC_RELEASE);
     HIP_TRY(launch_report(DevRetry{sc.err, nullptr, nullptr, sc.n_rows, report, false}, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    sindi_status st = wait_report(report, s);
+    if (st != SINDI_OK) return st;
     if (report[1]) return fail(SINDI_E_INVALID, "%s: malformed query rows (flags 0x%x)", fn, report[1]);
-    if ((int32_t)report[2] > bound) HIP_TRY(launch(dq, sc.err, (int32_t)report[2]));
+    *longest = (int32_t)report[2];
     return SINDI_OK;
 }
 
@@ -1152,12 +1163,14 @@ sindi_status sindi_score_forward(const sindi_index *idx, const sindi_csr *querie
     sindi_index *ix = const_cast<sindi_index *>(idx);
     std::lock_guard<std::mutex> lock(ix->mu);
     hipStream_t s = (hipStream_t)stream;
+    int32_t longest = 0;
+    sindi_status st = check_dev_queries(ix, queries, "sindi_score_forward", s, &longest);
+    if (st != SINDI_OK) return st;
+    DevQueries dq{queries->n_rows, queries->nnz, queries->indptr, queries->indices, queries->values};
     DevIndex dix = ix->dev();
     if (doc_values) dix.values = doc_values;
-    return checked_score(ix, queries, "sindi_score_forward", s,
-                         [&](const DevQueries &q, const int32_t *err, int32_t bound) {
-                             return launch_score_forward(dix, q, cand_ids, n_cand, err, bound, out_scores, s);
-                         });
+    HIP_TRY(launch_score_forward(dix, dq, cand_ids, n_cand, longest, out_scores, s));
+    return SINDI_OK;
 }
 
 sindi_status sindi_score_backward(const sindi_index *idx, const sindi_csr *queries,
@@ -1171,13 +1184,15 @@ sindi_status sindi_score_backward(const sindi_index *idx, const sindi_csr *queri
     sindi_index *ix = const_cast<sindi_index *>(idx);
     std::lock_guard<std::mutex> lock(ix->mu);
     hipStream_t s = (hipStream_t)stream;
+    int32_t longest = 0;
+    sindi_status st = check_dev_queries(ix, queries, "sindi_score_backward", s, &longest);
+    if (st != SINDI_OK) return st;
+    DevQueries dq{queries->n_rows, queries->nnz, queries->indptr, queries->indices, queries->values};
     DevIndex dix = ix->dev();
     if (doc_values) dix.values = doc_values;
-    return checked_score(ix, queries, "sindi_score_backward", s,
-                         [&](const DevQueries &q, const int32_t *err, int32_t bound) {
-                             return launch_score_backward(dix, q, cand_ids, n_cand, err, bound, grad_scores,
-                                                   grad_query_values, grad_doc_values, s);
-                         });
+    HIP_TRY(launch_score_backward(dix, dq, cand_ids, n_cand, longest, grad_scores,
+                                  grad_query_values, grad_doc_values, s));
+    return SINDI_OK;
 }
 
 sindi_status sindi_profile_enable(int32_t enable) { return profile_enable(enable); }

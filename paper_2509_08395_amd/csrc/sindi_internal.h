@@ -109,7 +109,7 @@ struct DevSlots {
 
 // Where a pass leaves its outcome: each row's status, the rows left to a retry (their number in
 // *count, zero when the pass starts), and, written by the pass's last kernel, report (pinned host
-// memory): {*count, err[0], err[1]}.  unchecked: the host has not seen the query flags err yet, so
+// memory): {*count, err[0], err[1]} (and 1, once they are there, by launch_report).  unchecked: the host has not seen the query flags err yet, so
 // a flagged call must write no output.
 struct DevRetry {
     const int32_t *err;
@@ -192,15 +192,12 @@ hipError_t build_deal_chunks(const uint32_t *goff, const int64_t *tile_post, int
                              int64_t n_cols, int32_t vbytes, uint16_t *post_doc, void *post_val,
                              hipStream_t s);
 
-// Pair scores and their gradients; max_qnnz: bound on the query rows (sizes the query tables).
-// err: k_query_prep's flags; a launch whose rows are flagged, or whose longest row is beyond the
-// bound, does nothing.
+// Pair scores and their gradients; max_qnnz: the longest query row (sizes the query tables).
 hipError_t launch_score_forward(const DevIndex &ix, const DevQueries &q, const int64_t *cand,
-                                int32_t n_cand, const int32_t *err, int32_t max_qnnz, float *out,
-                                hipStream_t s);
+                                int32_t n_cand, int32_t max_qnnz, float *out, hipStream_t s);
 
 hipError_t launch_score_backward(const DevIndex &ix, const DevQueries &q, const int64_t *cand,
-                                 int32_t n_cand, const int32_t *err, int32_t max_qnnz,
-                                 const float *grad, float *gq, float *gx, hipStream_t s);
+                                 int32_t n_cand, int32_t max_qnnz, const float *grad, float *gq,
+                                 float *gx, hipStream_t s);
 
 }  // namespace sindi

@@ -1475,7 +1475,12 @@ __device__ __forceinline__ void write_report(const DevRetry &r)
     __hip_atomic_store(r.report + 1, (uint32_t)r.err[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __hip_atomic_store(r.report + 2, (uint32_t)r.err[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-__global__ void k_report(DevRetry r) { write_report(r); }
+// On its own: for a host that waits for the words and not for the stream (report[3] last).
+__global__ void k_report(DevRetry r)
+{
+    write_report(r);
+    __hip_atomic_store(r.report + 3, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 // ------------------------------------------------------------------ finalize
 // Leave a row to a retry pass (one thread, once per row).
@@ -1995,16 +2000,13 @@ __device__ __forceinline__ void cand_bounds(const DevIndex &ix, const int64_t *c
 // candidates of ~180 entries take 11 us (145 us with one workgroup per query).
 __global__ __launch_bounds__(kFinThreads) void k_score_forward(DevIndex ix, DevQueries q,
                                                                const int64_t *cand, int32_t n_cand,
-                                                               int32_t tlg, int32_t groups,
-                                                               const int32_t *err, int32_t max_qnnz,
-                                                               float *out)
+                                                               int32_t tlg, int32_t groups, float *out)
 {
     constexpr int NW = kFinThreads / kWave;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t s_spill;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = (int)uni((uint32_t)threadIdx.x / kWave);
-    if (err[0] || err[1] > max_qnnz) return;  // malformed, or longer rows than the launch is for
     const int64_t b = blockIdx.x;
     QueryTable tb{reinterpret_cast<int4 *>(smem), tlg, 0u};
     const int64_t first = (int64_t)blockIdx.y * groups * NW;
@@ -2031,14 +2033,13 @@ __global__ __launch_bounds__(kFinThreads) void k_score_forward(DevIndex ix, DevQ
 // per query).
 __global__ __launch_bounds__(kFinThreads) void k_score_backward(
     DevIndex ix, DevQueries q, const int64_t *cand, int32_t n_cand, int32_t tlg, int32_t groups,
-    const int32_t *err, int32_t max_qnnz, const float *grad, float *gq, float *gx)
+    const float *grad, float *gq, float *gx)
 {
     constexpr int NW = kFinThreads / kWave;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t s_spill;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = (int)uni((uint32_t)threadIdx.x / kWave);
-    if (err[0] || err[1] > max_qnnz) return;  // as in k_score_forward
     const int64_t b = blockIdx.x;
     const int64_t qa = q.indptr[b], qb = q.indptr[b + 1];
     const int n = (int)(qb - qa);
@@ -2366,8 +2367,7 @@ dim3 score_grid(int64_t n_rows, int64_t n_cand, int32_t groups)
 }  // namespace
 
 hipError_t launch_score_forward(const DevIndex &ix, const DevQueries &q, const int64_t *cand,
-                                int32_t n_cand, const int32_t *err, int32_t max_qnnz, float *out,
-                                hipStream_t s)
+                                int32_t n_cand, int32_t max_qnnz, float *out, hipStream_t s)
 {
     if (q.n_rows == 0 || n_cand == 0) return hipSuccess;
     const int32_t tlg = table_lg(max_qnnz), groups = score_groups(q.n_rows, n_cand);
@@ -2375,13 +2375,13 @@ hipError_t launch_score_forward(const DevIndex &ix, const DevQueries &q, const i
     hipError_t e = set_lds(k_score_forward, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_score_forward, score_grid(q.n_rows, n_cand, groups), dim3(kFinThreads),
-                       lds, s, ix, q, cand, n_cand, tlg, groups, err, max_qnnz, out);
+                       lds, s, ix, q, cand, n_cand, tlg, groups, out);
     return hipGetLastError();
 }
 
 hipError_t launch_score_backward(const DevIndex &ix, const DevQueries &q, const int64_t *cand,
-                                 int32_t n_cand, const int32_t *err, int32_t max_qnnz,
-                                 const float *grad, float *gq, float *gx, hipStream_t s)
+                                 int32_t n_cand, int32_t max_qnnz, const float *grad, float *gq,
+                                 float *gx, hipStream_t s)
 {
     if (q.n_rows == 0 || n_cand == 0 || (!gq && !gx)) return hipSuccess;
     const int32_t tlg = table_lg(max_qnnz), groups = score_groups(q.n_rows, n_cand);
@@ -2389,7 +2389,7 @@ hipError_t launch_score_backward(const DevIndex &ix, const DevQueries &q, const 
     hipError_t e = set_lds(k_score_backward, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_score_backward, score_grid(q.n_rows, n_cand, groups), dim3(kFinThreads),
-                       lds, s, ix, q, cand, n_cand, tlg, groups, err, max_qnnz, grad, gq, gx);
+                       lds, s, ix, q, cand, n_cand, tlg, groups, grad, gq, gx);
     return hipGetLastError();
 }
 
