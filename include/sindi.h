@@ -104,15 +104,16 @@ typedef struct {
     int32_t cand_cap;        /* per-query candidate buffer entries; 0 -> 32768               */
     int32_t sample_tiles;    /* tiles scored first to set each query's candidate threshold;
                                 0 -> 8, -1 -> no threshold (keep every document)             */
-    int32_t tile_run;        /* consecutive tiles swept by one workgroup; 0 -> 8, 12 or 32 by
-                                the index's kept fraction of corpus entries times the call's
-                                mean query terms (above 12: 8; above 5: 12; else 32); halved
-                                while a launch would hold fewer than 4096 (query, tile run)
-                                items                                                       */
+    int32_t tile_run;        /* work per item of a scoring launch.  One query per workgroup:
+                                queries that an item takes one after another over one tile, at
+                                most 64; batch >= 2: consecutive tiles that a workgroup sweeps.
+                                0 -> by the bytes of a tile's lists and the number of queries;
+                                halved while a launch would hold fewer than 4096 items.  Results
+                                are the same bit for bit.                                      */
     int32_t schedule;        /* scoring launches with one query per workgroup: 1 one
-                                workgroup per (query, tile run); 2 one persistent launch of
-                                the workgroups the device holds at once, each taking (query,
-                                tile run) items from a device queue until it is empty;
+                                workgroup per item; 2 one persistent launch of
+                                the workgroups the device holds at once, each taking
+                                items from a device queue until it is empty;
                                 0 -> 2.  Results are the same bit for bit.                  */
 } sindi_search_params;
 

@@ -15,7 +15,10 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-I", os.path.join(ROOT, "include"),
           "-I", CSRC, "-Wall", "-Wno-unused-result"]
 DEVICE = ["--offload-arch=gfx950", "-munsafe-fp-atomics",
-          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+          # device atomics as written: the kernels elect their lane themselves, and the pass that
+          # rewrites them waits for the result at once
+          "-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]
 
 
 def compile_native(force: bool = True, verbose: bool = False) -> str:

@@ -141,8 +141,7 @@ static_assert(3 * ((accumulate_lds_bytes(1, kDefaultTile) + 128 + 511) / 512 * 5
 constexpr int32_t kDefaultBatch = 1;
 constexpr int32_t kDefaultCandCap = 32768;
 constexpr int32_t kDefaultSampleTiles = 8;
-// one persistent, queue-fed launch per scoring pass (58.7 against 58.9 ms per 7,000 queries
-// with one workgroup per (query, tile run); 79.0 against 80.5 ms on the serving mix)
+// one persistent, queue-fed launch per scoring pass instead of one workgroup per item
 constexpr int32_t kDefaultSchedule = 2;
 constexpr int32_t kDefaultGamma = 500;
 // Device queries of so few entries are searched without waiting for their check (one query, or
@@ -643,25 +642,48 @@ sindi_status build_impl(const sindi_csr *c, const sindi_build_params *p, hipStre
 }  // namespace
 
 // ------------------------------------------------------------------ search
-// Tiles per work item when the call leaves it open.  The workgroups resident together sweep
-// runs of the same tiles, so the lists of a run's tiles are shared through L2 as long as the
-// tiles the workgroups are spread over fit in it; the more list postings a query reads per
-// tile, the shorter the run.  That load is taken as the index's kept fraction of the corpus
-// entries times the mean query length.  Measured at 8.8M documents (scoring pass per 7,000
-// queries): alpha 0.5 and ~35 terms (x = 7.7) fastest at 12 tiles per run (16: 2.9% slower,
-// 8: 1.3%); the serving mix of 5 to 200 terms (x = 22) at 8 (12: 13% slower, 16: 29%); alpha
-// 0.3 and 0.2 with ~35 terms (x = 3.5 and 1.7) at 32 (24: 0.8% and 1.2% slower, 12: 5.6% and
-// 6.9%).
-void set_tile_run(Plan &pl, const sindi_index *ix, const sindi_search_params &p, int64_t nq,
+// Work per item when the call leaves it open.
+//
+// One query per workgroup: queries that an item takes one after another over its tile.  The
+// resident workgroups hold kResident * run / nq tiles at once, and a tile's lists are shared
+// through L2 (4 MB in each XCD) only while those tiles about fit it; a longer run hides an item's
+// set-up.  So the run is the longest power of two that keeps the lists in flight at 10 MB, at
+// least 2 (4 where the whole index stays in the 256 MB memory-side cache, so a miss costs
+// less; 1 where one tile's lists alone pass 4 MB), at most 32, and above those only while the
+// launch holds 16,384 items.  Scoring pass in us, runs 1, 2, 4, 8, 16, 32:
+//   8.8M documents, 1.6 MB a tile, 35 terms:  64 queries 923 762 809 903 903 903; 256: 2582 2063
+//     2051 2379 2889 3252; 1,000: 8907 7609 7355 7268 7560 9415; 7,000: - - 49973 48762 48357 48280;
+//     5 to 200 terms, 256 queries: 2680 2304 2587 3274 3639 3844
+//   1M documents in the cache, 2.3 MB a tile:  400 queries 602 439 423 - - -; 1,000: 1194 917 904
+//     933 1093 1094
+//   1M documents, 16 MB a tile:  256 queries 1536 1904 2173 2177 2175 2181; 1,000: 4004 4625 6177 7678
+//     8611 8598
+//
+// Merged batches (2 to 8 queries per workgroup): consecutive tiles swept by a workgroup, by the
+// index's kept fraction of the corpus entries times the mean query length.
+void set_item_run(Plan &pl, const sindi_index *ix, const sindi_search_params &p, int64_t nq,
                   int64_t nnz)
 {
     if (p.tile_run) {
-        pl.tile_run = p.tile_run;
+        pl.item_run = p.tile_run;
         return;
     }
-    const double kept = ix->nnz > 0 ? (double)ix->n_post / (double)ix->nnz : 1.0;
-    const double x = nq > 0 ? kept * (double)nnz / (double)nq : 0.0;
-    pl.tile_run = x > 12.0 ? 8 : (x > 5.0 ? 12 : 32);
+    if (pl.batch > 1) {
+        const double kept = ix->nnz > 0 ? (double)ix->n_post / (double)ix->nnz : 1.0;
+        const double x = nq > 0 ? kept * (double)nnz / (double)nq : 0.0;
+        pl.item_run = x > 12.0 ? 8 : (x > 5.0 ? 12 : 32);
+        return;
+    }
+    constexpr double kResident = 768.0;  // three workgroups on each of 256 CUs
+    const int64_t tiles = std::max<int64_t>(ix->n_tiles, 1);
+    const double lists = (double)ix->n_slots * (ix->dtype == SINDI_F32 ? 6.0 : 4.0);
+    const double per_tile = lists / (double)tiles;
+    const int32_t least = per_tile > 4e6 ? 1 : (lists <= 256e6 ? 4 : 2);
+    int32_t run = 32;
+    while (run > least && (kResident * run * per_tile > 10e6 * (double)nq ||
+                           tiles * ((nq + run - 1) / run) < 16384))
+        run >>= 1;
+    pl.item_run = run;
 }
 
 sindi_status make_plan(const sindi_index *ix, int64_t nq, int32_t k,
@@ -683,7 +705,7 @@ sindi_status make_plan(const sindi_index *ix, int64_t nq, int32_t k,
         return fail(SINDI_E_INVALID, "%s: batch must be 1, 2, 4 or 8", fn);
     while (b > 1 && (int64_t)accumulate_lds_bytes(b, ix->tile_stride) > ix->max_lds) b >>= 1;
     pl.batch = b;
-    pl.tile_run = p.tile_run;
+    pl.item_run = p.tile_run;
     if (p.schedule < 0 || p.schedule > 2)
         return fail(SINDI_E_INVALID, "%s: schedule must be 0, 1 or 2", fn);
     pl.queue = (p.schedule ? p.schedule : kDefaultSchedule) == 2;
@@ -768,7 +790,7 @@ PassShape pass_shape(const sindi_index *ix, const Plan &pl, PassKind kind)
 size_t pass_bytes(const PassShape &sh, const Plan &pl, int64_t g)
 {
     const size_t n = (size_t)g;
-    return align256(16 + n * 4) + align256(n * 4) + align256(n * (size_t)sh.n_max * 4) +
+    return align256(16 + n * 4) + 2 * align256(n * 4) + align256(n * (size_t)sh.n_max * 4) +
            align256(n * (size_t)sh.cap * 8) + (pl.rerank ? align256(n * (size_t)pl.need * 8) : 0);
 }
 
@@ -776,7 +798,7 @@ int64_t pass_group(const PassShape &sh, const Plan &pl, size_t bytes)
 {
     // pass_bytes(g) >= g * per (alignment only adds, at most 255 bytes per array), so
     // bytes / per bounds g from above and few steps down reach the largest fit
-    const size_t per = 8 + (size_t)sh.n_max * 4 + (size_t)sh.cap * 8 + (pl.rerank ? (size_t)pl.need * 8 : 0);
+    const size_t per = 12 + (size_t)sh.n_max * 4 + (size_t)sh.cap * 8 + (pl.rerank ? (size_t)pl.need * 8 : 0);
     int64_t g = (int64_t)(bytes / per);
     while (g > 0 && pass_bytes(sh, pl, g) > bytes) --g;
     return g;
@@ -827,6 +849,7 @@ sindi_status enqueue_passes(const sindi_index *ix, const Scratch &sc, const Plan
     unsigned long long *queue = reinterpret_cast<unsigned long long *>(take(16 + (size_t)g * 4));
     uint32_t *count = reinterpret_cast<uint32_t *>(queue + 2);
     float *theta = reinterpret_cast<float *>(take((size_t)g * 4));
+    int32_t *sum_min = reinterpret_cast<int32_t *>(take((size_t)g * 4));
     float *maxima = reinterpret_cast<float *>(take((size_t)g * sh.n_max * 4));
     uint64_t *cand = reinterpret_cast<uint64_t *>(take((size_t)g * sh.cap * 8));
     uint64_t *pool = pl.rerank ? reinterpret_cast<uint64_t *>(take((size_t)g * pl.need * 8)) : nullptr;
@@ -844,16 +867,16 @@ sindi_status enqueue_passes(const sindi_index *ix, const Scratch &sc, const Plan
         if (!sh.keep_all) {
             HIP_TRY(timed(kProfSample, s, [&] {
                 return launch_accumulate(dix, dq, dc, batch, true, slots, sh.n_sample, maxima,
-                                         nullptr, nullptr, nullptr, 0, pl.tile_run, pl.max_qnnz,
+                                         nullptr, nullptr, nullptr, nullptr, 0, pl.item_run, pl.max_qnnz,
                                          pl.queue ? queue : nullptr, s);
             }));
             HIP_TRY(timed(kProfTheta, s, [&] {
-                return launch_theta(maxima, sh.n_max, sh.rank, ns, theta, s);
+                return launch_theta(maxima, sh.n_max, sh.rank, slots, sc.qinv, theta, sum_min, s);
             }));
         }
         HIP_TRY(timed(kProfScore, s, [&] {
-            return launch_accumulate(dix, dq, dc, batch, false, slots, 0, nullptr, th, count,
-                                     cand, sh.cap, pl.tile_run, pl.max_qnnz,
+            return launch_accumulate(dix, dq, dc, batch, false, slots, 0, nullptr, th, sum_min, count,
+                                     cand, sh.cap, pl.item_run, pl.max_qnnz,
                                      pl.queue ? queue + 1 : nullptr, s);
         }));
         // without a threshold no sum is left implicit
@@ -950,7 +973,7 @@ sindi_status search_impl(sindi_index *ix, const sindi_csr *qc, int32_t k,
     sindi_status st = make_plan(ix, nq, k, p, rerank, fn, pl);
     if (st != SINDI_OK) return st;
     if (nq == 0) return SINDI_OK;
-    set_tile_run(pl, ix, p, nq, qc->nnz);
+    set_item_run(pl, ix, p, nq, qc->nnz);
     if (qc->on_device && (!qc->indptr || (qc->nnz > 0 && (!qc->indices || !qc->values))))
         return fail(SINDI_E_INVALID, "%s: null query array", fn);
     int64_t longest = 0;

@@ -131,17 +131,19 @@ hipError_t launch_query_prep(const DevQueries &q, int64_t n_cols, double beta, D
                              const float *term_max, double *scratch_abs, int32_t *err_flag,
                              uint32_t *zero, int64_t n_zero, hipStream_t s);
 
-// theta: null keeps every document.  queue: null launches one workgroup per (slot, tile run); otherwise (one query per
+// theta (and sum_min, the least sum that reaches it): null keeps every document.  per_item: the
+// plan's item_run.  queue: null launches one workgroup per item; otherwise (one query per
 // workgroup only) one persistent launch of the device's resident workgroups takes the items
 // from the 8-byte counter *queue, which must be zero when the launch starts.
 hipError_t launch_accumulate(const DevIndex &ix, const DevQueries &q, const DevCoarse &c,
                              int batch, bool sample, const DevSlots &slots,
                              int32_t n_sample_tiles, float *maxima, const float *theta,
-                             uint32_t *count, uint64_t *cand, int64_t cap, int32_t tiles_per_wg,
-                             int32_t max_terms, unsigned long long *queue, hipStream_t s);
+                             const int32_t *sum_min, uint32_t *count, uint64_t *cand, int64_t cap,
+                             int32_t per_item, int32_t max_terms, unsigned long long *queue, hipStream_t s);
 
-hipError_t launch_theta(const float *maxima, int64_t n_maxima, int64_t rank, int32_t n_slots,
-                        float *theta, hipStream_t s);
+// Per slot: the threshold and the least fixed-point sum that reaches it.
+hipError_t launch_theta(const float *maxima, int64_t n_maxima, int64_t rank, const DevSlots &slots,
+                        const float *qinv, float *theta, int32_t *sum_min, hipStream_t s);
 
 hipError_t launch_fill_f32(float *p, int64_t n, float v, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t s);

@@ -80,6 +80,11 @@ __device__ __forceinline__ int64_t uni64(int64_t x)
 {
     return (int64_t)(((uint64_t)uni((uint32_t)((uint64_t)x >> 32)) << 32) | uni((uint32_t)x));
 }
+__device__ __forceinline__ int64_t readlane64(int64_t x, int l)
+{
+    return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), l) << 32) |
+                     (uint32_t)__builtin_amdgcn_readlane((int)x, l));
+}
 // A wave-uniform pointer to global memory, held in scalar registers, and
 // loads of 8 or 16 bytes at a 32-bit byte offset from it (the scalar base +
 // vector offset form of the global load).
@@ -690,6 +695,24 @@ __device__ int64_t sum_threshold(float th, float qinv)
     return hi;
 }
 
+// The same bound by one wave, clamped to INT32_MAX: 64 probes a round.
+__device__ __forceinline__ int32_t sum_threshold_wave(float th, float qinv)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    auto reaches = [&](int64_t a) { return (float)(int32_t)a * qinv >= th; };
+    if (!reaches(INT32_MAX)) return INT32_MAX;
+    int64_t lo = INT32_MIN, hi = INT32_MAX;
+    if (reaches(lo)) return INT32_MIN;
+    while (hi - lo > 1) {  // invariants: !reaches(lo), reaches(hi); probes ascend inside (lo, hi)
+        const int64_t base = lo + 1, span = hi - lo - 1;
+        const uint64_t r = __ballot(reaches(base + span * lane / kWave));
+        const int f = r ? __ffsll((unsigned long long)r) - 1 : kWave;
+        if (f > 0) lo = base + span * (f - 1) / kWave;
+        if (f < kWave) hi = base + span * f / kWave;
+    }
+    return (int32_t)hi;
+}
+
 // Decode a pair-packed 64-bit score word into the two 32-bit sums it holds:
 // the word is H * 2^32 + L (exactly, modulo 2^64) with |L|, |H| < 2^31.
 __device__ __forceinline__ void unpack_pair(uint32_t wlo, uint32_t whi, int32_t &l, int32_t &h)
@@ -1092,29 +1115,37 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))
     }
 }
 
-// The single-query form of k_accumulate (same grid, same scores, same
-// read-out).  Every wave lays out the tile's chunks itself: the query's terms
+// The single-query form of k_accumulate (same scores, same read-out).  One work item: the query
+// slots [s0, s1), at most 64 of them, one after another over one tile.  The tile's data are then
+// fixed for the item, and the workgroups resident together hold the items of one or two tiles,
+// whose lists stay in each XCD's L2 (1.4 MB a tile at 8.8M documents and alpha 0.5) while every
+// query of the call passes over them: 7,000 queries at 8.8M documents read 13.5 GB beyond L2 (98% of
+// the list reads hit) and take 48.3 ms, where items of one query over a run of 12 tiles, drifting
+// apart within the run, read 292 GB (64%) and took 50.6 ms; 1,000 queries over 1M documents 0.90
+// against 1.11 ms.
+//
+// Every wave lays out a query's chunks itself: the query's terms
 // are taken 64 at a time (a segment, one list per lane), and a wave-wide
 // prefix sum over the lists' chunk counts numbers the segment's chunks.  The
 // waves then take batches of KU consecutive chunks: wave w's first batch of a
 // segment is fixed (chunks w KU to w KU + KU - 1, so its loads leave at once),
 // the next ones come from the segment's counter in LDS (one atomic by the
 // wave's first lane, taken while the current batch's loads are in flight), so
-// they finish the tile together however unevenly the lists' lengths and the
-// adds' bank conflicts fall; the counters are reset between the tile's two
+// they finish the query together however unevenly the lists' lengths and the
+// adds' bank conflicts fall; the counters are reset between the query's two
 // barriers.  The layout needs no LDS table:
-// a tile costs the two barriers around its read-out.  The first segment's
-// terms, weights and list bounds (the next tile's prefetched during the
-// current one) stay in registers; further segments are reloaded (cache hits).
+// a query costs the two barriers around its read-out.  The first segment's
+// list bounds are loaded one query ahead, its terms and weights two ahead (a
+// bound's address needs the term); further segments are reloaded (cache hits).
 //
-// One work item: query slot `slot` over tile run `run` (tiles [run R, (run + 1) R)).  The
-// score row must be all zero on entry unless clear_row (the read-out of every tile clears what
-// the tile's adds touched, so it is all zero again on return).
-template <int VT, bool SAMPLE>
+// The score row must be all zero on entry unless clear_row (the read-out of every query clears
+// what its adds touched, so it is all zero again on return).  last() is called once, as the
+// item's last query starts.
+template <int VT, bool SAMPLE, typename Last>
 __device__ __forceinline__ void accumulate1_item(
     const DevIndex &ix, const DevQueries &q, const DevCoarse &c, const DevSlots &slots,
-    int32_t n_sample, float *maxima, const float *theta, uint32_t *count, uint64_t *cand,
-    int64_t cap, int32_t tiles_per_wg, int32_t slot, int64_t run, bool clear_row)
+    int32_t n_sample, float *maxima, const float *theta, const int32_t *sum_min, uint32_t *count,
+    uint64_t *cand, int64_t cap, int64_t ti, int32_t s0, int32_t s1, bool clear_row, Last last)
 {
     constexpr int NT = kAccThreads, NW = NT / kWave;
     constexpr int KU = VT == 0 ? 3 : 5;  // chunks per batch of a wave
@@ -1122,94 +1153,84 @@ __device__ __forceinline__ void accumulate1_item(
     int32_t *A32 = reinterpret_cast<int32_t *>(smem);  // the query's score row [tile_stride]
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = (int)uni((uint32_t)tid / kWave);
-    const int32_t row = slots.row(slot);
-    const int64_t qa = q.indptr[row];
-    const int32_t n = c.cn[row];
-    const float qinv = c.qinv[row];
-    int32_t th = 0;
-    bool none = false, imp = false;
-    if (!SAMPLE) {
-        const float tv = theta ? theta[slot] : -INFINITY;
-        const int64_t a = sum_threshold(tv, qinv);
-        none = a > INT32_MAX;
-        th = none ? INT32_MAX : (int32_t)a;
-        imp = tv <= 0.0f && tv != -INFINITY;
-    }
-    const int32_t nseg = (n + kWave - 1) / kWave;
-    const int32_t term0 = lane < n ? c.ct[qa + lane] : 0;
-    const float w0 = lane < n ? c.cw[qa + lane] : 0.0f;
     using Raw = typename Val<VT>::Raw;
-    const int64_t n_tile_iter = SAMPLE ? n_sample : ix.n_tiles;
-    const int64_t ti_beg = run * tiles_per_wg;
-    const int64_t ti_end = min(n_tile_iter, ti_beg + tiles_per_wg);
-    const size_t toff_stride = (size_t)(ix.n_cols + 1);
-    auto tile_of = [&](int64_t ti) { return SAMPLE ? (ti * ix.n_tiles / n_sample) : ti; };
+    // the item's queries, one per lane: coarse terms, scale, least sum at the threshold
+    const int32_t m = s1 - s0;
+    int64_t r_qa = 0;
+    int32_t r_n = 0, r_th = INT32_MIN;  // r_n bit 16: threshold <= 0, zero sums left implicit
+    float r_qinv = 1.0f;
+    if (lane < m) {
+        const int32_t row = slots.row(s0 + lane);
+        r_qa = q.indptr[row];
+        r_n = c.cn[row];
+        r_qinv = c.qinv[row];
+        if (!SAMPLE && theta) {
+            const float tv = theta[s0 + lane];
+            r_th = sum_min[s0 + lane];
+            r_n |= (tv <= 0.0f && tv != -INFINITY) ? 1 << 16 : 0;
+        }
+    }
+    const int64_t t = SAMPLE ? (ti * ix.n_tiles / n_sample) : ti;
+    const int64_t d0 = uni64(ix.tile_doc[t]);
+    const int32_t len = (int32_t)uni((uint32_t)(ix.tile_doc[t + 1] - d0));
+    const int64_t p0 = uni64(ix.tile_post[t]);
+    const uint64_t G0 = (uint64_t)p0 >> 2;  // first 4-posting group of the tile
+    const uint32_t n_groups = uni((uint32_t)((ix.tile_post[t + 1] - p0) >> 2));
+    const uint32_t *toff = ix.term_goff + (size_t)t * (size_t)(ix.n_cols + 1);
+    // the tile's groups, addressed by 32-bit byte offsets (a tile holds at most
+    // kTileGroupsMax groups; the arrays end with kTailSlots zero postings)
+    const gbytes pd_t =
+        uni_ptr(reinterpret_cast<const unsigned char *>(ix.post_doc) + G0 * sizeof(uint2));
+    const gbytes pv_t =
+        uni_ptr(reinterpret_cast<const unsigned char *>(ix.post_val) + G0 * sizeof(Raw));
 
-    // the score row starts cleared; reading a tile's row clears it again
+    // the score row starts cleared; reading a query's row clears it again
     if (clear_row) {
         int4 *A4 = reinterpret_cast<int4 *>(smem);
         for (int i = tid; i < ix.tile_stride / 4; i += NT) A4[i] = make_int4(0, 0, 0, 0);
     }
-    // Bounds of the first segment's lists in the tile (the next tile's are
-    // loaded during the current one; every lane loads, lanes past the query's
-    // terms read term 0's bounds and ignore them).  The grid gives every
-    // workgroup at least one tile.
-    uint32_t pre_lo, pre_hi;
-    {
-        const uint32_t *toff = ix.term_goff + (size_t)tile_of(ti_beg) * toff_stride;
-        pre_lo = toff[term0];
-        pre_hi = toff[term0 + 1];
-    }
-    // The run's tiles, one per lane (reloaded every 64 tiles): first document,
-    // length, first 4-posting group and group count, so a tile starts without
-    // waiting for memory.
-    int64_t r_d0 = 0;
-    uint64_t r_g0 = 0;
-    int32_t r_len = 0;
-    uint32_t r_ng = 0;
-    int64_t r_base = ti_beg;
-    auto load_run = [&](int64_t base) {
-        const int64_t ti = base + lane;
-        if (ti < ti_end) {
-            const int64_t t = tile_of(ti);
-            r_d0 = ix.tile_doc[t];
-            r_len = (int32_t)(ix.tile_doc[t + 1] - r_d0);
-            const int64_t p0 = ix.tile_post[t];
-            r_g0 = (uint64_t)p0 >> 2;
-            r_ng = (uint32_t)((ix.tile_post[t + 1] - p0) >> 2);
-        }
-    };
-    load_run(r_base);
     // The waves take batches of KU chunks of a segment from the segment's counter, so that
-    // they reach the tile's barrier together; wave w's first batch of a segment is chunks
+    // they reach the query's barrier together; wave w's first batch of a segment is chunks
     // [w KU, (w + 1) KU), so the counters start past the NW first batches.
     constexpr uint32_t kFirstTaken = (uint32_t)(NW * KU);
     __shared__ uint32_t s_next[kMaxSeg];
     for (int i = tid; i < kMaxSeg; i += NT) s_next[i] = kFirstTaken;
+
+    // first segment of query i (none past the item): lane l holds term l
+    auto terms = [&](int32_t i, int32_t &term, float &w) {
+        term = 0;
+        w = 0.0f;
+        if (i >= m) return;  // uniform
+        const int32_t n = __builtin_amdgcn_readlane(r_n, i) & 0xFFFF;
+        const int64_t qa = readlane64(r_qa, i);
+        if (lane < n) {
+            term = (c.ct + qa)[lane];
+            w = (c.cw + qa)[lane];
+        }
+    };
+    int32_t term1, term2;
+    float w1, w2;
+    uint32_t lo, hi;  // lanes past the query's terms read term 0's bounds and ignore them
+    terms(0, term1, w1);
+    terms(1, term2, w2);
+    lo = toff[term1];
+    hi = toff[term1 + 1];
     __syncthreads();
 
-    for (int64_t ti = ti_beg; ti < ti_end; ++ti) {
-        if (ti - r_base == kWave) {
-            r_base = ti;
-            load_run(r_base);
-        }
-        const int j = (int)(ti - r_base);
-        const int64_t t = tile_of(ti);
-        const int64_t d0 = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(r_d0 >> 32), j) << 32) |
-                                     (uint32_t)__builtin_amdgcn_readlane((int)r_d0, j));
-        const int32_t len = __builtin_amdgcn_readlane(r_len, j);
-        const uint64_t G0 = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(r_g0 >> 32), j) << 32) |
-                            (uint32_t)__builtin_amdgcn_readlane((int)r_g0, j);
-        const uint32_t n_groups = (uint32_t)__builtin_amdgcn_readlane((int)r_ng, j);
-        const uint32_t *toff = ix.term_goff + (size_t)t * toff_stride;
-        const uint32_t gs0 = pre_lo & kGoffMask;
-        const uint32_t ng0 = lane < n ? (pre_hi & kGoffMask) - gs0 : 0u;
-        {
-            const int64_t tn = ti + 1 < ti_end ? ti + 1 : ti;
-            const uint32_t *toff2 = ix.term_goff + (size_t)tile_of(tn) * toff_stride;
-            pre_lo = toff2[term0];
-            pre_hi = toff2[term0 + 1];
-        }
+    for (int32_t i = 0; i < m; ++i) {
+        const int32_t slot = s0 + i;
+        const int32_t ni = __builtin_amdgcn_readlane(r_n, i);
+        const int32_t n = ni & 0xFFFF, nseg = (n + kWave - 1) / kWave;
+        const bool imp = (ni & (1 << 16)) != 0;
+        const int64_t qa = readlane64(r_qa, i);
+        const uint32_t gs0 = lo & kGoffMask;
+        const uint32_t ng0 = lane < n ? (hi & kGoffMask) - gs0 : 0u;
+        const float w0 = w1;
+        if (i == m - 1) last();
+        lo = toff[term2];
+        hi = toff[term2 + 1];
+        w1 = w2;
+        terms(i + 2, term2, w2);
         // segment s >= 1: lane l holds list 64 s + l
         auto segment = [&](int32_t s, uint32_t &gs, uint32_t &ng, float &w) {
             gs = 0;
@@ -1224,12 +1245,6 @@ __device__ __forceinline__ void accumulate1_item(
                 ng = (hi & kGoffMask) - gs;
             }
         };
-        // the tile's groups, addressed by 32-bit byte offsets (a tile holds at most
-        // kTileGroupsMax groups; the arrays end with kTailSlots zero postings)
-        const gbytes pd_t =
-            uni_ptr(reinterpret_cast<const unsigned char *>(ix.post_doc) + G0 * sizeof(uint2));
-        const gbytes pv_t =
-            uni_ptr(reinterpret_cast<const unsigned char *>(ix.post_val) + G0 * sizeof(Raw));
         for (int32_t s = 0; s < nseg; ++s) {
             uint32_t gs = gs0, ng = ng0;
             float wl = w0;
@@ -1312,14 +1327,14 @@ __device__ __forceinline__ void accumulate1_item(
             }
         }
         __syncthreads();
-        if (tid < nseg) s_next[tid] = kFirstTaken;  // every wave has taken its last batch of the tile
+        if (tid < nseg) s_next[tid] = kFirstTaken;  // every wave has taken its last batch
 
         // ---- read the row: sample maxima or emit every score at or above the
-        // query's threshold (as in k_accumulate)
-        if (!SAMPLE && none) {
-            for (int m = tid * 4; m < len; m += NT * 4)
-                *reinterpret_cast<int4 *>(A32 + m) = fresh_zero4();
-        } else if (SAMPLE) {
+        // query's threshold (as in k_accumulate; a threshold that no sum reaches is INT32_MAX,
+        // and sums stay within 2^30)
+        const float qinv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r_qinv), i));
+        const int32_t th = __builtin_amdgcn_readlane(r_th, i);
+        if (SAMPLE) {
             int32_t mx = INT32_MIN;
             for (int m = tid; m < len; m += NT) {
                 mx = max(mx, A32[m]);
@@ -1367,40 +1382,54 @@ __device__ __forceinline__ void accumulate1_item(
     }
 }
 
-// One workgroup per (query slot, tile run): grid (slots, runs), slots fastest, so the
-// workgroups resident together score the same tiles.
+// The items of a launch: tile-major, `run` slots each.
+struct AccItems {
+    int64_t n;           // items in all
+    int32_t run, groups; // slots per item, items per tile
+};
+
+// One workgroup per item.
 template <int VT, bool SAMPLE>
 __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_accumulate1(
-    DevIndex ix, DevQueries q, DevCoarse c, DevSlots slots,
-    int32_t n_sample, float *maxima, const float *theta, uint32_t *count, uint64_t *cand,
-    int64_t cap, int32_t tiles_per_wg)
+    DevIndex ix, DevQueries q, DevCoarse c, DevSlots slots, int32_t n_sample, float *maxima,
+    const float *theta, const int32_t *sum_min, uint32_t *count, uint64_t *cand, int64_t cap,
+    AccItems items)
 {
-    accumulate1_item<VT, SAMPLE>(ix, q, c, slots, n_sample, maxima, theta, count, cand, cap,
-                                 tiles_per_wg, (int32_t)blockIdx.x, (int64_t)blockIdx.y, true);
+    const int64_t ti = blockIdx.x / (uint32_t)items.groups;
+    const int32_t s0 = (int32_t)(blockIdx.x % (uint32_t)items.groups) * items.run;
+    accumulate1_item<VT, SAMPLE>(ix, q, c, slots, n_sample, maxima, theta, sum_min, count, cand,
+                                 cap, ti, s0, min(s0 + items.run, slots.n), true, [] {});
 }
 
 // The same work as one persistent launch fed by a device work queue: as many workgroups as
-// the device holds at once, each taking the next (slot, tile run) item from a counter until
-// the queue is empty.  Items run in the grid's order (tile run major, slots in order), so the
-// workgroups resident together still score the same tiles, and a caller that orders its
-// slots by decreasing work starts the long queries of each run first.  Every workgroup leaves
+// the device holds at once, each starting with the item of its own index and taking the next
+// from a counter until the items are used up (the counter is read as an item's last query
+// starts, so the wait for it is hidden).  Items run in the grid's order, so the workgroups
+// resident together still score the same tiles, and a caller that orders its
+// slots by decreasing work starts the long queries of each tile first.  Every workgroup leaves
 // once the counter passes the last item; *head must be 0 at launch.
 template <int VT, bool SAMPLE>
 __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_accumulate1_queue(
-    DevIndex ix, DevQueries q, DevCoarse c, DevSlots slots,
-    int32_t n_sample, float *maxima, const float *theta, uint32_t *count, uint64_t *cand,
-    int64_t cap, int32_t tiles_per_wg, int64_t n_items, unsigned long long *head)
+    DevIndex ix, DevQueries q, DevCoarse c, DevSlots slots, int32_t n_sample, float *maxima,
+    const float *theta, const int32_t *sum_min, uint32_t *count, uint64_t *cand, int64_t cap,
+    AccItems items, unsigned long long *head)
 {
     __shared__ int64_t s_item;
     bool first = true;
-    for (;;) {
-        if (threadIdx.x == 0) s_item = (int64_t)atomicAdd(head, 1ull);
+    for (int64_t it = blockIdx.x; it < items.n;) {
+        const int64_t ti = it / items.groups;
+        const int32_t s0 = (int32_t)(it - ti * items.groups) * items.run;
+        int64_t next = items.n;
+        accumulate1_item<VT, SAMPLE>(ix, q, c, slots, n_sample, maxima, theta, sum_min, count,
+                                     cand, cap, ti, s0, min(s0 + items.run, slots.n), first, [&] {
+                                         if (threadIdx.x == 0 && items.n > gridDim.x)
+                                             next = (int64_t)gridDim.x + (int64_t)atomicAdd(head, 1ull);
+                                     });
+        if (items.n <= gridDim.x) break;
+        // (the item's own barriers lie between this write and the last read)
+        if (threadIdx.x == 0) s_item = next;
         __syncthreads();
-        const int64_t it = s_item;
-        __syncthreads();  // every thread has the item before thread 0 takes the next
-        if (it >= n_items) break;
-        accumulate1_item<VT, SAMPLE>(ix, q, c, slots, n_sample, maxima, theta, count, cand, cap,
-                                     tiles_per_wg, (int32_t)(it % slots.n), it / slots.n, first);
+        it = uni64(s_item);
         first = false;
     }
 }
@@ -1415,7 +1444,8 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))
 // (4,096 maxima): 4.7 us; 7,000 queries: 40 us (7.8 and 150 us with four fixed digits from memory).
 template <int NT, int R>
 __global__ __launch_bounds__(NT) void k_theta(const float *maxima, int64_t n_m, int64_t rank,
-                                              float *theta)
+                                              DevSlots slots, const float *qinv, float *theta,
+                                              int32_t *sum_min)
 {
     __shared__ SelectLds L;
     __shared__ uint32_t s_min;
@@ -1449,9 +1479,13 @@ __global__ __launch_bounds__(NT) void k_theta(const float *maxima, int64_t n_m, 
             for (int64_t i = tid; i < n_m; i += NT) f(ord_f32(mx[i]));
         });
     }
+    if (tid >= kWave) return;
+    float th = unord_f32(key);
+    th = th > -INFINITY ? th : -INFINITY;
+    const int32_t a = sum_threshold_wave(th, qinv[slots.row(blockIdx.x)]);
     if (tid == 0) {
-        const float th = unord_f32(key);
-        theta[blockIdx.x] = th > -INFINITY ? th : -INFINITY;
+        theta[blockIdx.x] = th;
+        sum_min[blockIdx.x] = a;
     }
 }
 
@@ -2125,11 +2159,21 @@ hipError_t resident_workgroups(F *kernel, size_t lds, int64_t *out)
     return hipSuccess;
 }
 
+// Query slots per work item of a one-query launch: `want`, halved while the launch would hold
+// fewer than kItemsMin items; at most 64 (an item's queries sit one per lane).
+constexpr int64_t kItemsMin = 4096;
+int32_t item_run(int32_t want, int64_t n_slots, int64_t n_tiles)
+{
+    int64_t run = want > 0 ? std::min<int64_t>(want, kWave) : 12;
+    while (run > 1 && n_tiles * ((n_slots + run - 1) / run) < kItemsMin) run >>= 1;
+    return (int32_t)run;
+}
+
 template <int VT, int B, bool SAMPLE>
 hipError_t run_accumulate(const DevIndex &ix, const DevQueries &q, const DevCoarse &c,
                           const DevSlots &slots, int32_t n_sample, float *maxima,
-                          const float *theta, uint32_t *count, uint64_t *cand, int64_t cap,
-                          int32_t tiles_per_wg, int32_t max_terms, unsigned long long *queue,
+                          const float *theta, const int32_t *sum_min, uint32_t *count, uint64_t *cand,
+                          int64_t cap, int32_t per_item, int32_t max_terms, unsigned long long *queue,
                           hipStream_t s)
 {
     const int eb = entry_block(B, max_terms);
@@ -2140,37 +2184,45 @@ hipError_t run_accumulate(const DevIndex &ix, const DevQueries &q, const DevCoar
     else
         e = set_lds(k_accumulate<VT, B, SAMPLE>, lds);
     if (e != hipSuccess) return e;
-    const int64_t n_batches = (slots.n + B - 1) / B;
     const int64_t n_iter = SAMPLE ? n_sample : ix.n_tiles;
-    // Contiguous tile ranges per workgroup (see the kernel); the range length
-    // keeps the grid at least a few times the chip's resident workgroups.
-    int64_t per = tiles_per_wg > 0 ? tiles_per_wg : 12;
-    while (per > 1 && n_batches * ((n_iter + per - 1) / per) < 4096) per >>= 1;
-    int64_t groups = (n_iter + per - 1) / per;
-    if (groups > 65535) {
-        groups = 65535;
-        per = (n_iter + groups - 1) / groups;
-        groups = (n_iter + per - 1) / per;
-    }
-    dim3 grid((unsigned)n_batches, (unsigned)groups);
     if constexpr (B == 1) {
-        if (queue) {  // one persistent launch over the (slot, run) items
+        AccItems items;
+        items.run = item_run(per_item, slots.n, n_iter);
+        items.groups = (slots.n + items.run - 1) / items.run;
+        items.n = n_iter * items.groups;
+        if (queue) {  // one persistent launch over the items
             if ((e = set_lds(k_accumulate1_queue<VT, SAMPLE>, lds)) != hipSuccess) return e;
             int64_t wgs = 0;
             if ((e = resident_workgroups(k_accumulate1_queue<VT, SAMPLE>, lds, &wgs)) != hipSuccess)
                 return e;
-            const int64_t n_items = n_batches * groups;
-            hipLaunchKernelGGL((k_accumulate1_queue<VT, SAMPLE>), dim3((unsigned)std::min(wgs, n_items)),
-                               dim3(kAccThreads), lds, s, ix, q, c, slots, n_sample,
-                               maxima, theta, count, cand, cap, (int32_t)per, n_items, queue);
+            hipLaunchKernelGGL((k_accumulate1_queue<VT, SAMPLE>), dim3((unsigned)std::min(wgs, items.n)),
+                               dim3(kAccThreads), lds, s, ix, q, c, slots, n_sample, maxima, theta,
+                               sum_min, count, cand, cap, items, queue);
             return hipGetLastError();
         }
-        hipLaunchKernelGGL((k_accumulate1<VT, SAMPLE>), grid, dim3(kAccThreads), lds, s, ix, q, c,
-                           slots, n_sample, maxima, theta, count, cand, cap, (int32_t)per);
+        if (items.n > INT32_MAX) {  // beyond a grid: the longest items
+            items.run = kWave;
+            items.groups = (slots.n + items.run - 1) / items.run;
+            items.n = n_iter * items.groups;
+            if (items.n > INT32_MAX) return hipErrorInvalidValue;
+        }
+        hipLaunchKernelGGL((k_accumulate1<VT, SAMPLE>), dim3((unsigned)items.n), dim3(kAccThreads), lds,
+                           s, ix, q, c, slots, n_sample, maxima, theta, sum_min, count, cand, cap, items);
     } else {
-        hipLaunchKernelGGL((k_accumulate<VT, B, SAMPLE>), grid, dim3(kAccThreads), lds, s, ix, q, c,
-                           slots, n_sample, maxima, theta, count, cand, cap, (int32_t)per,
-                           (int32_t)eb);
+        const int64_t n_batches = (slots.n + B - 1) / B;
+        // Contiguous tile ranges per workgroup (see the kernel); the range length
+        // keeps the grid at least a few times the chip's resident workgroups.
+        int64_t per = per_item > 0 ? per_item : 12;
+        while (per > 1 && n_batches * ((n_iter + per - 1) / per) < 4096) per >>= 1;
+        int64_t groups = (n_iter + per - 1) / per;
+        if (groups > 65535) {
+            groups = 65535;
+            per = (n_iter + groups - 1) / groups;
+            groups = (n_iter + per - 1) / per;
+        }
+        hipLaunchKernelGGL((k_accumulate<VT, B, SAMPLE>), dim3((unsigned)n_batches, (unsigned)groups),
+                           dim3(kAccThreads), lds, s, ix, q, c, slots, n_sample, maxima, theta, count,
+                           cand, cap, (int32_t)per, (int32_t)eb);
     }
     return hipGetLastError();
 }
@@ -2178,15 +2230,15 @@ hipError_t run_accumulate(const DevIndex &ix, const DevQueries &q, const DevCoar
 template <int VT, bool SAMPLE>
 hipError_t dispatch_b(int batch, const DevIndex &ix, const DevQueries &q, const DevCoarse &c,
                       const DevSlots &slots, int32_t n_sample, float *maxima,
-                      const float *theta, uint32_t *count, uint64_t *cand, int64_t cap,
-                      int32_t tiles_per_wg, int32_t max_terms, unsigned long long *queue,
+                      const float *theta, const int32_t *sum_min, uint32_t *count, uint64_t *cand, int64_t cap,
+                      int32_t per_item, int32_t max_terms, unsigned long long *queue,
                       hipStream_t s)
 {
     switch (batch) {
-    case 1: return run_accumulate<VT, 1, SAMPLE>(ix, q, c, slots, n_sample, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
-    case 2: return run_accumulate<VT, 2, SAMPLE>(ix, q, c, slots, n_sample, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, nullptr, s);
-    case 4: return run_accumulate<VT, 4, SAMPLE>(ix, q, c, slots, n_sample, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, nullptr, s);
-    case 8: return run_accumulate<VT, 8, SAMPLE>(ix, q, c, slots, n_sample, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, nullptr, s);
+    case 1: return run_accumulate<VT, 1, SAMPLE>(ix, q, c, slots, n_sample, maxima, theta, sum_min, count, cand, cap, per_item, max_terms, queue, s);
+    case 2: return run_accumulate<VT, 2, SAMPLE>(ix, q, c, slots, n_sample, maxima, theta, sum_min, count, cand, cap, per_item, max_terms, nullptr, s);
+    case 4: return run_accumulate<VT, 4, SAMPLE>(ix, q, c, slots, n_sample, maxima, theta, sum_min, count, cand, cap, per_item, max_terms, nullptr, s);
+    case 8: return run_accumulate<VT, 8, SAMPLE>(ix, q, c, slots, n_sample, maxima, theta, sum_min, count, cand, cap, per_item, max_terms, nullptr, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -2235,19 +2287,20 @@ hipError_t launch_query_prep(const DevQueries &q, int64_t n_cols, double beta, D
 hipError_t launch_accumulate(const DevIndex &ix, const DevQueries &q, const DevCoarse &c,
                              int batch, bool sample, const DevSlots &slots,
                              int32_t n_sample_tiles, float *maxima, const float *theta,
-                             uint32_t *count, uint64_t *cand, int64_t cap, int32_t tiles_per_wg,
-                             int32_t max_terms, unsigned long long *queue, hipStream_t s)
+                             const int32_t *sum_min, uint32_t *count, uint64_t *cand, int64_t cap,
+                             int32_t per_item, int32_t max_terms, unsigned long long *queue,
+                             hipStream_t s)
 {
     if (slots.n == 0 || ix.n_tiles == 0) return hipSuccess;
     const int vt = ix.value_dtype;
     if (sample) {
-        if (vt == 0) return dispatch_b<0, true>(batch, ix, q, c, slots, n_sample_tiles, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
-        if (vt == 1) return dispatch_b<1, true>(batch, ix, q, c, slots, n_sample_tiles, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
-        return dispatch_b<2, true>(batch, ix, q, c, slots, n_sample_tiles, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
+        if (vt == 0) return dispatch_b<0, true>(batch, ix, q, c, slots, n_sample_tiles, maxima, theta, sum_min, count, cand, cap, per_item, max_terms, queue, s);
+        if (vt == 1) return dispatch_b<1, true>(batch, ix, q, c, slots, n_sample_tiles, maxima, theta, sum_min, count, cand, cap, per_item, max_terms, queue, s);
+        return dispatch_b<2, true>(batch, ix, q, c, slots, n_sample_tiles, maxima, theta, sum_min, count, cand, cap, per_item, max_terms, queue, s);
     }
-    if (vt == 0) return dispatch_b<0, false>(batch, ix, q, c, slots, n_sample_tiles, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
-    if (vt == 1) return dispatch_b<1, false>(batch, ix, q, c, slots, n_sample_tiles, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
-    return dispatch_b<2, false>(batch, ix, q, c, slots, n_sample_tiles, maxima, theta, count, cand, cap, tiles_per_wg, max_terms, queue, s);
+    if (vt == 0) return dispatch_b<0, false>(batch, ix, q, c, slots, n_sample_tiles, maxima, theta, sum_min, count, cand, cap, per_item, max_terms, queue, s);
+    if (vt == 1) return dispatch_b<1, false>(batch, ix, q, c, slots, n_sample_tiles, maxima, theta, sum_min, count, cand, cap, per_item, max_terms, queue, s);
+    return dispatch_b<2, false>(batch, ix, q, c, slots, n_sample_tiles, maxima, theta, sum_min, count, cand, cap, per_item, max_terms, queue, s);
 }
 
 // Selecting kernels (k_theta, k_finalize): large workgroups while they all run at once, small ones
@@ -2255,16 +2308,16 @@ hipError_t launch_accumulate(const DevIndex &ix, const DevQueries &q, const DevC
 // 1,024 threads, 8.7 with 256; of 1,000 queries: 12.4 and 11.2 us.
 constexpr int32_t kFewSlots = 512;
 
-hipError_t launch_theta(const float *maxima, int64_t n_maxima, int64_t rank, int32_t n_slots,
-                        float *theta, hipStream_t s)
+hipError_t launch_theta(const float *maxima, int64_t n_maxima, int64_t rank, const DevSlots &slots,
+                        const float *qinv, float *theta, int32_t *sum_min, hipStream_t s)
 {
-    if (n_slots == 0) return hipSuccess;
-    if (n_slots <= kFewSlots)
-        hipLaunchKernelGGL((k_theta<1024, 4>), dim3((unsigned)n_slots), dim3(1024), 0, s, maxima,
-                           n_maxima, rank, theta);
+    if (slots.n == 0) return hipSuccess;
+    if (slots.n <= kFewSlots)
+        hipLaunchKernelGGL((k_theta<1024, 4>), dim3((unsigned)slots.n), dim3(1024), 0, s, maxima,
+                           n_maxima, rank, slots, qinv, theta, sum_min);
     else
-        hipLaunchKernelGGL((k_theta<256, 16>), dim3((unsigned)n_slots), dim3(256), 0, s, maxima,
-                           n_maxima, rank, theta);
+        hipLaunchKernelGGL((k_theta<256, 16>), dim3((unsigned)slots.n), dim3(256), 0, s, maxima,
+                           n_maxima, rank, slots, qinv, theta, sum_min);
     return hipGetLastError();
 }
 

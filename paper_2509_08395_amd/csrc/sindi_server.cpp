@@ -223,8 +223,8 @@ sindi_status check_row(const sindi_server *srv, const int32_t *idx, const float 
 // completion event.
 bool sindi_server::launch(Slot &s, std::vector<Request *> &batch)
 {
-    // longest queries first: the scoring passes take (query, tile run) items in slot order,
-    // so each run starts with its longest work (results do not depend on the order)
+    // longest queries first: the scoring passes take a tile's items in slot order,
+    // so each tile starts with its longest work (results do not depend on the order)
     std::stable_sort(batch.begin(), batch.end(),
                      [](const Request *a, const Request *b) { return a->nnz > b->nnz; });
     const int32_t nb = (int32_t)batch.size();
@@ -247,7 +247,7 @@ bool sindi_server::launch(Slot &s, std::vector<Request *> &batch)
     s.pl = base;
     s.pl.k = kb;
     s.pl.max_qnnz = longest;  // sizes the kernels' per-query LDS for this batch
-    set_tile_run(s.pl, ix, p.search, nb, nnz);
+    set_item_run(s.pl, ix, p.search, nb, nnz);
     s.stage = 0;
     s.dq = DevQueries{nb, nnz, s.q_ptr.as<int64_t>(), s.q_idx.as<int32_t>(), s.q_val.as<float>()};
     auto enqueue = [&]() -> sindi_status {

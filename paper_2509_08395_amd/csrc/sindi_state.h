@@ -82,7 +82,7 @@ struct DBuf {
 
 // The parameters of one search, resolved against the index.
 struct Plan {
-    int32_t k = 0, gamma = 0, need = 0, batch = 1, n_sample = 0, tile_run = 0;
+    int32_t k = 0, gamma = 0, need = 0, batch = 1, n_sample = 0, item_run = 0;
     bool queue = false;    // scoring passes as one persistent, queue-fed launch
     int32_t max_qnnz = 0;  // bound on every query row's length (rerank table size)
     int64_t cap = 0, rank = 0;
@@ -192,10 +192,9 @@ namespace sindi {
 // Resolve search parameters for nq queries (no device work).
 sindi_status make_plan(const sindi_index *ix, int64_t nq, int32_t k,
                        const sindi_search_params &p, bool rerank, const char *fn, Plan &pl);
-// The plan's tiles per work item: the caller's, else 8, 12 or 32 by the list postings the nq
-// queries (nnz terms) read per tile, taken as the index's kept fraction times their mean
-// length (the tiles the resident workgroups share through L2).
-void set_tile_run(Plan &pl, const sindi_index *ix, const sindi_search_params &p, int64_t nq,
+// The plan's work per item of the scoring passes: the caller's, else by the lists a tile of the
+// index holds and the number of queries (nq, of nnz terms).
+void set_item_run(Plan &pl, const sindi_index *ix, const sindi_search_params &p, int64_t nq,
                   int64_t nnz);
 
 // Structural check of a host CSR (Def. 1).  max_row > 0 bounds row length;
