@@ -40,7 +40,7 @@ namespace {
 constexpr int kWave = 64;
 constexpr int kRerankPerWave = 4;  // pool entries one rerank wave scores at a time
 constexpr int kRerankGroups = 4;   // most such groups per wave (one query table per workgroup)
-constexpr uint32_t kCandBuf = 256;  // candidates a scoring workgroup holds in LDS
+constexpr uint32_t kCandBuf = 384;  // candidates a scoring workgroup holds in LDS
 constexpr int kRankSort = 256;     // most keys put in order by counting the larger ones
 constexpr int kTopkRegs = 8;       // pool keys per thread of a selecting k_topk
 constexpr int64_t kRerankFill = 2048;  // rerank workgroups that fill the chip
@@ -1115,6 +1115,37 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))
     }
 }
 
+// The items of a launch: tile-major, `run` slots each.
+struct AccItems {
+    int64_t n;           // items in all
+    int32_t run, groups; // slots per item, items per tile
+};
+// The arguments of a one-query launch.  They are read from the kernel-argument segment where they
+// are used (acc_args), through the scalar cache: held in registers across the items they took some
+// forty scalar registers, and what did not fit was spilled to vector lanes inside the loops.
+struct AccArgs {
+    DevIndex ix;
+    DevQueries q;
+    DevCoarse c;
+    DevSlots slots;
+    int32_t n_sample;
+    float *maxima;
+    const float *theta;
+    const int32_t *sum_min;
+    uint32_t *count;
+    uint64_t *cand;
+    int64_t cap;
+    AccItems items;
+    unsigned long long *head;
+};
+using acc_args_t = const AccArgs __attribute__((address_space(4))) *;
+__device__ __forceinline__ acc_args_t acc_args()
+{
+    acc_args_t p = (acc_args_t)__builtin_amdgcn_kernarg_segment_ptr();
+    __asm__ volatile("" : "+s"(p));  // a fresh pointer: loads through it are not kept from earlier
+    return p;
+}
+
 // The single-query form of k_accumulate (same scores, same read-out).  One work item: the query
 // slots [s0, s1), at most 64 of them, one after another over one tile.  The tile's data are then
 // fixed for the item, and the workgroups resident together hold the items of one or two tiles,
@@ -1142,10 +1173,8 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))
 // what its adds touched, so it is all zero again on return).  last() is called once, as the
 // item's last query starts.
 template <int VT, bool SAMPLE, typename Last>
-__device__ __forceinline__ void accumulate1_item(
-    const DevIndex &ix, const DevQueries &q, const DevCoarse &c, const DevSlots &slots,
-    int32_t n_sample, float *maxima, const float *theta, const int32_t *sum_min, uint32_t *count,
-    uint64_t *cand, int64_t cap, int64_t ti, int32_t s0, int32_t s1, bool clear_row, Last last)
+__device__ __forceinline__ void accumulate1_item(int64_t ti, int32_t s0, int32_t s1, bool clear_row,
+                                                 Last last)
 {
     constexpr int NT = kAccThreads, NW = NT / kWave;
     constexpr int KU = VT == 0 ? 3 : 5;  // chunks per batch of a wave
@@ -1154,40 +1183,44 @@ __device__ __forceinline__ void accumulate1_item(
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = (int)uni((uint32_t)tid / kWave);
     using Raw = typename Val<VT>::Raw;
+    const acc_args_t g = acc_args();
     // the item's queries, one per lane: coarse terms, scale, least sum at the threshold
     const int32_t m = s1 - s0;
     int64_t r_qa = 0;
     int32_t r_n = 0, r_th = INT32_MIN;  // r_n bit 16: threshold <= 0, zero sums left implicit
     float r_qinv = 1.0f;
+    const bool every = !SAMPLE && !g->theta;  // no threshold: every document is a candidate
     if (lane < m) {
-        const int32_t row = slots.row(s0 + lane);
-        r_qa = q.indptr[row];
-        r_n = c.cn[row];
-        r_qinv = c.qinv[row];
-        if (!SAMPLE && theta) {
-            const float tv = theta[s0 + lane];
-            r_th = sum_min[s0 + lane];
+        const int32_t row = g->slots.rows ? g->slots.rows[s0 + lane] : g->slots.row0 + s0 + lane;
+        r_qa = g->q.indptr[row];
+        r_n = g->c.cn[row];
+        r_qinv = g->c.qinv[row];
+        if (!SAMPLE && !every) {
+            const float tv = g->theta[s0 + lane];
+            r_th = g->sum_min[s0 + lane];
             r_n |= (tv <= 0.0f && tv != -INFINITY) ? 1 << 16 : 0;
         }
     }
-    const int64_t t = SAMPLE ? (ti * ix.n_tiles / n_sample) : ti;
-    const int64_t d0 = uni64(ix.tile_doc[t]);
-    const int32_t len = (int32_t)uni((uint32_t)(ix.tile_doc[t + 1] - d0));
-    const int64_t p0 = uni64(ix.tile_post[t]);
+    const int64_t t = SAMPLE ? (ti * g->ix.n_tiles / g->n_sample) : ti;
+    const int64_t d0 = uni64(g->ix.tile_doc[t]);
+    const int32_t len = (int32_t)uni((uint32_t)(g->ix.tile_doc[t + 1] - d0));
+    const int64_t p0 = uni64(g->ix.tile_post[t]);
     const uint64_t G0 = (uint64_t)p0 >> 2;  // first 4-posting group of the tile
-    const uint32_t n_groups = uni((uint32_t)((ix.tile_post[t + 1] - p0) >> 2));
-    const uint32_t *toff = ix.term_goff + (size_t)t * (size_t)(ix.n_cols + 1);
+    const uint32_t n_groups = uni((uint32_t)((g->ix.tile_post[t + 1] - p0) >> 2));
+    const uint32_t *toff = g->ix.term_goff + (size_t)t * (size_t)(g->ix.n_cols + 1);
+    const int32_t *ct = g->c.ct;
+    const float *cw = g->c.cw;
     // the tile's groups, addressed by 32-bit byte offsets (a tile holds at most
     // kTileGroupsMax groups; the arrays end with kTailSlots zero postings)
     const gbytes pd_t =
-        uni_ptr(reinterpret_cast<const unsigned char *>(ix.post_doc) + G0 * sizeof(uint2));
+        uni_ptr(reinterpret_cast<const unsigned char *>(g->ix.post_doc) + G0 * sizeof(uint2));
     const gbytes pv_t =
-        uni_ptr(reinterpret_cast<const unsigned char *>(ix.post_val) + G0 * sizeof(Raw));
+        uni_ptr(reinterpret_cast<const unsigned char *>(g->ix.post_val) + G0 * sizeof(Raw));
 
     // the score row starts cleared; reading a query's row clears it again
     if (clear_row) {
         int4 *A4 = reinterpret_cast<int4 *>(smem);
-        for (int i = tid; i < ix.tile_stride / 4; i += NT) A4[i] = make_int4(0, 0, 0, 0);
+        for (int i = tid; i < g->ix.tile_stride / 4; i += NT) A4[i] = make_int4(0, 0, 0, 0);
     }
     // The waves take batches of KU chunks of a segment from the segment's counter, so that
     // they reach the query's barrier together; wave w's first batch of a segment is chunks
@@ -1201,16 +1234,13 @@ __device__ __forceinline__ void accumulate1_item(
     // that atomic between the query's barriers, and the workgroups of few queries queue up at
     // their counters: 37 queries over 24 tiles 163 us, 30 us from the buffer; one query over 704
     // tiles 32 and 25 us.
-    // s_cand_n places are given out, those below s_cand_lim hold candidates, query by query: query
-    // i's end at lane i's r_end.
+    // s_cand_n counts them (and those past the buffer's end), query by query: query i's end at lane
+    // i's r_end.
     __shared__ uint64_t s_cand[kCandBuf];
-    __shared__ uint32_t s_cand_n, s_cand_lim, s_place[kWave];
+    __shared__ uint32_t s_cand_n, s_place[kWave];
     uint32_t r_end = 0;
     int32_t i_flush = 0;  // first query whose candidates are in the buffer
-    if (tid == 0) {
-        s_cand_n = 0;
-        s_cand_lim = kCandBuf;
-    }
+    if (tid == 0) s_cand_n = 0;
 
     // first segment of query i (none past the item): lane l holds term l
     auto terms = [&](int32_t i, int32_t &term, float &w) {
@@ -1220,8 +1250,8 @@ __device__ __forceinline__ void accumulate1_item(
         const int32_t n = __builtin_amdgcn_readlane(r_n, i) & 0xFFFF;
         const int64_t qa = readlane64(r_qa, i);
         if (lane < n) {
-            term = (c.ct + qa)[lane];
-            w = (c.cw + qa)[lane];
+            term = (ct + qa)[lane];
+            w = (cw + qa)[lane];
         }
     };
     int32_t term1, term2;
@@ -1254,8 +1284,8 @@ __device__ __forceinline__ void accumulate1_item(
             w = 0.0f;
             const int32_t li = s * kWave + lane;
             if (li < n) {
-                const int32_t term = c.ct[qa + li];
-                w = c.cw[qa + li];
+                const int32_t term = (ct + qa)[li];
+                w = (cw + qa)[li];
                 const uint32_t lo = toff[term], hi = toff[term + 1];
                 gs = lo & kGoffMask;
                 ng = (hi & kGoffMask) - gs;
@@ -1356,71 +1386,33 @@ __device__ __forceinline__ void accumulate1_item(
                 mx = max(mx, A32[m]);
                 A32[m] = 0;
             }
-            maxima[((size_t)slot * n_sample + ti) * NT + tid] = tid < len ? (float)mx * qinv : -INFINITY;
+            const acc_args_t h = acc_args();
+            h->maxima[((size_t)slot * h->n_sample + ti) * NT + tid] = tid < len ? (float)mx * qinv : -INFINITY;
         } else {
+            // The wave's steps: 256 sums each, NW * 256 apart, cleared as they are read.
             const int4 zero = fresh_zero4();  // one per read-out: the loops keep it live
-            // The sums of documents m0 .. m0 + 3 as candidates, by the waves' lanes together.
-            auto keep = [&](const int4 &r, int m0, bool (&ok)[4], bool direct) {
-                if (!direct) {
-                    // into the workgroup's buffer, or out at once where it is full
-                    uint64_t bal[4];
-                    uint32_t tot = 0;
-#pragma unroll
-                    for (int p = 0; p < 4; ++p) {
-                        bal[p] = __ballot(ok[p]);
-                        tot += (uint32_t)__popcll(bal[p]);
-                    }
-                    uint32_t at = 0;
-                    if (lane == 0) at = atomicAdd(&s_cand_n, tot);
-                    at = uni(at);
-                    if (at + tot <= kCandBuf) {
-                        const int32_t v[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-                        for (int p = 0; p < 4; ++p) {
-                            if (ok[p])
-                                s_cand[at + lanes_below(bal[p])] =
-                                    ((uint64_t)(uint32_t)v[p] << 32) | (uint32_t)(i << 16 | (m0 + p));
-                            at += (uint32_t)__popcll(bal[p]);
-                        }
+            int base = wave * 256;
+            if (!every && !imp) {
+                // A lane's sum at the threshold: into the workgroup's buffer, past its end (rare) to
+                // the list at once.
+                auto hit = [&](int32_t v, int m) {
+                    if (v < th) return;
+                    const uint32_t at = atomicAdd(&s_cand_n, 1u);
+                    if (at < kCandBuf) {
+                        s_cand[at] = ((uint64_t)(uint32_t)v << 32) | (uint32_t)(i << 16 | m);
                         return;
                     }
-                    if (lane == 0) atomicMin(&s_cand_lim, at);
-                }
-                const float sv[4] = {(float)r.x * qinv, (float)r.y * qinv, (float)r.z * qinv,
-                                     (float)r.w * qinv};
-                emit_candidates<4>(sv, ok, d0 + m0, count + slot, cand + (size_t)slot * cap, cap);
-            };
-            // The wave's 256 sums from base, some of which may lie past the tile.  Every document
-            // (no threshold): at its own place.  imp (threshold <= 0): every nonzero sum, negative
-            // ones included, so that the finalize kernel may take each document left out as a zero.
-            auto step = [&](int base) {
-                const int m0 = base + lane * 4;
-                int4 r = make_int4(0, 0, 0, 0);
-                if (m0 < len) {
-                    r = *reinterpret_cast<const int4 *>(A32 + m0);
-                    *reinterpret_cast<int4 *>(A32 + m0) = zero;
-                }
-                const int32_t v[4] = {r.x, r.y, r.z, r.w};
-                bool ok[4];
-#pragma unroll
-                for (int p = 0; p < 4; ++p)
-                    ok[p] = m0 + p < len && (imp ? v[p] != 0 : v[p] >= th);
-                if (!theta) {
-                    uint64_t *out = cand + (size_t)slot * cap + d0 + m0;
-#pragma unroll
-                    for (int p = 0; p < 4; ++p)
-                        if (ok[p]) out[p] = make_key((float)v[p] * qinv, (uint32_t)(d0 + m0 + p));
-                    return;
-                }
-                if (__ballot(ok[0] || ok[1] || ok[2] || ok[3])) keep(r, m0, ok, imp);
-            };
-            int base = wave * 256;
-            if (theta && !imp) {
-                // whole steps, four of them read together: most hold no candidate
+                    const acc_args_t h = acc_args();
+                    const uint32_t pos = atomicAdd(h->count + slot, 1u);
+                    if ((int64_t)pos < h->cap)
+                        h->cand[(size_t)slot * h->cap + pos] = make_key((float)v * qinv, (uint32_t)(d0 + m));
+                };
+                // whole steps, four of them read together (most hold no candidate), then at most
+                // one across the tile's end
                 for (; base + 256 <= len; base += 4 * NW * 256) {
                     const int m0 = base + lane * 4;
                     int4 r[4];
-                    int32_t mx = INT32_MIN;
+                    int32_t mx[4];
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         r[k] = make_int4(INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN);
@@ -1430,72 +1422,94 @@ __device__ __forceinline__ void accumulate1_item(
                         }
                     }
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) mx = max(mx, max(max(r[k].x, r[k].y), max(r[k].z, r[k].w)));
-                    if (__ballot(mx >= th) == 0) continue;
+                    for (int k = 0; k < 4; ++k) mx[k] = max(max(r[k].x, r[k].y), max(r[k].z, r[k].w));
+                    if (__ballot(max(max(mx[0], mx[1]), max(mx[2], mx[3])) >= th) == 0) continue;
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
-                        bool ok[4] = {r[k].x >= th, r[k].y >= th, r[k].z >= th, r[k].w >= th};
-                        if (__ballot(ok[0] || ok[1] || ok[2] || ok[3]))
-                            keep(r[k], m0 + k * NW * 256, ok, false);
+                        if (mx[k] < th) continue;
+                        hit(r[k].x, m0 + k * NW * 256);
+                        hit(r[k].y, m0 + k * NW * 256 + 1);
+                        hit(r[k].z, m0 + k * NW * 256 + 2);
+                        hit(r[k].w, m0 + k * NW * 256 + 3);
                     }
                 }
-                // at most one step across the tile's end
                 base = wave * 256 + (len - wave * 256) / (NW * 256) * (NW * 256);
-                if (wave * 256 < len && base + 256 > len && base < len) step(base);
+                const int m0 = base + lane * 4;
+                if (wave * 256 < len && base + 256 > len && m0 < len) {
+                    const int4 r = *reinterpret_cast<const int4 *>(A32 + m0);
+                    *reinterpret_cast<int4 *>(A32 + m0) = zero;
+                    hit(r.x, m0);
+                    if (m0 + 1 < len) hit(r.y, m0 + 1);
+                    if (m0 + 2 < len) hit(r.z, m0 + 2);
+                    if (m0 + 3 < len) hit(r.w, m0 + 3);
+                }
             } else {
-                for (; base < len; base += NW * 256) step(base);
+                const acc_args_t h = acc_args();
+                uint64_t *list = h->cand + (size_t)slot * h->cap;
+                for (; base < len; base += NW * 256) {
+                    const int m0 = base + lane * 4;
+                    int4 r = make_int4(0, 0, 0, 0);
+                    if (m0 < len) {
+                        r = *reinterpret_cast<const int4 *>(A32 + m0);
+                        *reinterpret_cast<int4 *>(A32 + m0) = zero;
+                    }
+                    const float sv[4] = {(float)r.x * qinv, (float)r.y * qinv, (float)r.z * qinv,
+                                         (float)r.w * qinv};
+                    if (every) {  // no threshold: each document at its own place
+#pragma unroll
+                        for (int p = 0; p < 4; ++p)
+                            if (m0 + p < len) list[d0 + m0 + p] = make_key(sv[p], (uint32_t)(d0 + m0 + p));
+                        continue;
+                    }
+                    // threshold <= 0: every nonzero sum, negative ones included, so that the finalize
+                    // kernel may take each document left out as a zero
+                    const bool ok[4] = {r.x != 0 && m0 < len, r.y != 0 && m0 + 1 < len,
+                                        r.z != 0 && m0 + 2 < len, r.w != 0 && m0 + 3 < len};
+                    if (__ballot(ok[0] || ok[1] || ok[2] || ok[3]))
+                        emit_candidates<4>(sv, ok, d0 + m0, h->count + slot, list, h->cap);
+                }
             }
         }
         __syncthreads();
         if (!SAMPLE) {
             // Every wave reads the same count here: the next query's read-out, behind a barrier,
             // is the next to change it.
-            const uint32_t held = min(uni(s_cand_n), uni(s_cand_lim));
+            const uint32_t held = min(uni(s_cand_n), kCandBuf);
             if (lane == i) r_end = held;
             if (held > kCandBuf / 2 || (i == m - 1 && held > 0)) {
                 // one place in its candidate list for each query's entries, all queries at once
+                const acc_args_t h = acc_args();
                 if (wave == 0) {
                     const uint32_t below = (uint32_t)__shfl_up((int)r_end, 1, kWave);
                     const uint32_t start = lane == i_flush ? 0u : below;
                     if (lane >= i_flush && lane <= i && r_end > start)
-                        s_place[lane] = atomicAdd(count + s0 + lane, r_end - start) - start;
+                        s_place[lane] = atomicAdd(h->count + s0 + lane, r_end - start) - start;
                 }
                 __syncthreads();
                 for (uint32_t e = tid; e < held; e += NT) {
                     const uint64_t x = s_cand[e];
                     const int32_t j = (int32_t)((uint32_t)x >> 16), local = (int32_t)(x & 0xFFFFu);
-                    const float s = (float)(int32_t)(x >> 32) * c.qinv[slots.row(s0 + j)];
+                    const float s = (float)(int32_t)(x >> 32) *
+                                    h->c.qinv[h->slots.rows ? h->slots.rows[s0 + j] : h->slots.row0 + s0 + j];
                     const uint32_t pos = s_place[j] + e;
-                    if ((int64_t)pos < cap)
-                        cand[(size_t)(s0 + j) * cap + pos] = make_key(s, (uint32_t)(d0 + local));
+                    if ((int64_t)pos < h->cap)
+                        h->cand[(size_t)(s0 + j) * h->cap + pos] = make_key(s, (uint32_t)(d0 + local));
                 }
                 i_flush = i + 1;
-                if (tid == 0) {
-                    s_cand_n = 0;
-                    s_cand_lim = kCandBuf;
-                }
+                if (tid == 0) s_cand_n = 0;
             }
         }
     }
 }
 
-// The items of a launch: tile-major, `run` slots each.
-struct AccItems {
-    int64_t n;           // items in all
-    int32_t run, groups; // slots per item, items per tile
-};
-
 // One workgroup per item.
 template <int VT, bool SAMPLE>
-__global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_accumulate1(
-    DevIndex ix, DevQueries q, DevCoarse c, DevSlots slots, int32_t n_sample, float *maxima,
-    const float *theta, const int32_t *sum_min, uint32_t *count, uint64_t *cand, int64_t cap,
-    AccItems items)
+__global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_accumulate1(AccArgs)
 {
-    const int64_t ti = blockIdx.x / (uint32_t)items.groups;
-    const int32_t s0 = (int32_t)(blockIdx.x % (uint32_t)items.groups) * items.run;
-    accumulate1_item<VT, SAMPLE>(ix, q, c, slots, n_sample, maxima, theta, sum_min, count, cand,
-                                 cap, ti, s0, min(s0 + items.run, slots.n), true, [] {});
+    const acc_args_t g = acc_args();
+    const int64_t ti = blockIdx.x / (uint32_t)g->items.groups;
+    const int32_t s0 = (int32_t)(blockIdx.x % (uint32_t)g->items.groups) * g->items.run;
+    accumulate1_item<VT, SAMPLE>(ti, s0, min(s0 + g->items.run, g->slots.n), true, [] {});
 }
 
 // The same work as one persistent launch fed by a device work queue: as many workgroups as
@@ -1506,23 +1520,22 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))
 // slots by decreasing work starts the long queries of each tile first.  Every workgroup leaves
 // once the counter passes the last item; *head must be 0 at launch.
 template <int VT, bool SAMPLE>
-__global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_accumulate1_queue(
-    DevIndex ix, DevQueries q, DevCoarse c, DevSlots slots, int32_t n_sample, float *maxima,
-    const float *theta, const int32_t *sum_min, uint32_t *count, uint64_t *cand, int64_t cap,
-    AccItems items, unsigned long long *head)
+__global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_accumulate1_queue(AccArgs)
 {
     __shared__ int64_t s_item;
     bool first = true;
-    for (int64_t it = blockIdx.x; it < items.n;) {
-        const int64_t ti = it / items.groups;
-        const int32_t s0 = (int32_t)(it - ti * items.groups) * items.run;
-        int64_t next = items.n;
-        accumulate1_item<VT, SAMPLE>(ix, q, c, slots, n_sample, maxima, theta, sum_min, count,
-                                     cand, cap, ti, s0, min(s0 + items.run, slots.n), first, [&] {
-                                         if (threadIdx.x == 0 && items.n > gridDim.x)
-                                             next = (int64_t)gridDim.x + (int64_t)atomicAdd(head, 1ull);
-                                     });
-        if (items.n <= gridDim.x) break;
+    for (int64_t it = blockIdx.x;;) {
+        const acc_args_t g = acc_args();
+        if (it >= g->items.n) break;
+        const int64_t ti = it / g->items.groups;
+        const int32_t s0 = (int32_t)(it - ti * g->items.groups) * g->items.run;
+        int64_t next = 0;
+        accumulate1_item<VT, SAMPLE>(ti, s0, min(s0 + g->items.run, g->slots.n), first, [&] {
+            const acc_args_t h = acc_args();
+            if (threadIdx.x == 0 && h->items.n > gridDim.x)
+                next = (int64_t)gridDim.x + (int64_t)atomicAdd(h->head, 1ull);
+        });
+        if (acc_args()->items.n <= gridDim.x) break;
         // (the item's own barriers lie between this write and the last read)
         if (threadIdx.x == 0) s_item = next;
         __syncthreads();
@@ -2284,7 +2297,8 @@ hipError_t run_accumulate(const DevIndex &ix, const DevQueries &q, const DevCoar
     if (e != hipSuccess) return e;
     const int64_t n_iter = SAMPLE ? n_sample : ix.n_tiles;
     if constexpr (B == 1) {
-        AccItems items;
+        AccArgs args{ix, q, c, slots, n_sample, maxima, theta, sum_min, count, cand, cap, {}, queue};
+        AccItems &items = args.items;
         items.run = item_run(per_item, slots.n, n_iter);
         items.groups = (slots.n + items.run - 1) / items.run;
         items.n = n_iter * items.groups;
@@ -2294,8 +2308,7 @@ hipError_t run_accumulate(const DevIndex &ix, const DevQueries &q, const DevCoar
             if ((e = resident_workgroups(k_accumulate1_queue<VT, SAMPLE>, lds, &wgs)) != hipSuccess)
                 return e;
             hipLaunchKernelGGL((k_accumulate1_queue<VT, SAMPLE>), dim3((unsigned)std::min(wgs, items.n)),
-                               dim3(kAccThreads), lds, s, ix, q, c, slots, n_sample, maxima, theta,
-                               sum_min, count, cand, cap, items, queue);
+                               dim3(kAccThreads), lds, s, args);
             return hipGetLastError();
         }
         if (items.n > INT32_MAX) {  // beyond a grid: the longest items
@@ -2305,7 +2318,7 @@ hipError_t run_accumulate(const DevIndex &ix, const DevQueries &q, const DevCoar
             if (items.n > INT32_MAX) return hipErrorInvalidValue;
         }
         hipLaunchKernelGGL((k_accumulate1<VT, SAMPLE>), dim3((unsigned)items.n), dim3(kAccThreads), lds,
-                           s, ix, q, c, slots, n_sample, maxima, theta, sum_min, count, cand, cap, items);
+                           s, args);
     } else {
         const int64_t n_batches = (slots.n + B - 1) / B;
         // Contiguous tile ranges per workgroup (see the kernel); the range length

@@ -194,3 +194,23 @@ def test_few_entries_malformed_device_queries_write_nothing(sindi, lens):
     assert torch.equal(got[0], host[0]) and torch.equal(got[1], host[1])
     with pytest.raises(sindi.SindiError, match="malformed"):
         idx.score(next(broken()), torch.zeros((q.n_rows, 3), dtype=torch.int64, device="cuda"))
+
+
+# ------------------------------------------------------------------ scoring items
+@pytest.mark.parametrize("run", [1, 8, 64])
+@pytest.mark.parametrize("schedule", [1, 2])
+def test_items_of_many_queries(sindi, run, schedule):
+    """Items of up to 64 queries over one tile, with few and with hundreds of candidates per query
+    and tile (the workgroup's candidate buffer filling, flushed inside an item and passed), tiles
+    of 1 to 16,384 documents: exactly the ranking order."""
+    corpus, q, scores = _int_setup(17_400, 600, False, seed=10)
+    ref = _ranked(scores, 40)
+    for tile, window, cap in ((16_384, 16_384, 2_500), (1_000, 3_001, 400)):
+        idx = sindi.Index(corpus, alpha=1.0, window=window, tile=tile, value_dtype="f16")
+        reps = max(1, -(-4096 * run // (600 * idx.info()["n_tiles"])))  # items enough for the run
+        many = synth.Csr(np.concatenate([[0], np.cumsum(np.tile(np.diff(q.indptr), reps))]),
+                         np.tile(q.indices, reps), np.tile(q.values, reps), q.n_cols)
+        got = idx.search_coarse(sindi.DeviceCsr.from_host(many), 40, cand_cap=cap, tile_run=run,
+                                schedule=schedule)
+        assert np.array_equal(_np(got[0]), np.tile(ref[0], (reps, 1)))
+        assert np.array_equal(_np(got[1]), np.tile(ref[1], (reps, 1)))
