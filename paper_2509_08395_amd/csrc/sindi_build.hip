@@ -43,6 +43,8 @@ constexpr int kFillThreads = 1024;   // k_fill_lists workgroup
 constexpr int kFillDocs = 16;        // documents placed together by k_fill_lists (one bit each)
 constexpr int kFillPer = 2;          // entries per thread and batch of k_fill_lists
 constexpr int64_t kFillCap = (int64_t)kFillThreads * kFillPer;  // entries per batch
+constexpr int kOffsetThreads = 1024; // k_list_offsets workgroup (one tile)
+constexpr int kOffsetPer = 8;        // consecutive terms per thread of k_list_offsets
 constexpr int kDealThreads = 256;    // k_deal_chunks workgroup (one list per wave at a time)
 constexpr int kLdsBanks = 32;        // words of one 32-lane LDS pass in distinct classes mod 32
                                      // fall in distinct banks (the LDS has 64 banks)
@@ -415,25 +417,40 @@ __global__ __launch_bounds__(256) void k_prune_long(const int64_t *ptr, const in
         keep[a + e] = rk[i] < s_keep ? 1 : 0;
 }
 
-// One workgroup per (tile, pass of pass_terms terms): the tile's entries are
+// A tile's documents are cut into `parts` of equal length that separate workgroups count and
+// fill, so that an index of few tiles fills the chip: document range of part p of tile t.
+__device__ __forceinline__ void part_docs(const int64_t *tile_doc, int64_t t, int32_t p, int32_t parts,
+                                          int64_t &d0, int64_t &d1)
+{
+    const int64_t a = tile_doc[t], n = tile_doc[t + 1] - a;
+    d0 = a + n * p / parts;
+    d1 = a + n * (p + 1) / parts;
+}
+
+// Counters of one part: the vocabulary rounded up to whole 16-byte loads.
+__host__ __device__ __forceinline__ size_t part_stride(int64_t n_cols) { return (size_t)(n_cols + 7) / 8 * 8; }
+
+// One workgroup per (part of a tile, pass of pass_terms terms): the part's entries are
 // contiguous in the corpus, so the workgroup streams them and counts every
 // kept entry of the pass's terms in LDS, two 16-bit counters per word (a list
 // of a tile holds at most kTileMax < 2^16 entries), then writes the counts.
+// 1M documents in 80 tiles: 0.94 ms with one workgroup a tile, 0.60 ms in 16 parts.
 // Also the largest stored |x| per term (bits of a non-negative float order like
 // the floats; the atomic only where the value read is smaller), the kept total
 // and the storage range check (err bit 32).
 __global__ __launch_bounds__(kCountThreads) void k_count_lists(
     const int64_t *ptr, const int32_t *idx, const float *val, const uint8_t *keep,
-    int64_t n_cols, const int64_t *tile_doc, int32_t dtype, int32_t pass_terms, int64_t passes,
-    uint32_t *cnt, uint32_t *term_max_bits, unsigned long long *n_kept, int32_t *err)
+    int64_t n_cols, const int64_t *tile_doc, int32_t parts, int32_t dtype, int32_t pass_terms,
+    int64_t passes, uint16_t *part_cnt, uint32_t *term_max_bits, unsigned long long *n_kept, int32_t *err)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     uint32_t *c16 = reinterpret_cast<uint32_t *>(smem);  // [(pass_terms + 1) / 2]
     __shared__ unsigned long long s_kept;
     __shared__ int32_t s_bad;
-    const int64_t t = blockIdx.x;
-    const int64_t e0 = ptr[tile_doc[t]], e1 = ptr[tile_doc[t + 1]];
-    uint32_t *c = cnt + (size_t)t * (size_t)(n_cols + 1);
+    int64_t d0, d1;
+    part_docs(tile_doc, blockIdx.x / (uint32_t)parts, (int32_t)(blockIdx.x % (uint32_t)parts), parts, d0, d1);
+    const int64_t e0 = ptr[d0], e1 = ptr[d1];
+    uint16_t *c = part_cnt + (size_t)blockIdx.x * part_stride(n_cols);
     const int lane = threadIdx.x & (kWave - 1);
     for (int64_t pass = blockIdx.y; pass < passes; pass += gridDim.y) {
         const int64_t j0 = pass * pass_terms, j1 = min(n_cols, j0 + pass_terms);
@@ -496,7 +513,7 @@ __global__ __launch_bounds__(kCountThreads) void k_count_lists(
         if (__ballot(bad) && lane == 0) s_bad = 1;
         __syncthreads();
         for (int64_t i = threadIdx.x; i < j1 - j0; i += blockDim.x)
-            c[j0 + i] = (c16[i >> 1] >> ((i & 1) * 16)) & 0xFFFFu;
+            c[j0 + i] = (uint16_t)(c16[i >> 1] >> ((i & 1) * 16));
         if (threadIdx.x == 0) {
             if (s_kept) atomicAdd(n_kept, s_kept);
             if (s_bad) atomicOr(err, 32);
@@ -505,48 +522,85 @@ __global__ __launch_bounds__(kCountThreads) void k_count_lists(
     }
 }
 
-// One workgroup per tile: group offsets of its lists (exclusive scan of
+// One workgroup per tile: its lists' lengths (the parts' counts summed into cnt, each part's
+// count replaced by the postings of the parts before it) and group offsets (exclusive scan of
 // ceil(count / 4) over terms), pad counts in the top two bits, the tile's
 // group total in goff[n_cols] and tile_groups[t]; err bit 16 if the tile holds
 // more than kTileGroupsMax groups.
-__global__ __launch_bounds__(256) void k_list_offsets(const uint32_t *cnt, int64_t n_cols,
-                                                      uint32_t *goff, int64_t *tile_groups,
-                                                      int32_t *err)
+// A thread takes kOffsetPer consecutive terms, a wave scan and the waves' sums give their offsets:
+// 30,522 terms take four rounds of two barriers (80 tiles: 0.14 ms with a barrier per scan step of
+// 256 terms, 0.08 ms with the sums of 16 parts added).
+__global__ __launch_bounds__(kOffsetThreads) void k_list_offsets(uint16_t *part_cnt, int32_t parts,
+                                                                 int64_t n_cols, uint32_t *cnt,
+                                                                 uint32_t *goff, int64_t *tile_groups,
+                                                                 int32_t *err)
 {
-    __shared__ uint64_t s_part[256];
-    __shared__ uint64_t s_base;
+    constexpr int NW = kOffsetThreads / kWave;
+    __shared__ uint32_t s_sum[NW];
     const int64_t t = blockIdx.x;
-    const uint32_t *c = cnt + (size_t)t * (size_t)(n_cols + 1);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    uint16_t *pc = part_cnt + (size_t)t * (size_t)parts * part_stride(n_cols);
+    uint32_t *c = cnt + (size_t)t * (size_t)(n_cols + 1);
     uint32_t *g = goff + (size_t)t * (size_t)(n_cols + 1);
-    if (threadIdx.x == 0) s_base = 0;
-    __syncthreads();
-    for (int64_t j0 = 0; j0 < n_cols; j0 += 256) {
-        const int64_t j = j0 + threadIdx.x;
-        const uint32_t n = j < n_cols ? c[j] : 0u;
-        const uint64_t ng = (n + 3u) / 4u;
-        s_part[threadIdx.x] = ng;
-        __syncthreads();
-        for (int d = 1; d < 256; d <<= 1) {  // inclusive scan (Hillis-Steele)
-            const uint64_t v = threadIdx.x >= d ? s_part[threadIdx.x - d] : 0ull;
-            __syncthreads();
-            s_part[threadIdx.x] += v;
-            __syncthreads();
+    uint64_t base = 0;
+    for (int64_t r = 0; r < n_cols; r += kOffsetThreads * kOffsetPer) {
+        const int64_t j0 = r + (int64_t)tid * kOffsetPer;
+        uint32_t n[kOffsetPer] = {}, mine = 0;
+        static_assert(kOffsetPer == 8, "one 16-byte load a part");
+        if (j0 < n_cols)
+            for (int32_t p0 = 0; p0 < parts; p0 += 4) {  // four parts' counts in flight
+                uint4 k[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (p0 + i < parts)
+                        k[i] = *reinterpret_cast<const uint4 *>(pc + (size_t)(p0 + i) * part_stride(n_cols) + j0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (p0 + i >= parts) break;
+                    *reinterpret_cast<uint4 *>(pc + (size_t)(p0 + i) * part_stride(n_cols) + j0) =
+                        make_uint4(n[0] | n[1] << 16, n[2] | n[3] << 16, n[4] | n[5] << 16, n[6] | n[7] << 16);
+                    const uint32_t w[4] = {k[i].x, k[i].y, k[i].z, k[i].w};
+#pragma unroll
+                    for (int u = 0; u < kOffsetPer; ++u) n[u] += (w[u / 2] >> (16 * (u & 1))) & 0xFFFFu;
+                }
+            }
+#pragma unroll
+        for (int u = 0; u < kOffsetPer; ++u) {
+            if (j0 + u >= n_cols) n[u] = 0;  // (the stride's pad holds no counts)
+            mine += (n[u] + 3u) / 4u;
         }
-        const uint64_t excl = s_base + s_part[threadIdx.x] - ng;
-        if (j < n_cols) g[j] = (uint32_t)(excl & kGoffMask) | (((4u - (n & 3u)) & 3u) << 30);
+        uint32_t incl = mine;
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) {
+            const uint32_t y = (uint32_t)__shfl_up((int)incl, d, kWave);
+            if (lane >= d) incl += y;
+        }
+        if (lane == kWave - 1) s_sum[wave] = incl;
         __syncthreads();
-        if (threadIdx.x == 255) s_base += s_part[255];
+        uint64_t at = base + incl - mine;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            at += w < wave ? s_sum[w] : 0u;
+            base += s_sum[w];
+        }
+#pragma unroll
+        for (int u = 0; u < kOffsetPer; ++u)
+            if (j0 + u < n_cols) {
+                c[j0 + u] = n[u];
+                g[j0 + u] = (uint32_t)(at & kGoffMask) | (((4u - (n[u] & 3u)) & 3u) << 30);
+                at += (n[u] + 3u) / 4u;
+            }
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        g[n_cols] = (uint32_t)(s_base & kGoffMask);
-        tile_groups[t] = (int64_t)s_base;
-        if (s_base > kTileGroupsMax) atomicOr(err, 16);
+    if (tid == 0) {
+        g[n_cols] = (uint32_t)(base & kGoffMask);
+        tile_groups[t] = (int64_t)base;
+        if (base > kTileGroupsMax) atomicOr(err, 16);
     }
 }
 
-// One workgroup per (tile, pass of pass_terms terms) places the tile's kept
-// entries of the pass's terms in their lists, each list holding its documents
+// One workgroup per (part of a tile, pass of pass_terms terms) places the part's kept
+// entries of the pass's terms in their lists (behind those of the parts before it), each list holding its documents
 // in ascending order (Alg. 1).  The documents are taken in batches: up to
 // kFillDocs whole documents of at most kFillCap entries together, or a longer
 // document alone, kFillCap entries at a time.  One LDS word per term holds the
@@ -562,25 +616,32 @@ __global__ __launch_bounds__(256) void k_list_offsets(const uint32_t *cnt, int64
 // advances go with the next batch's bits, two barriers per batch.  The next
 // batch's entries (at most kFillCap from its first) and their lists' offsets
 // are loaded while the current batch is placed.
+// Bound by the latency of its barrier-separated phases (a CU holds one workgroup), so the parts
+// matter where the tiles alone do not cover the CUs: 1M documents in 80 tiles
+// 3.23 ms whole, 1.15 ms in 16 parts.
 __global__ __launch_bounds__(kFillThreads) void k_fill_lists(
     const int64_t *ptr, const int32_t *idx, const float *val, const uint8_t *keep,
-    const int64_t *tile_doc, const int64_t *tile_post, const uint32_t *goff, int64_t n_cols,
-    int32_t dtype, int32_t pass_terms, uint16_t *post_doc, void *post_val)
+    const int64_t *tile_doc, const int64_t *tile_post, const uint32_t *goff,
+    const uint16_t *part_cnt, int32_t parts, int64_t n_cols, int32_t dtype, int32_t pass_terms,
+    uint16_t *post_doc, void *post_val)
 {
     constexpr int P = kFillPer;
     extern __shared__ __align__(16) unsigned char smem[];
     uint32_t *word = reinterpret_cast<uint32_t *>(smem);  // [pass_terms]
     __shared__ int64_t s_bnd[2][kFillDocs + 1];           // first entries of the batch's documents
     const int tid = threadIdx.x;
-    const int64_t t = blockIdx.x;
+    const int64_t t = blockIdx.x / (uint32_t)parts;
     const int64_t j0 = (int64_t)blockIdx.y * pass_terms;
     const int64_t j1 = min(n_cols, j0 + pass_terms);
     if (j0 >= n_cols) return;  // the whole workgroup
     const uint32_t *g = goff + (size_t)t * (size_t)(n_cols + 1);
-    for (int64_t j = tid; j < j1 - j0; j += kFillThreads) word[j] = 0u;
-    const int64_t d0 = tile_doc[t], d1 = tile_doc[t + 1], P0 = tile_post[t];
+    const uint16_t *before = part_cnt + (size_t)blockIdx.x * part_stride(n_cols) + (size_t)j0;
+    for (int64_t j = tid; j < j1 - j0; j += kFillThreads) word[j] = before[j];
+    const int64_t tile0 = tile_doc[t], P0 = tile_post[t];
+    int64_t d, d1;
+    part_docs(tile_doc, t, (int32_t)(blockIdx.x % (uint32_t)parts), parts, d, d1);
     const int64_t e1 = ptr[d1];
-    int64_t d = d0, e = ptr[d0];
+    int64_t e = ptr[d];
     int buf = 0;
     if (tid <= kFillDocs) s_bnd[0][tid] = ptr[min(d + tid, d1)];
     int32_t rj[P], nj[P];  // this batch's entries, and the next batch's (in flight)
@@ -651,7 +712,7 @@ __global__ __launch_bounds__(kFillThreads) void k_fill_lists(
             const uint32_t bits = wd >> 16;
             const uint32_t slot = (wd & 0xFFFFu) + (uint32_t)__popc(bits & ((1u << bit[u]) - 1u));
             const int64_t pos = P0 + 4ll * (int64_t)(go[u] & kGoffMask) + slot;
-            post_doc[pos] = (uint16_t)((d + bit[u] - d0) * 4);
+            post_doc[pos] = (uint16_t)((d + bit[u] - tile0) * 4);
             const float v = rv[u];
             if (dtype == SINDI_F32) reinterpret_cast<float *>(post_val)[pos] = v;
             else
@@ -703,9 +764,11 @@ __global__ void k_fill_pads(const uint32_t *goff, const uint32_t *cnt, const int
 // postings taken by (bank, document) fill, in that order, positions 4 (32 h + r) + p for
 // r = 0..31, h = 0..1, p = 0..3 (those below n), so postings of one bank go to successive bins
 // and a bin holds ceil(count / bins) of them at most.  A chunk of one group (one lane) keeps its
-// order, and pads stay at the list's end.  A wave takes 64 consecutive lists of tile blockIdx.x
-// at a time (their offsets loaded together, a list per lane; the grid's columns stride over the
-// vocabulary) and reorders those of two or more groups one after another.
+// order, and pads stay at the list's end.  A wave takes 64 lists of tile blockIdx.x at a time
+// (their offsets loaded together, a list per lane) and reorders those of two or more groups one
+// after another.  The lists of a wave lie the grid's number of waves apart: the long lists of a
+// vocabulary ordered by frequency sit side by side, and a wave that took 64 neighbours walked
+// some 700 chunks alone (1M documents 1.80 ms, interleaved 0.52 ms).
 __global__ __launch_bounds__(kDealThreads) void k_deal_chunks(const uint32_t *goff,
                                                               const int64_t *tile_post,
                                                               int64_t n_cols, int32_t vbytes,
@@ -717,11 +780,11 @@ __global__ __launch_bounds__(kDealThreads) void k_deal_chunks(const uint32_t *go
     const int64_t t = blockIdx.x;
     const int r = lane & 31, h = lane >> 5;
     const int64_t tile_first = tile_post[t];
-    const int64_t stride = (int64_t)gridDim.y * NW * kWave;
-    for (int64_t j0 = ((int64_t)blockIdx.y * NW + w) * kWave; j0 < n_cols; j0 += stride) {
+    const int64_t waves = (int64_t)gridDim.y * NW;
+    for (int64_t j0 = (int64_t)blockIdx.y * NW + w; j0 < n_cols; j0 += waves * kWave) {
         uint32_t gs_l = 0, pad_l = 0, ng_l = 0;
-        if (j0 + lane < n_cols) {
-            const size_t o = (size_t)t * (size_t)(n_cols + 1) + (size_t)(j0 + lane);
+        if (j0 + lane * waves < n_cols) {
+            const size_t o = (size_t)t * (size_t)(n_cols + 1) + (size_t)(j0 + lane * waves);
             const uint32_t g = goff[o];
             gs_l = g & kGoffMask;
             pad_l = g >> 30;
@@ -862,37 +925,65 @@ hipError_t build_prune_long(const int64_t *ptr, const int32_t *idx, const float 
     return hipGetLastError();
 }
 
+// Parts per tile: a CU holds one fill workgroup, so the fill takes as many rounds as its workgroups
+// (tiles, parts, term passes) fill the 256 CUs, each a part long plus setting up its cursors (0.003 of
+// a tile's time); the count that makes this least, of at least 256 documents of a full tile.
+// 80 tiles: 16 parts (10 parts, four rounds with the last nearly empty: 1.40 ms).
+int32_t build_parts(int64_t n_tiles, int64_t n_cols, int32_t tile_max)
+{
+    const int64_t wgs = std::max<int64_t>(1, n_tiles * ((n_cols + kFillTerms - 1) / kFillTerms));
+    const int32_t most = (int32_t)std::max<int64_t>(1, std::min<int64_t>(16, tile_max / 256));
+    int32_t best = 1;
+    double least = 1e300;
+    for (int32_t p = 1; p <= most; ++p) {
+        const double cost = (double)((wgs * p + 255) / 256) * (1.0 / p + 0.003);
+        if (cost < 0.98 * least) {
+            least = cost;
+            best = p;
+        }
+    }
+    return best;
+}
+
+size_t build_part_bytes(int64_t n_tiles, int32_t parts, int64_t n_cols)
+{
+    return (size_t)n_tiles * (size_t)parts * part_stride(n_cols) * 2;
+}
+
 hipError_t build_count_lists(const int64_t *ptr, const int32_t *idx, const float *val,
                              const uint8_t *keep, int64_t n_rows, int64_t n_cols,
-                             const int64_t *tile_doc, int64_t n_tiles, int32_t dtype,
-                             uint32_t *cnt, uint32_t *term_max_bits, unsigned long long *n_kept,
+                             const int64_t *tile_doc, int64_t n_tiles, int32_t parts, int32_t dtype,
+                             uint16_t *part_cnt, uint32_t *term_max_bits, unsigned long long *n_kept,
                              int32_t *err, hipStream_t s)
 {
     if (n_rows == 0 || n_tiles == 0) return hipSuccess;
+    if (n_tiles * parts > 0x7FFFFFFF) return hipErrorInvalidValue;
     const int32_t pass_terms = (int32_t)std::min<int64_t>(n_cols, kCountTerms);
     const int64_t passes = (n_cols + pass_terms - 1) / pass_terms;
     const size_t lds = (size_t)(pass_terms + 1) / 2 * 4;
     hipError_t e = set_lds(k_count_lists, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_count_lists, dim3((unsigned)n_tiles, (unsigned)std::min<int64_t>(passes, 65535)),
-                       dim3(kCountThreads), lds, s, ptr, idx, val, keep, n_cols, tile_doc, dtype,
-                       pass_terms, passes, cnt, term_max_bits, n_kept, err);
+    hipLaunchKernelGGL(k_count_lists, dim3((unsigned)(n_tiles * parts), (unsigned)std::min<int64_t>(passes, 65535)),
+                       dim3(kCountThreads), lds, s, ptr, idx, val, keep, n_cols, tile_doc, parts, dtype,
+                       pass_terms, passes, part_cnt, term_max_bits, n_kept, err);
     return hipGetLastError();
 }
 
-hipError_t build_list_offsets(const uint32_t *cnt, int64_t n_tiles, int64_t n_cols,
-                              uint32_t *goff, int64_t *tile_groups, int32_t *err, hipStream_t s)
+hipError_t build_list_offsets(uint16_t *part_cnt, int32_t parts, int64_t n_tiles, int64_t n_cols,
+                              uint32_t *cnt, uint32_t *goff, int64_t *tile_groups, int32_t *err,
+                              hipStream_t s)
 {
     if (n_tiles == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_list_offsets, dim3((unsigned)n_tiles), dim3(256), 0, s, cnt, n_cols,
-                       goff, tile_groups, err);
+    hipLaunchKernelGGL(k_list_offsets, dim3((unsigned)n_tiles), dim3(kOffsetThreads), 0, s, part_cnt,
+                       parts, n_cols, cnt, goff, tile_groups, err);
     return hipGetLastError();
 }
 
 hipError_t build_fill_lists(const int64_t *ptr, const int32_t *idx, const float *val,
                             const uint8_t *keep, const int64_t *tile_doc, const int64_t *tile_post,
-                            const uint32_t *goff, int64_t n_tiles, int64_t n_cols, int32_t dtype,
-                            uint16_t *post_doc, void *post_val, hipStream_t s)
+                            const uint32_t *goff, const uint16_t *part_cnt, int32_t parts,
+                            int64_t n_tiles, int64_t n_cols, int32_t dtype, uint16_t *post_doc,
+                            void *post_val, hipStream_t s)
 {
     if (n_tiles == 0) return hipSuccess;
     // at most kFillTerms list cursors per wave; each pass streams the tile once
@@ -901,9 +992,9 @@ hipError_t build_fill_lists(const int64_t *ptr, const int32_t *idx, const float 
     const size_t lds = (size_t)pass_terms * 4;
     hipError_t e = set_lds(k_fill_lists, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_fill_lists, dim3((unsigned)n_tiles, (unsigned)passes), dim3(kFillThreads), lds, s,
-                       ptr, idx, val, keep, tile_doc, tile_post, goff, n_cols, dtype, pass_terms,
-                       post_doc, post_val);
+    hipLaunchKernelGGL(k_fill_lists, dim3((unsigned)(n_tiles * parts), (unsigned)passes), dim3(kFillThreads), lds, s,
+                       ptr, idx, val, keep, tile_doc, tile_post, goff, part_cnt, parts, n_cols, dtype,
+                       pass_terms, post_doc, post_val);
     return hipGetLastError();
 }
 

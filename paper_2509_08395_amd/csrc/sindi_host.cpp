@@ -11,6 +11,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <map>
 #include <memory>
 #include <mutex>
 #include <new>
@@ -48,6 +49,104 @@ int host_threads()
     int n = env ? atoi(env) : 0;
     if (n <= 0) n = (int)std::thread::hardware_concurrency();
     return n < 1 ? 1 : (n > 64 ? 64 : n);
+}
+
+// ------------------------------------------------------------------ device memory
+namespace {
+constexpr size_t kPoolMin = size_t(1) << 20;  // smaller blocks go to the driver at once
+
+size_t size_class(size_t n)
+{
+    size_t step = size_t(2) << 20;
+    while (step * 32 <= n) step <<= 1;  // between 1/32 and 1/16 of n
+    return (n + step - 1) / step * step;
+}
+
+struct BlockPool {
+    std::mutex mu;
+    std::multimap<size_t, void *> kept;  // capacity -> block
+    size_t kept_bytes = 0, used_bytes = 0, most = 0;
+};
+
+// One per device; never destroyed (indexes may outlive the library's static objects).
+BlockPool &pool_of(int device)
+{
+    static std::mutex mu;
+    static std::map<int, BlockPool *> *pools = new std::map<int, BlockPool *>();
+    std::lock_guard<std::mutex> lock(mu);
+    BlockPool *&p = (*pools)[device];
+    if (!p) p = new BlockPool();
+    return *p;
+}
+
+// Gives kept blocks back, the largest first, until at most `bytes` are kept.
+void give_back(BlockPool &b, size_t bytes)
+{
+    while (b.kept_bytes > bytes && !b.kept.empty()) {
+        auto it = std::prev(b.kept.end());
+        (void)hipFree(it->second);
+        b.kept_bytes -= it->first;
+        b.kept.erase(it);
+    }
+}
+}  // namespace
+
+hipError_t device_alloc(void **p, size_t bytes, size_t *capacity, int *device)
+{
+    *p = nullptr;
+    hipError_t e = hipGetDevice(device);
+    if (e != hipSuccess) return e;
+    if (bytes < kPoolMin) {
+        *capacity = bytes;
+        return hipMalloc(p, bytes);
+    }
+    *capacity = size_class(bytes);
+    BlockPool &b = pool_of(*device);
+    std::lock_guard<std::mutex> lock(b.mu);
+    const auto it = b.kept.find(*capacity);
+    if (it != b.kept.end()) {
+        *p = it->second;
+        b.kept_bytes -= it->first;
+        b.kept.erase(it);
+    } else if ((e = hipMalloc(p, *capacity)) != hipSuccess) {
+        if (b.kept.empty() || e != hipErrorOutOfMemory) return e;
+        (void)hipGetLastError();
+        give_back(b, 0);
+        if ((e = hipMalloc(p, *capacity)) != hipSuccess) return e;
+    }
+    b.used_bytes += *capacity;
+    return hipSuccess;
+}
+
+void device_free(void *p, size_t capacity, int device)
+{
+    if (capacity < kPoolMin) {
+        (void)hipFree(p);
+        return;
+    }
+    BlockPool &b = pool_of(device);
+    int current = device;
+    const bool here = hipGetDevice(&current) == hipSuccess &&
+                      (current == device || hipSetDevice(device) == hipSuccess);
+    const bool idle = here && hipDeviceSynchronize() == hipSuccess;
+    {
+        std::lock_guard<std::mutex> lock(b.mu);
+        b.used_bytes -= capacity;
+        if (!b.most) {
+            size_t free_bytes = 0, total = 0;
+            if (!here || hipMemGetInfo(&free_bytes, &total) != hipSuccess) total = 0;
+            b.most = total / 16;
+        }
+        const size_t room = std::min(b.used_bytes, b.most);
+        if (idle && capacity <= room) {
+            b.kept.emplace(capacity, p);
+            b.kept_bytes += capacity;
+        } else {
+            (void)hipFree(p);
+        }
+        give_back(b, room);
+    }
+    if (here && current != device) (void)hipSetDevice(current);
 }
 
 // ------------------------------------------------------------------ profiling
@@ -292,6 +391,13 @@ void list_prune(const sindi_csr *c, int64_t lmax, std::vector<uint8_t> &keep)
     });
 }
 
+// A part of one device allocation.
+struct ScratchPiece {
+    size_t at;
+    unsigned char *base;
+    template <typename T> T *as() const { return reinterpret_cast<T *>(base + at); }
+};
+
 // The same index built on the device (sindi_build.hip): pruning, per-list
 // counts, group offsets and the ordered fill run as kernels; the host only
 // lays out the tiles, scans the per-tile totals and checks the flags.
@@ -318,11 +424,25 @@ sindi_status build_device(const sindi_csr *c, const sindi_build_params *p, hipSt
     const int64_t *ptr = ix->indptr.as<int64_t>();
     const int32_t *idx = ix->indices.as<int32_t>();
     const float *val = ix->values.as<float>();
-    DBuf err, keep, long_rows, n_long, cnt, kept, tgroups;
-    BUILD_ALLOC(err, 4, "flags");
+    // the build's scratch as one allocation (each one more costs some 0.15 ms to make and free)
+    const int32_t parts = build_parts(n_tiles, nc, ix->tile_max);
+    const size_t stride = (size_t)nc + 1;
+    size_t scratch = 0;
+    auto piece = [&](size_t bytes) {
+        ScratchPiece p{scratch, nullptr};
+        scratch += (bytes + 255) & ~(size_t)255;
+        return p;
+    };
+    ScratchPiece err = piece(4), n_long = piece(4), kept = piece(8), tgroups = piece((size_t)n_tiles * 8 + 8),
+          keep = piece((size_t)nnz + 4), long_rows = piece((size_t)nd * 4 + 4),
+          cnt = piece((size_t)n_tiles * stride * 4), part_cnt = piece(build_part_bytes(n_tiles, parts, nc));
+    DBuf scratch_buf;
+    BUILD_ALLOC(scratch_buf, scratch, "build scratch");
+    for (ScratchPiece *p : {&err, &n_long, &kept, &tgroups, &keep, &long_rows, &cnt, &part_cnt})
+        p->base = scratch_buf.as<unsigned char>();
     HIP_TRY(launch_fill_u32(err.as<uint32_t>(), 1, 0u, s));
     auto flags = [&](int32_t &out_err) -> sindi_status {
-        HIP_TRY(hipMemcpyAsync(&out_err, err.p, 4, hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipMemcpyAsync(&out_err, err.as<void>(), 4, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
         return SINDI_OK;
     };
@@ -337,44 +457,35 @@ sindi_status build_device(const sindi_csr *c, const sindi_build_params *p, hipSt
                         "id range, 4 order, 8 non-finite)", ferr);
     }
     // Alg. 3's pruning step on the device
-    BUILD_ALLOC(keep, (size_t)nnz + 4, "keep mask");
-    BUILD_ALLOC(long_rows, (size_t)nd * 4 + 4, "long-row list");
-    BUILD_ALLOC(n_long, 4, "counter");
     HIP_TRY(launch_fill_u32(n_long.as<uint32_t>(), 1, 0u, s));
     const int32_t mode = p->prune == SINDI_PRUNE_VNP ? SINDI_PRUNE_VNP : SINDI_PRUNE_MRP;
     HIP_TRY(build_prune_rows(ptr, idx, val, nd, mode, p->alpha, p->vn, keep.as<uint8_t>(),
                              long_rows.as<int32_t>(), n_long.as<uint32_t>(), err.as<int32_t>(), s));
     uint32_t h_long = 0;
-    HIP_TRY(hipMemcpyAsync(&h_long, n_long.p, 4, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(&h_long, n_long.as<void>(), 4, hipMemcpyDeviceToHost, s));
     if ((st = flags(ferr)) != SINDI_OK) return st;
     if (ferr & 128)
         return fail(SINDI_E_INVALID, "sindi_build: a row holds more than %d entries; build it on "
                     "the host (gpu_build = 0)", kLongRow);
     HIP_TRY(build_prune_long(ptr, idx, val, long_rows.as<int32_t>(), (int32_t)h_long, mode,
                              p->alpha, p->vn, keep.as<uint8_t>(), s));
-    long_rows.release();
     // Alg. 1: list sizes per (tile, term)
-    const size_t stride = (size_t)nc + 1;
     BUILD_ALLOC(ix->tile_doc, tile_doc.size() * 8, "tile_doc");
     HIP_TRY(hipMemcpyAsync(ix->tile_doc.p, tile_doc.data(), tile_doc.size() * 8, hipMemcpyHostToDevice, s));
-    BUILD_ALLOC(cnt, (size_t)n_tiles * stride * 4, "list counts");
     BUILD_ALLOC(ix->term_max, (size_t)nc * 4, "term maxima");
-    BUILD_ALLOC(kept, 8, "counter");
-    HIP_TRY(launch_fill_u32(cnt.as<uint32_t>(), (int64_t)n_tiles * (int64_t)stride, 0u, s));
     HIP_TRY(launch_fill_u32(ix->term_max.as<uint32_t>(), nc, 0u, s));
     HIP_TRY(launch_fill_u32(kept.as<uint32_t>(), 2, 0u, s));
     HIP_TRY(build_count_lists(ptr, idx, val, keep.as<uint8_t>(), nd, nc, ix->tile_doc.as<int64_t>(),
-                              n_tiles, p->value_dtype, cnt.as<uint32_t>(),
+                              n_tiles, parts, p->value_dtype, part_cnt.as<uint16_t>(),
                               ix->term_max.as<uint32_t>(), kept.as<unsigned long long>(),
                               err.as<int32_t>(), s));
     BUILD_ALLOC(ix->term_goff, (size_t)n_tiles * stride * 4, "term offsets");
-    BUILD_ALLOC(tgroups, (size_t)n_tiles * 8 + 8, "tile totals");
-    HIP_TRY(build_list_offsets(cnt.as<uint32_t>(), n_tiles, nc, ix->term_goff.as<uint32_t>(),
-                               tgroups.as<int64_t>(), err.as<int32_t>(), s));
+    HIP_TRY(build_list_offsets(part_cnt.as<uint16_t>(), parts, n_tiles, nc, cnt.as<uint32_t>(),
+                               ix->term_goff.as<uint32_t>(), tgroups.as<int64_t>(), err.as<int32_t>(), s));
     std::vector<int64_t> tile_post((size_t)n_tiles + 1, 0);
     unsigned long long h_kept = 0;
-    HIP_TRY(hipMemcpyAsync(tile_post.data() + 1, tgroups.p, (size_t)n_tiles * 8, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(&h_kept, kept.p, 8, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(tile_post.data() + 1, tgroups.as<void>(), (size_t)n_tiles * 8, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(&h_kept, kept.as<void>(), 8, hipMemcpyDeviceToHost, s));
     if ((st = flags(ferr)) != SINDI_OK) return st;
     if (ferr & 32) return fail(SINDI_E_RANGE, "sindi_build: a kept value overflows the storage type");
     if (ferr & 16)
@@ -394,8 +505,9 @@ sindi_status build_device(const sindi_csr *c, const sindi_build_params *p, hipSt
     HIP_TRY(launch_fill_u32(ix->post_val.as<uint32_t>(), (int64_t)(ix->post_val.bytes / 4), 0u, s));
     HIP_TRY(launch_fill_u32(ix->post_doc.as<uint32_t>(), (int64_t)(ix->post_doc.bytes / 4), 0u, s));
     HIP_TRY(build_fill_lists(ptr, idx, val, keep.as<uint8_t>(), ix->tile_doc.as<int64_t>(),
-                             ix->tile_post.as<int64_t>(), ix->term_goff.as<uint32_t>(), n_tiles, nc,
-                             p->value_dtype, ix->post_doc.as<uint16_t>(), ix->post_val.p, s));
+                             ix->tile_post.as<int64_t>(), ix->term_goff.as<uint32_t>(),
+                             part_cnt.as<uint16_t>(), parts, n_tiles, nc, p->value_dtype,
+                             ix->post_doc.as<uint16_t>(), ix->post_val.p, s));
     HIP_TRY(build_fill_pads(ix->term_goff.as<uint32_t>(), cnt.as<uint32_t>(), ix->tile_post.as<int64_t>(),
                             n_tiles, nc, ix->post_doc.as<uint16_t>(), s));
     HIP_TRY(build_deal_chunks(ix->term_goff.as<uint32_t>(), ix->tile_post.as<int64_t>(), n_tiles, nc,

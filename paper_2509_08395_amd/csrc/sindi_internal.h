@@ -174,17 +174,24 @@ hipError_t build_prune_rows(const int64_t *ptr, const int32_t *idx, const float 
 hipError_t build_prune_long(const int64_t *ptr, const int32_t *idx, const float *val,
                             const int32_t *rows, int32_t n_rows, int32_t mode, double alpha,
                             int32_t vn, uint8_t *keep, hipStream_t s);
+// Parts that separate workgroups count and fill of every tile; part_cnt (build_part_bytes): the
+// parts' counts per term, then (after build_list_offsets, which also writes the
+// lists' lengths cnt) the postings of the parts before.
+int32_t build_parts(int64_t n_tiles, int64_t n_cols, int32_t tile_max);
+size_t build_part_bytes(int64_t n_tiles, int32_t parts, int64_t n_cols);
 hipError_t build_count_lists(const int64_t *ptr, const int32_t *idx, const float *val,
                              const uint8_t *keep, int64_t n_rows, int64_t n_cols,
-                             const int64_t *tile_doc, int64_t n_tiles, int32_t dtype,
-                             uint32_t *cnt, uint32_t *term_max_bits, unsigned long long *n_kept,
+                             const int64_t *tile_doc, int64_t n_tiles, int32_t parts, int32_t dtype,
+                             uint16_t *part_cnt, uint32_t *term_max_bits, unsigned long long *n_kept,
                              int32_t *err, hipStream_t s);
-hipError_t build_list_offsets(const uint32_t *cnt, int64_t n_tiles, int64_t n_cols,
-                              uint32_t *goff, int64_t *tile_groups, int32_t *err, hipStream_t s);
+hipError_t build_list_offsets(uint16_t *part_cnt, int32_t parts, int64_t n_tiles, int64_t n_cols,
+                              uint32_t *cnt, uint32_t *goff, int64_t *tile_groups, int32_t *err,
+                              hipStream_t s);
 hipError_t build_fill_lists(const int64_t *ptr, const int32_t *idx, const float *val,
                             const uint8_t *keep, const int64_t *tile_doc, const int64_t *tile_post,
-                            const uint32_t *goff, int64_t n_tiles, int64_t n_cols, int32_t dtype,
-                            uint16_t *post_doc, void *post_val, hipStream_t s);
+                            const uint32_t *goff, const uint16_t *part_cnt, int32_t parts,
+                            int64_t n_tiles, int64_t n_cols, int32_t dtype, uint16_t *post_doc,
+                            void *post_val, hipStream_t s);
 hipError_t build_fill_pads(const uint32_t *goff, const uint32_t *cnt, const int64_t *tile_post,
                            int64_t n_tiles, int64_t n_cols, uint16_t *post_doc, hipStream_t s);
 // Reorders every list chunk of kChunk groups (ascending by document on entry: run once, after

@@ -214,3 +214,44 @@ def test_items_of_many_queries(sindi, run, schedule):
                                 schedule=schedule)
         assert np.array_equal(_np(got[0]), np.tile(ref[0], (reps, 1)))
         assert np.array_equal(_np(got[1]), np.tile(ref[1], (reps, 1)))
+
+
+# ------------------------------------------------------------------ device build
+@pytest.mark.parametrize("nd, vocab, tile", [(255, 9, 300), (513, 4_001, 600), (5_000, 33_000, 5_000),
+                                             (9_001, 70_001, 700), (40_000, 300, 1_000)])
+def test_device_build_parts(sindi, nd, vocab, tile):
+    """Tiles cut into one to sixteen parts, one to three fill passes, vocabularies off every vector
+    and round width: the same arrays as the host build."""
+    rng = np.random.default_rng(11)
+    corpus = synth.random_csr(rng, nd, vocab, min(40, vocab), signed=True)
+    a, b = (sindi.Index(corpus, alpha=0.7, window=max(tile, nd // 2), tile=tile, value_dtype="bf16",
+                        gpu_build=g).export(raw=True) for g in (False, True))
+    for name in a:
+        assert np.array_equal(a[name], b[name]), name
+
+
+def test_rebuilt_indexes_reuse_and_return_memory(sindi):
+    """Indexes built beside the one they replace take its memory over (old contents must not
+    show), and the last one to go gives the library's memory back to the driver."""
+    def corpus(nd, seed):
+        return synth.generate(nd, 3_000, nnz=("poisson", 60.0), seed=seed)
+    q = synth.generate(20, 3_000, nnz=("poisson", 15.0), seed=3, stream=1)
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    want = []
+    for seed in range(3):
+        idx = sindi.Index(corpus(30_000 - 500 * seed, seed), alpha=0.5, window=10_000, value_dtype="f16")
+        want.append(tuple(_np(t) for t in idx.search(q, 10, gamma=60)))
+        idx.close()
+    live = None
+    for k in range(9):
+        new = sindi.Index(corpus(30_000 - 500 * (k % 3), k % 3), alpha=0.5, window=10_000,
+                          value_dtype="f16", gpu_build=k % 2 == 0)
+        got = tuple(_np(t) for t in new.search(q, 10, gamma=60))
+        assert np.array_equal(got[0], want[k % 3][0]) and np.array_equal(got[1], want[k % 3][1])
+        if live:
+            live.close()
+        live = new
+    live.close()
+    torch.cuda.synchronize()
+    assert free0 - torch.cuda.mem_get_info()[0] < 64 << 20  # torch's own small results
