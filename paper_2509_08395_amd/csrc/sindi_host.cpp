@@ -232,9 +232,9 @@ uint16_t to_bf16(float x)
 // Largest tile of a window split: three 512-thread scoring workgroups (one
 // query each) still share a CU's 160 KB of LDS, and fewer, larger tiles cut
 // the per-tile work (list layout, barriers, read-out) per posting.  (LDS is
-// allocated in 512-byte units; the kernel's static LDS is under 3,840 bytes.)
+// allocated in 512-byte units; the kernel's static LDS is under 4,096 bytes.)
 constexpr int32_t kDefaultTile = 12500;
-static_assert(3 * ((accumulate_lds_bytes(1, kDefaultTile) + 3840 + 511) / 512 * 512) <=
+static_assert(3 * ((accumulate_lds_bytes(1, kDefaultTile) + 4096 + 511) / 512 * 512) <=
                   160 * 1024,
               "default tile too large");
 constexpr int32_t kDefaultBatch = 1;

@@ -40,7 +40,7 @@ namespace {
 constexpr int kWave = 64;
 constexpr int kRerankPerWave = 4;  // pool entries one rerank wave scores at a time
 constexpr int kRerankGroups = 4;   // most such groups per wave (one query table per workgroup)
-constexpr uint32_t kCandBuf = 384;  // candidates a scoring workgroup holds in LDS
+constexpr uint32_t kCandBuf = 256;  // candidates a scoring workgroup holds in LDS
 constexpr int kRankSort = 256;     // most keys put in order by counting the larger ones
 constexpr int kTopkRegs = 8;       // pool keys per thread of a selecting k_topk
 constexpr int64_t kRerankFill = 2048;  // rerank workgroups that fill the chip
@@ -1155,8 +1155,7 @@ __device__ __forceinline__ acc_args_t acc_args()
 // apart within the run, read 292 GB (64%) and took 50.6 ms; 1,000 queries over 1M documents 0.90
 // against 1.11 ms.
 //
-// Every wave lays out a query's chunks itself: the query's terms
-// are taken 64 at a time (a segment, one list per lane), and a wave-wide
+// The query's terms are taken 64 at a time (a segment, one list per lane), and a wave-wide
 // prefix sum over the lists' chunk counts numbers the segment's chunks.  The
 // waves then take batches of KU consecutive chunks: wave w's first batch of a
 // segment is fixed (chunks w KU to w KU + KU - 1, so its loads leave at once),
@@ -1164,10 +1163,8 @@ __device__ __forceinline__ acc_args_t acc_args()
 // wave's first lane, taken while the current batch's loads are in flight), so
 // they finish the query together however unevenly the lists' lengths and the
 // adds' bank conflicts fall; the counters are reset between the query's two
-// barriers.  The layout needs no LDS table:
-// a query costs the two barriers around its read-out.  The first segment's
-// list bounds are loaded one query ahead, its terms and weights two ahead (a
-// bound's address needs the term); further segments are reloaded (cache hits).
+// barriers.  One wave lays out a query's first segment for all, a query ahead; of a longer query
+// every wave lays out the further segments itself.
 //
 // The score row must be all zero on entry unless clear_row (the read-out of every query clears
 // what its adds touched, so it is all zero again on return).  last() is called once, as the
@@ -1254,13 +1251,45 @@ __device__ __forceinline__ void accumulate1_item(int64_t ti, int32_t s0, int32_t
             w = (cw + qa)[lane];
         }
     };
-    int32_t term1, term2;
-    float w1, w2;
-    uint32_t lo, hi;  // lanes past the query's terms read term 0's bounds and ignore them
-    terms(0, term1, w1);
-    terms(1, term2, w2);
-    lo = toff[term1];
-    hi = toff[term1 + 1];
+    // The lists of a segment, one per lane, as numbered chunks: list l holds chunks [incl - nch,
+    // incl) of the segment, its chunk 0 would start at group basel, it ends at group endl.
+    struct Lists {
+        uint32_t cpn, basel, endl;
+        float w;
+    };
+    auto plan = [&](uint32_t lo, uint32_t hi, bool live, float w) {
+        const uint32_t gs = lo & kGoffMask, ng = live ? (hi & kGoffMask) - gs : 0u;
+        const uint32_t nch = (ng + kChunk - 1) / kChunk;
+        Lists r;
+        r.cpn = wave_incl_scan(nch);
+        r.basel = gs - (r.cpn - nch) * (uint32_t)kChunk;
+        r.endl = gs + ng;
+        r.w = w;
+        return r;
+    };
+    // One wave, the planner, lays out the first segment of the next query while this one is
+    // scored and leaves it in LDS; it also keeps the loads ahead: the next query's list bounds, the
+    // terms and weights two further (a bound's address needs the term).  Eight waves each doing
+    // this spent a sixth of the pass's vector instructions on it: 48.0 ms for 7,000 queries over
+    // 8.8M documents, 46.4 from one planner; 19.0 and 17.8 ms with alpha 0.2, beta 0.8, where a
+    // tile has fewer chunks.  The last wave plans: short queries leave it without chunks.
+    __shared__ Lists s_lists[kWave];
+    const bool planner = wave == NW - 1;
+    int32_t term2 = 0;
+    float w1 = 0.0f, w2 = 0.0f;
+    uint32_t lo = 0, hi = 0;  // lanes past the query's terms read term 0's bounds and ignore them
+    auto ahead = [&](int32_t i) {  // bounds of query i, whose terms are loaded, and terms of i + 1
+        lo = toff[term2];
+        hi = toff[term2 + 1];
+        w1 = w2;
+        terms(i + 1, term2, w2);
+    };
+    if (planner) {
+        terms(0, term2, w2);
+        ahead(0);
+        s_lists[lane] = plan(lo, hi, lane < (__builtin_amdgcn_readlane(r_n, 0) & 0xFFFF), w1);
+        ahead(1);
+    }
     __syncthreads();
 
     for (int32_t i = 0; i < m; ++i) {
@@ -1268,42 +1297,27 @@ __device__ __forceinline__ void accumulate1_item(int64_t ti, int32_t s0, int32_t
         const int32_t ni = __builtin_amdgcn_readlane(r_n, i);
         const int32_t n = ni & 0xFFFF, nseg = (n + kWave - 1) / kWave;
         const bool imp = (ni & (1 << 16)) != 0;
-        const int64_t qa = readlane64(r_qa, i);
-        const uint32_t gs0 = lo & kGoffMask;
-        const uint32_t ng0 = lane < n ? (hi & kGoffMask) - gs0 : 0u;
-        const float w0 = w1;
         if (i == m - 1) last();
-        lo = toff[term2];
-        hi = toff[term2 + 1];
-        w1 = w2;
-        terms(i + 2, term2, w2);
-        // segment s >= 1: lane l holds list 64 s + l
-        auto segment = [&](int32_t s, uint32_t &gs, uint32_t &ng, float &w) {
-            gs = 0;
-            ng = 0;
-            w = 0.0f;
-            const int32_t li = s * kWave + lane;
-            if (li < n) {
-                const int32_t term = (ct + qa)[li];
-                w = (cw + qa)[li];
-                const uint32_t lo = toff[term], hi = toff[term + 1];
-                gs = lo & kGoffMask;
-                ng = (hi & kGoffMask) - gs;
-            }
-        };
         for (int32_t s = 0; s < nseg; ++s) {
-            uint32_t gs = gs0, ng = ng0;
-            float wl = w0;
-            if (s > 0) segment(s, gs, ng, wl);
-            // chunk numbers: list l of the segment holds its chunks [incl - nch, incl)
-            const uint32_t nch = (ng + kChunk - 1) / kChunk;
-            const uint32_t incl = wave_incl_scan(nch);
-            const uint32_t st = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+            Lists ls;
+            if (s == 0) {
+                ls = s_lists[lane];
+            } else {  // lane l holds list 64 s + l
+                const int64_t qa = readlane64(r_qa, i);
+                const int32_t li = s * kWave + lane;
+                int32_t term = 0;
+                float w = 0.0f;
+                if (li < n) {
+                    term = (ct + qa)[li];
+                    w = (cw + qa)[li];
+                }
+                ls = plan(toff[term], toff[term + 1], li < n, w);
+            }
+            const uint32_t st = (uint32_t)__builtin_amdgcn_readlane((int)ls.cpn, kWave - 1);
             if (st == 0) continue;
             // list of chunk ci: the lanes whose lists end at or before ci, counted
-            const uint32_t cpn = incl;
-            const uint32_t basel = gs - (incl - nch) * (uint32_t)kChunk;
-            const uint32_t endl = gs + ng;
+            const uint32_t cpn = ls.cpn, basel = ls.basel, endl = ls.endl;
+            const float wl = ls.w;
             auto take = [&]() {  // the first chunk of the wave's next batch
                 uint32_t g = 0;
                 if (lane == 0) g = atomicAdd(&s_next[s], (uint32_t)KU);
@@ -1372,7 +1386,14 @@ __device__ __forceinline__ void accumulate1_item(int64_t ti, int32_t s0, int32_t
                 cs = next;
             }
         }
+        Lists next;
+        const bool plans = planner && i + 1 < m;
+        if (plans) next = plan(lo, hi, lane < (__builtin_amdgcn_readlane(r_n, i + 1) & 0xFFFF), w1);
         __syncthreads();
+        if (plans) {
+            s_lists[lane] = next;
+            ahead(i + 2);
+        }
         if (tid < nseg) s_next[tid] = kFirstTaken;  // every wave has taken its last batch
 
         // ---- read the row: sample maxima or emit every score at or above the
