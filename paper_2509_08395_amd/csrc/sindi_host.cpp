@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -1133,13 +1134,21 @@ sindi_status search_impl(sindi_index *ix, const sindi_csr *qc, int32_t k,
                       grow_workspace, &ws);
 }
 
-// Wait for the report of a launch_report on s (report[3] was 0 before it).
+// Wait for the report of a launch_report on s (report[3] was 0 before it).  The stream is asked
+// only every half millisecond (a query of it costs several microseconds), so that a stream that
+// failed, which never writes the report, ends the wait.
 sindi_status wait_report(uint32_t *report, hipStream_t s)
 {
+    using Clock = std::chrono::steady_clock;
     for (;;) {
-        for (int i = 0; i < 2000; ++i)
-            if (__atomic_load_n(report + 3, __ATOMIC_ACQUIRE)) return SINDI_OK;
-        const hipError_t e = hipStreamQuery(s);  // a stream that failed never writes it
+        const auto until = Clock::now() + std::chrono::microseconds(500);
+        do {
+            for (int i = 0; i < 64; ++i) {
+                if (__atomic_load_n(report + 3, __ATOMIC_ACQUIRE)) return SINDI_OK;
+                __builtin_ia32_pause();
+            }
+        } while (Clock::now() < until);
+        const hipError_t e = hipStreamQuery(s);
         if (e == hipErrorNotReady) continue;
         HIP_TRY(e);
         if (!__atomic_load_n(report + 3, __ATOMIC_ACQUIRE))
