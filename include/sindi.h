@@ -107,13 +107,13 @@ typedef struct {
     int32_t tile_run;        /* work per item of a scoring launch.  One query per workgroup:
                                 queries that an item takes one after another over one tile, at
                                 most 64; batch >= 2: consecutive tiles that a workgroup sweeps.
-                                0 -> by the bytes of a tile's lists and the number of queries;
-                                halved while a launch would hold fewer than 4096 items.  Results
+                                0 -> by the numbers of tiles and queries and the bytes of a tile's
+                                lists; halved while a launch would hold fewer than 4096 items.  Results
                                 are the same bit for bit.                                      */
     int32_t schedule;        /* scoring launches with one query per workgroup: 1 one
                                 workgroup per item; 2 one persistent launch of
                                 the workgroups the device holds at once, each taking
-                                items from a device queue until it is empty;
+                                items from device queues until they are empty;
                                 0 -> 2.  Results are the same bit for bit.                  */
 } sindi_search_params;
 

@@ -757,20 +757,18 @@ sindi_status build_impl(const sindi_csr *c, const sindi_build_params *p, hipStre
 // ------------------------------------------------------------------ search
 // Work per item when the call leaves it open.
 //
-// One query per workgroup: queries that an item takes one after another over its tile.  The
-// resident workgroups hold kResident * run / nq tiles at once, and a tile's lists are shared
-// through L2 (4 MB in each XCD) only while those tiles about fit it; a longer run hides an item's
-// set-up.  So the run is the longest power of two that keeps the lists in flight at 10 MB, at
-// least 2 (4 where the whole index stays in the 256 MB memory-side cache, so a miss costs
-// less; 1 where one tile's lists alone pass 4 MB), at most 32, and above those only while the
-// launch holds 16,384 items.  Scoring pass in us, runs 1, 2, 4, 8, 16, 32:
-//   8.8M documents, 1.6 MB a tile, 35 terms:  64 queries 923 762 809 903 903 903; 256: 2582 2063
-//     2051 2379 2889 3252; 1,000: 8907 7609 7355 7268 7560 9415; 7,000: - - 49973 48762 48357 48280;
-//     5 to 200 terms, 256 queries: 2680 2304 2587 3274 3639 3844
-//   1M documents in the cache, 2.3 MB a tile:  400 queries 602 439 423 - - -; 1,000: 1194 917 904
-//     933 1093 1094
-//   1M documents, 16 MB a tile:  256 queries 1536 1904 2173 2177 2175 2181; 1,000: 4004 4625 6177 7678
-//     8611 8598
+// One query per workgroup: queries that an item takes one after another over its tile.  A longer
+// run hides an item's set-up and keeps more of the workgroups of an XCD on one tile, whose lists its
+// L2 (4 MB) then holds; but the launch ends with items that few workgroups share.  So the run is the
+// longest power of two, from 64 down to 2, that leaves 6,144 items, or 16,384 where one tile's lists
+// alone pass 4 MB and do not stay in L2.  (Calls of fewer than 4,096 items get shorter ones.)
+// Scoring pass in us, runs 1, 2, 4, 8, 16, 32:
+//   8.8M documents, 704 tiles of 1.6 MB, 35 terms:  16 queries 219 199 199 - - -; 64: 720 622 577 - - -;
+//     256: 2582 2238 2022 1933 1917 2019; 1,000: 9237 8107 7363 7012 6867 6859; 7,000: - 54469 49980
+//     47610 46511 -, run 64 45955; 5 to 200 terms, 256 queries: 4147 3814 3659 3639 3770 4981
+//   1M documents, 80 tiles of 2.3 MB:  400 queries 462 400 370 - - -; 1,000: 1077 932 852 822 847 -
+//   1M documents, 80 tiles of 16 MB:  256 queries 1034 1050 1181 - - -; 1,000: 3694 3620 3678 3869
+//     4471 -
 //
 // Merged batches (2 to 8 queries per workgroup): consecutive tiles swept by a workgroup, by the
 // index's kept fraction of the corpus entries times the mean query length.
@@ -787,15 +785,11 @@ void set_item_run(Plan &pl, const sindi_index *ix, const sindi_search_params &p,
         pl.item_run = x > 12.0 ? 8 : (x > 5.0 ? 12 : 32);
         return;
     }
-    constexpr double kResident = 768.0;  // three workgroups on each of 256 CUs
     const int64_t tiles = std::max<int64_t>(ix->n_tiles, 1);
     const double lists = (double)ix->n_slots * (ix->dtype == SINDI_F32 ? 6.0 : 4.0);
-    const double per_tile = lists / (double)tiles;
-    const int32_t least = per_tile > 4e6 ? 1 : (lists <= 256e6 ? 4 : 2);
-    int32_t run = 32;
-    while (run > least && (kResident * run * per_tile > 10e6 * (double)nq ||
-                           tiles * ((nq + run - 1) / run) < 16384))
-        run >>= 1;
+    const int64_t items = lists > 4e6 * (double)tiles ? 16384 : 6144;
+    int32_t run = 64;
+    while (run > 2 && tiles * ((nq + run - 1) / run) < items) run >>= 1;
     pl.item_run = run;
 }
 
@@ -903,7 +897,7 @@ PassShape pass_shape(const sindi_index *ix, const Plan &pl, PassKind kind)
 size_t pass_bytes(const PassShape &sh, const Plan &pl, int64_t g)
 {
     const size_t n = (size_t)g;
-    return align256(16 + n * 4) + 2 * align256(n * 4) + align256(n * (size_t)sh.n_max * 4) +
+    return align256(kQueueBytes + n * 4) + 2 * align256(n * 4) + align256(n * (size_t)sh.n_max * 4) +
            align256(n * (size_t)sh.cap * 8) + (pl.rerank ? align256(n * (size_t)pl.need * 8) : 0);
 }
 
@@ -926,7 +920,7 @@ sindi_status enqueue_prep(const sindi_index *ix, const Scratch &sc, const Plan &
     DevCoarse dc{sc.ct, sc.cw, sc.cn, sc.qinv};
     HIP_TRY(timed(kProfPrep, s, [&] {
         return launch_query_prep(dq, ix->n_cols, pl.beta, dc, ix->term_max.as<float>(), sc.sabs,
-                                 sc.err, reinterpret_cast<uint32_t *>(sc.arena), g > 0 ? 4 + g : 0, s);
+                                 sc.err, reinterpret_cast<uint32_t *>(sc.arena), g > 0 ? (int64_t)(kQueueBytes / 4) + g : 0, s);
     }));
     return SINDI_OK;
 }
@@ -959,8 +953,8 @@ sindi_status enqueue_passes(const sindi_index *ix, const Scratch &sc, const Plan
     // the work-queue counters of the persistent scoring launches (sample, score), then the
     // per-slot candidate counts: one fill clears both (for the sampled pass's first group the
     // preparation has cleared them)
-    unsigned long long *queue = reinterpret_cast<unsigned long long *>(take(16 + (size_t)g * 4));
-    uint32_t *count = reinterpret_cast<uint32_t *>(queue + 2);
+    unsigned long long *queue = reinterpret_cast<unsigned long long *>(take(kQueueBytes + (size_t)g * 4));
+    uint32_t *count = reinterpret_cast<uint32_t *>(queue + 2 * kQueues * kQueueStep);
     float *theta = reinterpret_cast<float *>(take((size_t)g * 4));
     int32_t *sum_min = reinterpret_cast<int32_t *>(take((size_t)g * 4));
     float *maxima = reinterpret_cast<float *>(take((size_t)g * sh.n_max * 4));
@@ -976,7 +970,8 @@ sindi_status enqueue_passes(const sindi_index *ix, const Scratch &sc, const Plan
         const int32_t ns = (int32_t)std::min<int64_t>(g, n - g0);
         const DevSlots slots{rows ? rows + g0 : nullptr, (int32_t)g0, ns};
         if (rows || g0 > 0)
-            HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t *>(queue), 4 + (int64_t)ns, 0u, s));
+            HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t *>(queue), (int64_t)(kQueueBytes / 4) + ns, 0u,
+                                    s));
         if (!sh.keep_all) {
             HIP_TRY(timed(kProfSample, s, [&] {
                 return launch_accumulate(dix, dq, dc, batch, true, slots, sh.n_sample, maxima,
@@ -990,7 +985,7 @@ sindi_status enqueue_passes(const sindi_index *ix, const Scratch &sc, const Plan
         HIP_TRY(timed(kProfScore, s, [&] {
             return launch_accumulate(dix, dq, dc, batch, false, slots, 0, nullptr, th, sum_min, count,
                                      cand, sh.cap, pl.item_run, pl.max_qnnz,
-                                     pl.queue ? queue + 1 : nullptr, s);
+                                     pl.queue ? queue + kQueues * kQueueStep : nullptr, s);
         }));
         // without a threshold no sum is left implicit
         HIP_TRY(timed(kProfFinal, s, [&] {

@@ -56,6 +56,9 @@ struct DevCoarse {
 };
 
 constexpr int kAccThreads = 512;       // accumulate kernel workgroup
+constexpr int kQueues = 8;             // work queues of a scoring launch: one per XCD
+constexpr int kQueueStep = 16;         // 8-byte words from one queue's counter to the next: 128-byte lines
+constexpr size_t kQueueBytes = 2 * kQueues * kQueueStep * sizeof(unsigned long long);  // sample, score
 constexpr int kFinThreads = 256;       // rerank, top-k and pair-score kernels
 constexpr int kGammaMax = 4096;        // largest reorder pool
 constexpr int kQueryHash = 8192;       // rerank hash slots (query nnz <= kQueryHash / 2)

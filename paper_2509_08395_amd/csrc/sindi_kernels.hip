@@ -1131,10 +1131,13 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))
     }
 }
 
-// The items of a launch: tile-major, `run` slots each.
+// The items of a launch: tile-major, `run` slots each.  Queue x of a queue-fed launch holds those of
+// tiles x, x + queues, ...
 struct AccItems {
     int64_t n;           // items in all
     int32_t run, groups; // slots per item, items per tile
+    uint32_t tiles;
+    int32_t queues;
 };
 // The arguments of a one-query launch.  They are read from the kernel-argument segment where they
 // are used (acc_args), through the scalar cache: held in registers across the items they took some
@@ -1164,12 +1167,11 @@ __device__ __forceinline__ acc_args_t acc_args()
 
 // The single-query form of k_accumulate (same scores, same read-out).  One work item: the query
 // slots [s0, s1), at most 64 of them, one after another over one tile.  The tile's data are then
-// fixed for the item, and the workgroups resident together hold the items of one or two tiles,
-// whose lists stay in each XCD's L2 (1.4 MB a tile at 8.8M documents and alpha 0.5) while every
-// query of the call passes over them: 7,000 queries at 8.8M documents read 13.5 GB beyond L2 (98% of
-// the list reads hit) and take 48.3 ms, where items of one query over a run of 12 tiles, drifting
-// apart within the run, read 292 GB (64%) and took 50.6 ms; 1,000 queries over 1M documents 0.90
-// against 1.11 ms.
+// fixed for the item, and the workgroups resident together hold the items of few tiles, whose lists
+// stay in L2 (1.4 MB a tile at 8.8M documents and alpha 0.5) while every query of the call passes over
+// them: 7,000 queries at 8.8M documents read 13.5 GB beyond L2 and take 48.3 ms, where items of one
+// query over a run of 12 tiles, drifting apart within the run, read 292 GB and took 50.6 ms; 1,000
+// queries over 1M documents 0.90 against 1.11 ms.  (46.0 and 0.82 ms with what is described below.)
 //
 // The query's terms are taken 64 at a time (a segment, one list per lane), and a wave-wide
 // prefix sum over the lists' chunk counts numbers the segment's chunks.  The
@@ -1553,35 +1555,74 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))
     accumulate1_item<VT, SAMPLE>(ti, s0, min(s0 + g->items.run, g->slots.n), true, [] {});
 }
 
-// The same work as one persistent launch fed by a device work queue: as many workgroups as
+// The same work as one persistent launch fed by device work queues: as many workgroups as
 // the device holds at once, each starting with the item of its own index and taking the next
-// from a counter until the items are used up (the counter is read as an item's last query
-// starts, so the wait for it is hidden).  Items run in the grid's order, so the workgroups
-// resident together still score the same tiles, and a caller that orders its
-// slots by decreasing work starts the long queries of each tile first.  Every workgroup leaves
-// once the counter passes the last item; *head must be 0 at launch.
+// from its queue's counter until the items are used up (the counter is read as an item's last
+// query starts, so the wait for it is hidden), then from the other queues'.  Items run in the
+// grid's order, so the workgroups of a queue score the same tile, and a caller that orders its
+// slots by decreasing work starts the long queries of each tile first.  Workgroups go to the
+// eight XCDs in turn, so with eight queues a tile's lists are read by one XCD and stay in its L2;
+// with one queue every L2 held the lists of the one to three tiles in work.  256 queries over 1M
+// unpruned documents (16 MB a tile), scoring pass 1.54 -> 1.05 ms; 1,000 over 1M documents of 250K
+// terms 0.50 -> 0.48, the sampling pass 0.107 -> 0.077.  Fewer than four items a workgroup stay in
+// one queue (37 queries, 24 tiles: 30 us, 43 from eight): all workgroups come back at once there.
+// A workgroup leaves once it has found every queue's counter past its last item; the counters
+// (kQueueStep words apart) must be 0 at launch.
 template <int VT, bool SAMPLE>
 __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_accumulate1_queue(AccArgs)
 {
     __shared__ int64_t s_item;
+    uint32_t x = blockIdx.x % (uint32_t)acc_args()->items.queues;  // the queue, and the item's place in it
+    int64_t j = blockIdx.x / (uint32_t)acc_args()->items.queues;
+    // The first wave: the next item as j * kQueues + x, from queue x on; -1: none is left.  Past the
+    // end of its own queue it looks at all counters at once before it takes from another: at the
+    // end of the launch every workgroup comes by, and atomics on one word take 12 ns each.
+    auto take = [&]() -> int64_t {
+        const acc_args_t h = acc_args();
+        const uint32_t nq = (uint32_t)h->items.queues, y = threadIdx.x & (kWave - 1);
+        const int64_t begin = (gridDim.x - y + nq - 1) / nq;  // lane y < nq: queue y
+        const int64_t left = (int64_t)((h->items.tiles - y + nq - 1) / nq) * h->items.groups - begin;
+        uint32_t from = x;
+        for (;;) {
+            int64_t i = 0;
+            if (y == from) i = (int64_t)atomicAdd(h->head + y * kQueueStep, 1ull);
+            if (__ballot(y == from && i < left)) {
+                const uint64_t it = (uint64_t)((begin + i) * kQueues + y);
+                return readlane64((int64_t)it, (int)from);
+            }
+            if (nq == 1) return -1;
+            const uint64_t open = __ballot(
+                y < nq && (int64_t)__hip_atomic_load(h->head + (y < nq ? y : 0) * kQueueStep, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT) < left);
+            if (open == 0) return -1;
+            const uint64_t on = open >> from << from;  // the next open one from there, in turn
+            from = (uint32_t)__builtin_ctzll(on ? on : open);
+        }
+    };
     bool first = true;
-    for (int64_t it = blockIdx.x;;) {
+    for (;;) {
         const acc_args_t g = acc_args();
-        if (it >= g->items.n) break;
-        const int64_t ti = it / g->items.groups;
-        const int32_t s0 = (int32_t)(it - ti * g->items.groups) * g->items.run;
-        int64_t next = 0;
-        accumulate1_item<VT, SAMPLE>(ti, s0, min(s0 + g->items.run, g->slots.n), first, [&] {
-            const acc_args_t h = acc_args();
-            if (threadIdx.x == 0 && h->items.n > gridDim.x)
-                next = (int64_t)gridDim.x + (int64_t)atomicAdd(h->head, 1ull);
-        });
-        if (acc_args()->items.n <= gridDim.x) break;
+        const int64_t row = j / g->items.groups;
+        const int64_t ti = row * g->items.queues + x;
+        const bool one = g->items.n <= gridDim.x;  // an item each at most (the host sets one queue)
+        int64_t next = -1;
+        if (ti < (int64_t)g->items.tiles) {
+            const int32_t s0 = (int32_t)(j - row * g->items.groups) * g->items.run;
+            accumulate1_item<VT, SAMPLE>(ti, s0, min(s0 + g->items.run, g->slots.n), first, [&] {
+                if (threadIdx.x < kWave && !one) next = take();
+            });
+            first = false;
+        } else if (threadIdx.x < kWave && !one) {  // more workgroups than items in the queue
+            next = take();
+        }
+        if (one) break;
         // (the item's own barriers lie between this write and the last read)
         if (threadIdx.x == 0) s_item = next;
         __syncthreads();
-        it = uni64(s_item);
-        first = false;
+        const int64_t it = uni64(s_item);
+        if (it < 0) break;
+        x = (uint32_t)it % kQueues;
+        j = it / kQueues;
     }
 }
 
@@ -2340,6 +2381,8 @@ hipError_t run_accumulate(const DevIndex &ix, const DevQueries &q, const DevCoar
     if constexpr (B == 1) {
         AccArgs args{ix, q, c, slots, n_sample, maxima, theta, sum_min, count, cand, cap, {}, queue};
         AccItems &items = args.items;
+        items.tiles = (uint32_t)n_iter;
+        items.queues = 1;
         items.run = item_run(per_item, slots.n, n_iter);
         items.groups = (slots.n + items.run - 1) / items.run;
         items.n = n_iter * items.groups;
@@ -2348,6 +2391,7 @@ hipError_t run_accumulate(const DevIndex &ix, const DevQueries &q, const DevCoar
             int64_t wgs = 0;
             if ((e = resident_workgroups(k_accumulate1_queue<VT, SAMPLE>, lds, &wgs)) != hipSuccess)
                 return e;
+            if (n_iter >= kQueues && items.n >= 4 * wgs) items.queues = kQueues;  // see the kernel
             hipLaunchKernelGGL((k_accumulate1_queue<VT, SAMPLE>), dim3((unsigned)std::min(wgs, items.n)),
                                dim3(kAccThreads), lds, s, args);
             return hipGetLastError();

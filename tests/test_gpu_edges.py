@@ -216,6 +216,20 @@ def test_items_of_many_queries(sindi, run, schedule):
         assert np.array_equal(_np(got[1]), np.tile(ref[1], (reps, 1)))
 
 
+@pytest.mark.parametrize("n_tiles", [7, 8, 9, 15, 26])
+def test_items_over_queues(sindi, n_tiles):
+    """Eight work queues of equal and unequal length (tiles off every multiple of eight), from which
+    the workgroups that run dry take: every item is scored once, exactly as by a workgroup each."""
+    corpus, q, scores = _int_setup(100 * n_tiles - 37, 600, False, seed=12)
+    ref = _ranked(scores, 30)
+    idx = sindi.Index(corpus, alpha=1.0, window=100, tile=100, value_dtype="f16")
+    assert idx.info()["n_tiles"] == n_tiles
+    for run in (1, 0):  # 4,200 to 15,600 items of one query, and the call's own choice
+        got = idx.search_coarse(sindi.DeviceCsr.from_host(q), 30, tile_run=run, sample_tiles=n_tiles)
+        assert np.array_equal(_np(got[0]), ref[0])
+        assert np.array_equal(_np(got[1]), ref[1])
+
+
 # ------------------------------------------------------------------ device build
 @pytest.mark.parametrize("nd, vocab, tile", [(255, 9, 300), (513, 4_001, 600), (5_000, 33_000, 5_000),
                                              (9_001, 70_001, 700), (40_000, 300, 1_000)])
