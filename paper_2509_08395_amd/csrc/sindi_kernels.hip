@@ -1604,18 +1604,13 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))
         const acc_args_t g = acc_args();
         const int64_t row = j / g->items.groups;
         const int64_t ti = row * g->items.queues + x;
-        const bool one = g->items.n <= gridDim.x;  // an item each at most (the host sets one queue)
         int64_t next = -1;
-        if (ti < (int64_t)g->items.tiles) {
-            const int32_t s0 = (int32_t)(j - row * g->items.groups) * g->items.run;
-            accumulate1_item<VT, SAMPLE>(ti, s0, min(s0 + g->items.run, g->slots.n), first, [&] {
-                if (threadIdx.x < kWave && !one) next = take();
-            });
-            first = false;
-        } else if (threadIdx.x < kWave && !one) {  // more workgroups than items in the queue
-            next = take();
-        }
-        if (one) break;
+        const int32_t s0 = (int32_t)(j - row * g->items.groups) * g->items.run;
+        accumulate1_item<VT, SAMPLE>(ti, s0, min(s0 + g->items.run, g->slots.n), first, [&] {
+            if (threadIdx.x < kWave && acc_args()->items.n > gridDim.x) next = take();
+        });
+        first = false;
+        if (acc_args()->items.n <= gridDim.x) break;  // an item each (the host sets one queue)
         // (the item's own barriers lie between this write and the last read)
         if (threadIdx.x == 0) s_item = next;
         __syncthreads();
@@ -2391,7 +2386,8 @@ hipError_t run_accumulate(const DevIndex &ix, const DevQueries &q, const DevCoar
             int64_t wgs = 0;
             if ((e = resident_workgroups(k_accumulate1_queue<VT, SAMPLE>, lds, &wgs)) != hipSuccess)
                 return e;
-            if (n_iter >= kQueues && items.n >= 4 * wgs) items.queues = kQueues;  // see the kernel
+            // every queue then holds at least 4/15 of the workgroups' number in items, an eighth start on it
+            if (n_iter >= kQueues && items.n >= 4 * wgs) items.queues = kQueues;
             hipLaunchKernelGGL((k_accumulate1_queue<VT, SAMPLE>), dim3((unsigned)std::min(wgs, items.n)),
                                dim3(kAccThreads), lds, s, args);
             return hipGetLastError();
