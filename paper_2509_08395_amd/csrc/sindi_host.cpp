@@ -1029,11 +1029,11 @@ sindi_status run_search(const sindi_index *ix, Scratch &sc, const Plan &plan, co
                              out_ids, out_scores, s)) != SINDI_OK)
         return st;
     HIP_TRY(hipStreamSynchronize(s));
-    if (sc.report[1]) {
-        if (device_queries) return malformed(sc.report[1]);
-        return fail(SINDI_E_INTERNAL, "%s: validated host queries flagged 0x%x", fn, sc.report[1]);
+    if (sc.report->flags) {
+        if (device_queries) return malformed(sc.report->flags);
+        return fail(SINDI_E_INTERNAL, "%s: validated host queries flagged 0x%x", fn, sc.report->flags);
     }
-    uint32_t n_fail = sc.report[0];
+    uint32_t n_fail = sc.report->left;
     // rows whose sampled threshold missed: a threshold over every tile, then no threshold
     const PassKind retry[2] = {kPassFullSample, kPassKeepAll};
     int32_t *lists[3] = {sc.rows, sc.rows2, sc.rows};
@@ -1047,7 +1047,7 @@ sindi_status run_search(const sindi_index *ix, Scratch &sc, const Plan &plan, co
                                  sc.n_rows + 1, false, out_ids, out_scores, s)) != SINDI_OK)
             return st;
         HIP_TRY(hipStreamSynchronize(s));
-        n_fail = sc.report[0];
+        n_fail = sc.report->left;
     }
     if (n_fail) return fail(SINDI_E_INTERNAL, "%s: %u queries unresolved", fn, n_fail);
     return SINDI_OK;
@@ -1129,24 +1129,24 @@ sindi_status search_impl(sindi_index *ix, const sindi_csr *qc, int32_t k,
                       grow_workspace, &ws);
 }
 
-// Wait for the report of a launch_report on s (report[3] was 0 before it).  The stream is asked
+// Wait for the report of a launch_report on s (report->there was 0 before it).  The stream is asked
 // only every half millisecond (a query of it costs several microseconds), so that a stream that
 // failed, which never writes the report, ends the wait.
-sindi_status wait_report(uint32_t *report, hipStream_t s)
+sindi_status wait_report(PassReport *report, hipStream_t s)
 {
     using Clock = std::chrono::steady_clock;
     for (;;) {
         const auto until = Clock::now() + std::chrono::microseconds(500);
         do {
             for (int i = 0; i < 64; ++i) {
-                if (__atomic_load_n(report + 3, __ATOMIC_ACQUIRE)) return SINDI_OK;
+                if (__atomic_load_n(&report->there, __ATOMIC_ACQUIRE)) return SINDI_OK;
                 __builtin_ia32_pause();
             }
         } while (Clock::now() < until);
         const hipError_t e = hipStreamQuery(s);
         if (e == hipErrorNotReady) continue;
         HIP_TRY(e);
-        if (!__atomic_load_n(report + 3, __ATOMIC_ACQUIRE))
+        if (!__atomic_load_n(&report->there, __ATOMIC_ACQUIRE))
             return fail(SINDI_E_INTERNAL, "the query check left no report");
     }
 }
@@ -1171,13 +1171,14 @@ sindi_status check_dev_queries(sindi_index *ix, const sindi_csr *qc, const char 
     DevCoarse dc{sc.ct, sc.cw, sc.cn, sc.qinv};
     HIP_TRY(launch_query_prep(dq, ix->n_cols, 1.0, dc, ix->term_max.as<float>(), nullptr, sc.err,
                               nullptr, 0, s));
-    uint32_t *report = ix->stage.report();
-    __atomic_store_n(report + 3, 0u, __ATOMIC_RELEASE);
+    PassReport *report = ix->stage.report();
+    __atomic_store_n(&report->there, 0u, __ATOMIC_RELEASE);
     HIP_TRY(launch_report(DevRetry{sc.err, nullptr, nullptr, sc.n_rows, report, false}, s));
     sindi_status st = wait_report(report, s);
     if (st != SINDI_OK) return st;
-    if (report[1]) return fail(SINDI_E_INVALID, "%s: malformed query rows (flags 0x%x)", fn, report[1]);
-    *longest = (int32_t)report[2];
+    if (report->flags)
+        return fail(SINDI_E_INVALID, "%s: malformed query rows (flags 0x%x)", fn, report->flags);
+    *longest = (int32_t)report->longest;
     return SINDI_OK;
 }
 

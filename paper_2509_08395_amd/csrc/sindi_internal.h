@@ -110,14 +110,22 @@ struct DevSlots {
     __device__ __forceinline__ int32_t row(int32_t slot) const { return rows ? rows[slot] : row0 + slot; }
 };
 
+// A pass's outcome as the host reads it (pinned host memory, written by the pass's last kernel).
+struct PassReport {
+    uint32_t left;     // rows left to a retry
+    uint32_t flags;    // the query flags err[0]
+    uint32_t longest;  // err[1]
+    uint32_t there;    // set to 1 behind the others, by launch_report only
+};
+
 // Where a pass leaves its outcome: each row's status, the rows left to a retry (their number in
-// *count, zero when the pass starts), and, written by the pass's last kernel, report (pinned host
-// memory): {*count, err[0], err[1]} (and 1, once they are there, by launch_report).  unchecked: the host has not seen the query flags err yet, so
-// a flagged call must write no output.
+// *count, zero when the pass starts), and the report.  unchecked: the host has not seen the query
+// flags err yet, so a flagged call must write no output.
 struct DevRetry {
     const int32_t *err;
     int32_t *status, *rows;
-    uint32_t *count, *report;
+    uint32_t *count;
+    PassReport *report;
     bool unchecked;
 };
 

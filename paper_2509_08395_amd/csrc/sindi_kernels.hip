@@ -1692,15 +1692,15 @@ __global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v)
 // longest row, into pinned host memory.
 __device__ __forceinline__ void write_report(const DevRetry &r)
 {
-    __hip_atomic_store(r.report, *r.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    __hip_atomic_store(r.report + 1, (uint32_t)r.err[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    __hip_atomic_store(r.report + 2, (uint32_t)r.err[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&r.report->left, *r.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&r.report->flags, (uint32_t)r.err[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&r.report->longest, (uint32_t)r.err[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-// On its own: for a host that waits for the words and not for the stream (report[3] last).
+// On its own: for a host that waits for the words and not for the stream.
 __global__ void k_report(DevRetry r)
 {
     write_report(r);
-    __hip_atomic_store(r.report + 3, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&r.report->there, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ------------------------------------------------------------------ finalize

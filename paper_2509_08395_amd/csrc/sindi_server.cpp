@@ -136,7 +136,7 @@ struct Slot {
     bool wants_retry_buffer = false;          // a retry waits for the server's retry buffer
     Pinned<int64_t> h_ptr, h_ids;
     Pinned<int32_t> h_idx;
-    Pinned<uint32_t> h_report;  // [3] rows the last pass left, query flags, longest row
+    Pinned<PassReport> h_report;  // of the batch's last pass
     Pinned<float> h_val, h_scores;
     std::vector<Request *> reqs;
     Plan pl;
@@ -340,12 +340,12 @@ void sindi_server::finish(Slot &s, sindi_status st, const std::string &msg)
 // when no row is left.
 void sindi_server::complete(Slot &s)
 {
-    if (s.stage == 0 && s.h_report.p[1] != 0) {
-        finish(s, fail(SINDI_E_INTERNAL, "sindi_server: validated queries flagged 0x%x", s.h_report.p[1]),
+    if (s.stage == 0 && s.h_report.p->flags != 0) {
+        finish(s, fail(SINDI_E_INTERNAL, "sindi_server: validated queries flagged 0x%x", s.h_report.p->flags),
                last_error());
         return;
     }
-    const uint32_t left = s.h_report.p[0];
+    const uint32_t left = s.h_report.p->left;
     if (left == 0) {
         finish(s, SINDI_OK, std::string());
         return;
@@ -378,9 +378,9 @@ void sindi_server::start_retry(Slot &s)
     s.sc.arena_bytes = retry_buf.bytes;
     sindi_status e;
     if (s.stage == 0)
-        e = enqueue_retry(s, kPassFullSample, s.sc.rows, s.h_report.p[0], s.sc.rows2, s.sc.n_rows + 1);
+        e = enqueue_retry(s, kPassFullSample, s.sc.rows, s.h_report.p->left, s.sc.rows2, s.sc.n_rows + 1);
     else
-        e = enqueue_retry(s, kPassKeepAll, s.sc.rows2, s.h_report.p[0], s.sc.rows, s.sc.n_rows);
+        e = enqueue_retry(s, kPassKeepAll, s.sc.rows2, s.h_report.p->left, s.sc.rows, s.sc.n_rows);
     s.stage += 1;
     if (e != SINDI_OK) {
         s.launch_st = e;  // the dispatcher drains the stream and publishes the error
@@ -525,7 +525,7 @@ sindi_status create_impl(const sindi_index *ix, const sindi_server_params *pp, s
             HIP_TRY(s.h_val.alloc(qn));
             HIP_TRY(s.h_ids.alloc(mb * kk));
             HIP_TRY(s.h_scores.alloc(mb * kk));
-            HIP_TRY(s.h_report.alloc(3));
+            HIP_TRY(s.h_report.alloc(1));
             s.sc.report = s.h_report.p;
         }
         return SINDI_OK;

@@ -115,7 +115,7 @@ struct Scratch {
     int32_t *ct = nullptr, *cn = nullptr, *err = nullptr, *status = nullptr;
     int32_t *rows = nullptr, *rows2 = nullptr;  // failed rows, two lists for two retries
     uint32_t *n_rows = nullptr;                 // [2] lengths of rows / rows2 (behind err[2])
-    uint32_t *report = nullptr;                 // [3] pinned host memory: DevRetry's report
+    PassReport *report = nullptr;               // pinned host memory
     float *cw = nullptr, *qinv = nullptr;
     double *sabs = nullptr;
     unsigned char *arena = nullptr;
@@ -161,8 +161,8 @@ struct HostStage {
         if (p) (void)hipHostFree(p);
     }
     hipError_t alloc() { return hipHostMalloc((void **)&p, kBytes + 256, hipHostMallocDefault); }
-    uint32_t *report() const { return reinterpret_cast<uint32_t *>(p + kBytes); }
-    uint32_t *report_noalloc() const { return reinterpret_cast<uint32_t *>(p + kBytes + 128); }
+    PassReport *report() const { return reinterpret_cast<PassReport *>(p + kBytes); }
+    PassReport *report_noalloc() const { return reinterpret_cast<PassReport *>(p + kBytes + 128); }
 };
 
 // Grow-only owner of a Scratch (sindi_search's, one per index).

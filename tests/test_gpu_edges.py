@@ -269,3 +269,18 @@ def test_rebuilt_indexes_reuse_and_return_memory(sindi):
     live.close()
     torch.cuda.synchronize()
     assert free0 - torch.cuda.mem_get_info()[0] < 64 << 20  # torch's own small results
+
+
+# ------------------------------------------------------------------ empty index
+def test_search_and_server_over_an_empty_index(sindi):
+    """No documents: every result is padding.  The pass then ends with the report launch, whose
+    words the server keeps a buffer for of its own."""
+    corpus = synth.Csr(np.zeros(1, np.int64), np.zeros(0, np.int32), np.zeros(0, np.float32), 50)
+    idx = sindi.Index(corpus, alpha=0.5, window=1_000)
+    q = _rows(np.random.default_rng(13), [0, 3, 7], 50)
+    for queries in (q, sindi.DeviceCsr.from_host(q)):
+        for ids, sc in (idx.search(queries, 5), idx.search_coarse(queries, 5)):
+            assert (_np(ids) == -1).all() and np.isneginf(_np(sc)).all()
+    with sindi.Server(idx, max_inflight=2, max_batch=2, k_max=5) as srv:
+        got = srv.replay(q, np.full(3, 5, np.int32), np.zeros(3))
+    assert (np.asarray(got[0]) == -1).all() and np.isneginf(np.asarray(got[1])).all()
