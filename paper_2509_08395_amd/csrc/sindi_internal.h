@@ -152,7 +152,8 @@ hipError_t launch_accumulate(const DevIndex &ix, const DevQueries &q, const DevC
                              const int32_t *sum_min, uint32_t *count, uint64_t *cand, int64_t cap,
                              int32_t per_item, int32_t max_terms, unsigned long long *queue, hipStream_t s);
 
-// Per slot: the threshold and the least fixed-point sum that reaches it.
+// Per slot: the threshold and the least fixed-point sum that reaches it (INT32_MAX: none is to be
+// kept; so too where the threshold is -infinity, which leaves the row to a retry).
 hipError_t launch_theta(const float *maxima, int64_t n_maxima, int64_t rank, const DevSlots &slots,
                         const float *qinv, float *theta, int32_t *sum_min, hipStream_t s);
 

@@ -284,3 +284,23 @@ def test_search_and_server_over_an_empty_index(sindi):
     with sindi.Server(idx, max_inflight=2, max_batch=2, k_max=5) as srv:
         got = srv.replay(q, np.full(3, 5, np.int32), np.zeros(3))
     assert (np.asarray(got[0]) == -1).all() and np.isneginf(np.asarray(got[1])).all()
+
+
+# ------------------------------------------------------------------ thresholds out of reach
+@pytest.mark.parametrize("batch", [1, 2])
+@pytest.mark.parametrize("tile, short", [(500, 300), (400, 1), (600, 511)])
+def test_fewer_sampled_maxima_than_the_rank(sindi, tile, short, batch):
+    """Tiles of fewer documents than sampling threads and a pool that asks for more maxima than
+    there are: no threshold is found, and the retries give exactly the ranking order."""
+    nd = 6 * tile + short
+    need = nd // 2 - 3
+    # every tile is sampled: the rank exceeds the maxima that documents have
+    assert 6 * min(tile, 512) + min(short, 512) < min(2 * need + 8, 7 * 512)
+    corpus, q, scores = _int_setup(nd, 40, False, seed=14)
+    idx = sindi.Index(corpus, alpha=1.0, window=tile, tile=tile)
+    assert idx.info()["n_tiles"] == 7
+    ref = _ranked(scores, 30)
+    for schedule in (1, 2):
+        got = idx.search(sindi.DeviceCsr.from_host(q), 30, gamma=need, cand_cap=200, batch=batch,
+                         schedule=schedule)
+        assert np.array_equal(_np(got[0]), ref[0]) and np.array_equal(_np(got[1]), ref[1])
