@@ -41,6 +41,7 @@ constexpr int kWave = 64;
 constexpr int kRerankPerWave = 4;  // pool entries one rerank wave scores at a time
 constexpr int kRerankGroups = 4;   // most such groups per wave (one query table per workgroup)
 constexpr uint32_t kCandBuf = 256;  // candidates a scoring workgroup holds in LDS
+constexpr int kFewHits = 4;        // lanes that place their candidates one by one
 constexpr int kRankSort = 256;     // most keys put in order by counting the larger ones
 constexpr int kTopkRegs = 8;       // pool keys per thread of a selecting k_topk
 constexpr int64_t kRerankFill = 2048;  // rerank workgroups that fill the chip
@@ -1437,26 +1438,76 @@ __device__ __forceinline__ void accumulate1_item(int64_t ti, int32_t s0, int32_t
             const int4 zero = fresh_zero4();  // one per read-out: the loops keep it live
             int base = wave * 256;
             if (!every && !imp) {
-                // A lane's sum at the threshold: into the workgroup's buffer, past its end (rare) to
-                // the list at once.
-                auto hit = [&](int32_t v, int m) {
-                    if (v < th) return;
-                    const uint32_t at = atomicAdd(&s_cand_n, 1u);
-                    if (at < kCandBuf) {
-                        s_cand[at] = ((uint64_t)(uint32_t)v << 32) | (uint32_t)(i << 16 | m);
-                        return;
+                // The sums of K steps that reach the threshold.  Few lanes with any (the common
+                // case): each takes its own place in the workgroup's buffer.  Many lanes, or no room:
+                // the sums go back to the row, then one place in the buffer for all of the wave's and,
+                // for what lies past its end, one in the list.  (Atomics on one word take 12 ns each,
+                // and a query whose pool comes from few tiles has hundreds of candidates in each.
+                // With an atomic for each past the buffer's end, 1,000 queries over 40,000 documents,
+                // gamma 1,000, took 2.85 ms, 0.41 so; over 100,000, gamma 4,096, 36.1 and 2.2; 300,000
+                // in topical order, gamma 500, 0.89 and 0.70.  Without the first case 8.8M documents
+                // with alpha 0.2, beta 0.8 take 4% longer; its limit may be 1 to 16.)
+                auto place = [&](const auto &r, int m0) {
+                    constexpr int K = sizeof(r) / sizeof(int4);
+                    int32_t mx[K], most = INT32_MIN;
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        mx[k] = max(max(r[k].x, r[k].y), max(r[k].z, r[k].w));
+                        most = max(most, mx[k]);
                     }
+                    const int32_t lanes = (int32_t)__popcll(__ballot(most >= th));
+                    if (lanes == 0) return;
+                    const bool few = lanes <= kFewHits;
+                    uint32_t todo = 0;  // bit e: the sum at document at(e) is still to be placed
+                    auto at = [&](int e) { return m0 + (e >> 2) * NW * 256 + (e & 3); };
+                    auto hit = [&](int32_t v, int e) {
+                        if (v < th) return;
+                        if (few) {
+                            const uint32_t j = atomicAdd(&s_cand_n, 1u);
+                            if (j < kCandBuf) {
+                                s_cand[j] = ((uint64_t)(uint32_t)v << 32) | (uint32_t)(i << 16 | at(e));
+                                return;
+                            }
+                        }
+                        A32[at(e)] = v;
+                        todo |= 1u << e;
+                    };
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        if (mx[k] < th) continue;
+                        hit(r[k].x, 4 * k);
+                        hit(r[k].y, 4 * k + 1);
+                        hit(r[k].z, 4 * k + 2);
+                        hit(r[k].w, 4 * k + 3);
+                    }
+                    if (__ballot(todo != 0) == 0) return;
+                    const uint32_t mine = (uint32_t)__popc(todo), incl = wave_incl_scan(mine);
+                    const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+                    uint32_t first = 0, pos = 0;
+                    if (lane == 0) first = atomicAdd(&s_cand_n, n);
+                    first = uni(first);
                     const acc_args_t h = acc_args();
-                    const uint32_t pos = atomicAdd(h->count + slot, 1u);
-                    if ((int64_t)pos < h->cap)
-                        h->cand[(size_t)slot * h->cap + pos] = make_key((float)v * qinv, (uint32_t)(d0 + m));
+                    if (first + n > kCandBuf) {
+                        const uint32_t past = max(first, kCandBuf);  // the first number past the buffer
+                        if (lane == 0) pos = atomicAdd(h->count + slot, first + n - past);
+                        pos = uni(pos) - past;
+                    }
+                    for (uint32_t j = first + incl - mine; todo; todo &= todo - 1u, ++j) {
+                        const int m = at(__ffs(todo) - 1);
+                        const int32_t v = lds_take(A32 + m);
+                        if (j < kCandBuf)
+                            s_cand[j] = ((uint64_t)(uint32_t)v << 32) | (uint32_t)(i << 16 | m);
+                        else if ((int64_t)(pos + j) < h->cap)
+                            h->cand[(size_t)slot * h->cap + (pos + j)] =
+                                make_key((float)v * qinv, (uint32_t)(d0 + m));
+                    }
                 };
                 // whole steps, four of them read together (most hold no candidate), then at most
-                // one across the tile's end
+                // one across the tile's end.  Sums that are not there read INT32_MIN: the threshold
+                // is above zero here, so they are no candidates.
                 for (; base + 256 <= len; base += 4 * NW * 256) {
                     const int m0 = base + lane * 4;
                     int4 r[4];
-                    int32_t mx[4];
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         r[k] = make_int4(INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN);
@@ -1464,27 +1515,20 @@ __device__ __forceinline__ void accumulate1_item(int64_t ti, int32_t s0, int32_t
                             r[k] = lds_take4(A32 + m0 + k * NW * 256);
                         }
                     }
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) mx[k] = max(max(r[k].x, r[k].y), max(r[k].z, r[k].w));
-                    if (__ballot(max(max(mx[0], mx[1]), max(mx[2], mx[3])) >= th) == 0) continue;
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        if (mx[k] < th) continue;
-                        hit(r[k].x, m0 + k * NW * 256);
-                        hit(r[k].y, m0 + k * NW * 256 + 1);
-                        hit(r[k].z, m0 + k * NW * 256 + 2);
-                        hit(r[k].w, m0 + k * NW * 256 + 3);
-                    }
+                    place(r, m0);
                 }
                 base = wave * 256 + (len - wave * 256) / (NW * 256) * (NW * 256);
-                const int m0 = base + lane * 4;
-                if (wave * 256 < len && base + 256 > len && m0 < len) {
-                    const int4 r = *reinterpret_cast<const int4 *>(A32 + m0);
-                    *reinterpret_cast<int4 *>(A32 + m0) = zero;
-                    hit(r.x, m0);
-                    if (m0 + 1 < len) hit(r.y, m0 + 1);
-                    if (m0 + 2 < len) hit(r.z, m0 + 2);
-                    if (m0 + 3 < len) hit(r.w, m0 + 3);
+                if (wave * 256 < len && base + 256 > len) {  // uniform
+                    const int m0 = base + lane * 4;
+                    int4 r[1] = {make_int4(INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN)};
+                    if (m0 < len) {
+                        r[0] = *reinterpret_cast<const int4 *>(A32 + m0);
+                        *reinterpret_cast<int4 *>(A32 + m0) = zero;
+                        if (m0 + 1 >= len) r[0].y = INT32_MIN;
+                        if (m0 + 2 >= len) r[0].z = INT32_MIN;
+                        if (m0 + 3 >= len) r[0].w = INT32_MIN;
+                    }
+                    place(r, m0);
                 }
             } else {
                 const acc_args_t h = acc_args();

@@ -304,3 +304,31 @@ def test_fewer_sampled_maxima_than_the_rank(sindi, tile, short, batch):
         got = idx.search(sindi.DeviceCsr.from_host(q), 30, gamma=need, cand_cap=200, batch=batch,
                          schedule=schedule)
         assert np.array_equal(_np(got[0]), ref[0]) and np.array_equal(_np(got[1]), ref[1])
+
+
+# ------------------------------------------------------------------ candidates past the buffer
+@pytest.mark.parametrize("gamma", [90, 300, 1_100, 2_900])
+@pytest.mark.parametrize("order", ["mixed", "sorted"])
+@pytest.mark.parametrize("tile", [16_381, 2_300, 257])
+def test_candidates_past_the_workgroups_buffer(sindi, tile, order, gamma):
+    """From a few to thousands of candidates per query and tile, spread over the corpus or gathered
+    in its first tiles, so that steps place theirs lane by lane, together, across the buffer's end
+    and past it, whole steps and the one across the tile's end: exactly the ranking order."""
+    rng = np.random.default_rng(15)
+    nd, nq, vocab = 16_381, 70, 40
+    dense = rng.choice([0.0, 1.0, 2.0, 3.0], (nd, vocab), p=[0.6, 0.2, 0.1, 0.1])
+    if order == "sorted":
+        dense = dense[np.argsort(-dense[:, :12].sum(1), kind="stable")]
+    lens = (dense != 0).sum(1)
+    corpus = synth.Csr(np.concatenate([[0], np.cumsum(lens)]), np.nonzero(dense)[1].astype(np.int32),
+                       dense[dense != 0].astype(np.float32), vocab)
+    qd = np.zeros((nq, vocab))
+    qd[:, :12] = rng.choice([1.0, 2.0, 5.0], (nq, 12))
+    q = synth.Csr(np.arange(nq + 1, dtype=np.int64) * 12, np.tile(np.arange(12, dtype=np.int32), nq),
+                  qd[:, :12].reshape(-1).astype(np.float32), vocab)
+    ref = _ranked(qd @ dense.T, gamma)
+    idx = sindi.Index(corpus, alpha=1.0, window=16_384, tile=tile, value_dtype="f16")
+    for run in (1, 64):
+        ids, sc = (_np(t) for t in idx.search_coarse(sindi.DeviceCsr.from_host(q), gamma, cand_cap=9_000,
+                                                     sample_tiles=64, tile_run=run))
+        assert np.array_equal(ids, ref[0]) and np.array_equal(sc, ref[1])
