@@ -2002,8 +2002,9 @@ __global__ __launch_bounds__(NT) void k_finalize(
     extern __shared__ __align__(16) unsigned char smem[];
     const int32_t P = pow2_at_least(need);
     uint64_t *keys = reinterpret_cast<uint64_t *>(smem);                   // [P]
+    // the bitmap of the implicit zeros and the select's tables, used in turn
     uint32_t *bm = reinterpret_cast<uint32_t *>(keys + P);                  // [bm_words]
-    __shared__ SelectLds L;
+    SelectLds &L = *reinterpret_cast<SelectLds *>(keys + P);
     __shared__ uint32_t s_n, s_wsum[NW];
     const int tid = threadIdx.x;
     const int32_t slot = blockIdx.x;
@@ -2090,6 +2091,7 @@ __global__ __launch_bounds__(NT) void k_finalize(
                 each([&](uint64_t key) { f((uint32_t)(key >> 32) < kZeroOrd ? key : 0ull); });
             };
             const uint64_t first = (uint32_t)(cs[0] >> 32) < kZeroOrd ? cs[0] : 0ull;
+            __syncthreads();  // the bitmap gives way to the tables
             const uint64_t kthn = block_select<NT, uint64_t>(first, nt, neg, L, nullptr);
             if (tid == 0) s_n = 0;
             __syncthreads();
@@ -2596,12 +2598,16 @@ hipError_t launch_finalize(const DevIndex &ix, const DevQueries &q, const DevSlo
     // bitmap of candidate ids below need + cap: zero-score documents in id order
     const int64_t bm = theta ? (need + cap + 31) / 32 : 0;
     if (bm > (int64_t)1 << 20) return hipErrorInvalidValue;
+    // Keys and bitmap may take the LDS but for 1,056 bytes, 1,024 of them beside the kernel's own: a
+    // pool of 500 takes candidate buffers of up to 1,269,004 entries.  (With the select's tables in
+    // LDS of their own it was 9,344 fewer.)
+    constexpr size_t kSpare = 1024;
     const size_t keys = (size_t)pow2_at_least(need) * 8;
-    const size_t lds = keys + (size_t)bm * 4;
+    const size_t lds = keys + std::max((size_t)bm * 4, sizeof(SelectLds));
     if (rerank && !pool) return hipErrorInvalidValue;
     hipError_t e;
     auto finalize = [&](auto kernel, int nt) -> hipError_t {
-        hipError_t r = set_lds(kernel, lds);
+        hipError_t r = set_lds(kernel, std::max(lds, keys + (size_t)bm * 4 + kSpare));
         if (r != hipSuccess) return r;
         hipLaunchKernelGGL(kernel, dim3((unsigned)n_slots), dim3(nt), lds, s, ix, slots, count,
                            cand, theta, cap, need, k, (int32_t)bm, pool, out_ids, out_scores, retry);

@@ -332,3 +332,21 @@ def test_candidates_past_the_workgroups_buffer(sindi, tile, order, gamma):
         ids, sc = (_np(t) for t in idx.search_coarse(sindi.DeviceCsr.from_host(q), gamma, cand_cap=9_000,
                                                      sample_tiles=64, tile_run=run))
         assert np.array_equal(ids, ref[0]) and np.array_equal(sc, ref[1])
+
+
+# ------------------------------------------------------------------ limits of the calls
+def test_largest_candidate_buffer(sindi):
+    """The candidate buffer's limit (its bitmap and the pool's keys in LDS): the largest size is
+    taken, one entry more is refused."""
+    nd, vocab = 1_300_000, 64
+    rng = np.random.default_rng(16)
+    ids = np.sort(rng.integers(0, vocab // 2, (nd, 2)) * 2 + [0, 1], axis=1).astype(np.int32)
+    corpus = synth.Csr(np.arange(nd + 1, dtype=np.int64) * 2, ids.reshape(-1),
+                       rng.lognormal(0, 0.8, 2 * nd).astype(np.float32), vocab)
+    idx = sindi.Index(corpus, alpha=1.0, window=100_000, value_dtype="f32", gpu_build=True)
+    q = sindi.DeviceCsr.from_host(_rows(rng, [3, 1, 2], vocab))
+    ref = idx.search(q, 20, gamma=500)
+    got = idx.search(q, 20, gamma=500, cand_cap=1_269_004)
+    assert torch.equal(ref[0], got[0]) and torch.equal(ref[1], got[1])
+    with pytest.raises(sindi.SindiError):
+        idx.search(q, 20, gamma=500, cand_cap=1_269_005)
