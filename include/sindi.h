@@ -203,7 +203,7 @@ sindi_status sindi_search(const sindi_index *idx, const sindi_csr *queries, int3
  * the same search, results bit for bit those of sindi_search, with every
  * piece of device scratch (coarse query terms, per-query status, sampled
  * maxima, candidate lists, rerank pools) carved from one array of 256 MiB
- * that the library holds on each device it runs on until the process ends.
+ * and 1,792 bytes that the library holds on each device it runs on until the process ends.
  * The call allocates nothing: no hipMalloc, hipFree or allocating library
  * routine; the caller passes only inputs and outputs.
  *   queries   device memory only (on_device = 1), of the index's device,

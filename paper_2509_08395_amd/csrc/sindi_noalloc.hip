@@ -13,9 +13,12 @@
 namespace sindi {
 namespace {
 
-// 256 MiB per device: the per-query rows of the call (coarse terms and
-// weights, status, failed-row lists) first, the rest a pass arena.
-constexpr size_t kScratchBytes = size_t(256) << 20;
+// Per device: the per-query rows of the call (coarse terms and weights,
+// status, failed-row lists) first, the rest a pass arena.  256 MiB, and beside
+// them the 1,792 bytes that the work queues' counters take, so that the
+// counters leave the calls as much as there was without them (one query over
+// 33,553,984 documents).
+constexpr size_t kScratchBytes = (size_t(256) << 20) + 1792;
 constexpr int kMaxDevices = 64;
 
 // In host code this name is a host-side stand-in; kernels take the device

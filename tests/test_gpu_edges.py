@@ -350,3 +350,30 @@ def test_largest_candidate_buffer(sindi):
     assert torch.equal(ref[0], got[0]) and torch.equal(ref[1], got[1])
     with pytest.raises(sindi.SindiError):
         idx.search(q, 20, gamma=500, cand_cap=1_269_005)
+
+
+def test_largest_index_of_a_search_without_allocations(sindi):
+    """The static array's limit, one query of the pass that keeps every document: the largest index
+    is searched, with one document more the call is refused and leaves its outputs."""
+    import ctypes
+    lib = sindi._lib.load()
+    q = sindi.DeviceCsr.from_host(synth.Csr(np.array([0, 1], np.int64), np.zeros(1, np.int32),
+                                            np.ones(1, np.float32), 1))
+    qs, p = q.struct(), sindi._lib.SindiSearchParams(1.0, 5, 0, 0, 0, 0)
+    for nd, fits in ((33_553_984, True), (33_553_985, False)):
+        indptr = np.zeros(nd + 1, np.int64)
+        indptr[nd - 2:] = [1, 2, 2]
+        corpus = synth.Csr(indptr, np.zeros(2, np.int32), np.array([1, 2], np.float32), 1)
+        idx = sindi.Index(corpus, alpha=1.0, window=100_000, value_dtype="f32", gpu_build=True)
+        ids = torch.full((1, 5), -7, dtype=torch.int64, device="cuda")
+        sc = torch.full((1, 5), 7.0, device="cuda")
+        rc = lib.sindi_search_noalloc(idx._h, ctypes.byref(qs), 5, ctypes.byref(p),
+                                      ctypes.c_void_p(ids.data_ptr()), ctypes.c_void_p(sc.data_ptr()),
+                                      ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        idx.close()
+        if fits:
+            assert rc == 0
+            assert ids.tolist() == [[nd - 2, nd - 3, 0, 1, 2]] and sc.tolist() == [[2.0, 1.0, 0.0, 0.0, 0.0]]
+        else:
+            assert rc == sindi._lib.SINDI_E_INVALID
+            assert (ids == -7).all() and (sc == 7.0).all()
