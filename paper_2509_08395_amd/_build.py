@@ -16,8 +16,8 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-I", os.path.joi
           "-I", CSRC, "-Wall", "-Wno-unused-result"]
 DEVICE = ["--offload-arch=gfx950", "-munsafe-fp-atomics",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-          # device atomics as written: the kernels elect their lane themselves, and the pass that
-          # rewrites them waits for the result at once
+          # atomics as written: where many lanes of a wave meet on one word the kernels place them
+          # together themselves; the pass that does so for every atomic waits for the result at once
           "-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]
 
 

@@ -2054,7 +2054,9 @@ __global__ __launch_bounds__(NT) void k_finalize(
         if (nt > (int64_t)cnt - n_pos || words > bm_words) return false;
         __syncthreads();
         each([&](uint64_t key) {
-            if ((uint32_t)(key >> 32) > kZeroOrd) keys[atomicAdd(&s_n, 1u)] = key;
+            const bool take = (uint32_t)(key >> 32) > kZeroOrd;
+            const uint32_t p = wave_place(&s_n, take);
+            if (take) keys[p] = key;
         });
         for (int w = tid; w < words; w += NT) bm[w] = 0u;
         __syncthreads();
@@ -2096,7 +2098,9 @@ __global__ __launch_bounds__(NT) void k_finalize(
             if (tid == 0) s_n = 0;
             __syncthreads();
             neg([&](uint64_t key) {
-                if (key && key >= kthn) keys[n_pos + zt + atomicAdd(&s_n, 1u)] = key;
+                const bool take = key && key >= kthn;
+                const uint32_t p = wave_place(&s_n, take);
+                if (take) keys[n_pos + zt + p] = key;
             });
         }
         __syncthreads();

@@ -377,3 +377,25 @@ def test_largest_index_of_a_search_without_allocations(sindi):
         else:
             assert rc == sindi._lib.SINDI_E_INVALID
             assert (ids == -7).all() and (sc == 7.0).all()
+
+
+# ------------------------------------------------------------------ implicit zeros
+@pytest.mark.parametrize("nd, cand_cap", [(12_000, 5_000), (12_000, 2_060), (3_000, 2_700)])
+@pytest.mark.parametrize("signed", [False, True])
+def test_pools_of_positives_zeros_and_negatives(sindi, nd, cand_cap, signed):
+    """Pools of one to thousands of positive sums, of documents without a common term, and of
+    negative sums where those run out, from registers and from memory: exactly the ranking order."""
+    rng = np.random.default_rng(17)
+    vocab, nq = 50, 24
+    dense = np.where(rng.random((nd, vocab)) < np.linspace(0.0005, 0.8, vocab) ** 2, rng.choice([1.0, 2.0], (nd, vocab)), 0.0)
+    if signed:
+        dense *= rng.choice([-1.0, 1.0], (nd, vocab), p=[0.8, 0.2])
+    corpus = synth.Csr(np.concatenate([[0], np.cumsum((dense != 0).sum(1))]), np.nonzero(dense)[1].astype(np.int32),
+                       dense[dense != 0].astype(np.float32), vocab)
+    terms = rng.integers(0, vocab, nq).astype(np.int32)
+    q = synth.Csr(np.arange(nq + 1, dtype=np.int64), terms, np.ones(nq, np.float32), vocab)
+    idx = sindi.Index(corpus, alpha=1.0, window=1_000, tile=500)
+    for k in (10, 2_000):
+        ref = _ranked(dense.T[terms], k)
+        got = idx.search_coarse(sindi.DeviceCsr.from_host(q), k, cand_cap=cand_cap)
+        assert np.array_equal(_np(got[0]), ref[0]) and np.array_equal(_np(got[1]), ref[1])
