@@ -157,6 +157,17 @@ sindi_status sindi_build(const sindi_csr *corpus, const sindi_build_params *para
 
 void sindi_index_free(sindi_index *idx);
 
+/*
+ * Give device memory that the library holds idle back to the driver.  Memory
+ * of freed indexes and of builds is kept for the next build, so that an index
+ * rebuilt beside the one it replaces does not wait for the driver: on each
+ * device at most as much as the library still has in use there, and 1/128 of
+ * the device's memory; with the last index all of it goes back, and so it does
+ * when an allocation of the library fails.  This call gives it back at once,
+ * for other users of the device.
+ */
+sindi_status sindi_release_memory(void);
+
 sindi_status sindi_index_get_info(const sindi_index *idx, sindi_index_info *out);
 
 /*

@@ -20,12 +20,17 @@ import numpy as np
 from . import _lib
 from ._lib import DTYPES, SindiError  # noqa: F401
 
-__all__ = ["Index", "Server", "DeviceCsr", "SindiScore", "SindiError", "version",
+__all__ = ["Index", "Server", "DeviceCsr", "SindiScore", "SindiError", "version", "release_memory",
            "profile_enable", "profile_read"]
 
 
 def version() -> str:
     return _lib.load().sindi_version().decode()
+
+
+def release_memory() -> None:
+    """Give device memory that the library keeps for the next build back to the driver."""
+    _lib.check(_lib.load().sindi_release_memory())
 
 
 def profile_enable(on: bool = True) -> None:

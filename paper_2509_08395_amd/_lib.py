@@ -68,7 +68,8 @@ class SindiProfile(ctypes.Structure):
 PROFILE_CLASSES = ("query_prep", "accumulate_threshold", "accumulate_score", "threshold_select",
                    "finalize")
 
-EXPORTS = ("sindi_build", "sindi_index_free", "sindi_index_get_info", "sindi_index_export",
+EXPORTS = ("sindi_build", "sindi_index_free", "sindi_release_memory", "sindi_index_get_info",
+           "sindi_index_export",
            "sindi_search", "sindi_search_noalloc", "sindi_search_coarse", "sindi_score_forward",
            "sindi_score_backward",
            "sindi_server_create", "sindi_server_submit", "sindi_server_wait",
@@ -103,13 +104,14 @@ def load():
                                 ctypes.POINTER(P)]
     lib.sindi_index_free.argtypes = [P]
     lib.sindi_index_free.restype = None
+    lib.sindi_release_memory.argtypes = []
     lib.sindi_index_get_info.argtypes = [P, ctypes.POINTER(SindiIndexInfo)]
     lib.sindi_index_export.argtypes = [P, P, P, P, P, P]
     for f in (lib.sindi_search, lib.sindi_search_coarse, lib.sindi_search_noalloc):
         f.argtypes = [P, ctypes.POINTER(SindiCsr), I32, ctypes.POINTER(SindiSearchParams), P, P, P]
     lib.sindi_score_forward.argtypes = [P, ctypes.POINTER(SindiCsr), P, I32, P, P, P]
     lib.sindi_score_backward.argtypes = [P, ctypes.POINTER(SindiCsr), P, I32, P, P, P, P, P]
-    for f in (lib.sindi_build, lib.sindi_index_get_info, lib.sindi_index_export,
+    for f in (lib.sindi_build, lib.sindi_release_memory, lib.sindi_index_get_info, lib.sindi_index_export,
               lib.sindi_search, lib.sindi_search_coarse, lib.sindi_search_noalloc,
               lib.sindi_score_forward, lib.sindi_score_backward):
         f.restype = ctypes.c_int

@@ -55,13 +55,20 @@ int host_threads()
 // ------------------------------------------------------------------ device memory
 namespace {
 constexpr size_t kPoolMin = size_t(1) << 20;  // smaller blocks go to the driver at once
+constexpr size_t kPoolShare = 128;            // of the device's memory, the most that is kept
 
-size_t size_class(size_t n)
+// Sixteen to thirty-two classes to each power of two: at most 1/16 more than asked for.
+constexpr size_t size_class(size_t n)
 {
-    size_t step = size_t(2) << 20;
-    while (step * 32 <= n) step <<= 1;  // between 1/32 and 1/16 of n
+    size_t step = size_t(64) << 10;
+    while (step * 32 <= n) step <<= 1;
     return (n + step - 1) / step * step;
 }
+static_assert(size_class(kPoolMin) == kPoolMin && size_class(kPoolMin + 1) <= kPoolMin / 16 * 17 &&
+                  size_class((size_t(1) << 35) + 1) <= (size_t(1) << 35) / 16 * 17,
+              "size classes");
+// What device_free may keep: blocks of a class (not those of an allocation's last resort).
+constexpr bool pooled(size_t capacity) { return capacity >= kPoolMin && size_class(capacity) == capacity; }
 
 struct BlockPool {
     std::mutex mu;
@@ -69,13 +76,21 @@ struct BlockPool {
     size_t kept_bytes = 0, used_bytes = 0, most = 0;
 };
 
-// One per device; never destroyed (indexes may outlive the library's static objects).
+struct Pools {
+    std::mutex mu;
+    std::map<int, BlockPool *> of;
+};
+Pools &pools()
+{
+    static Pools *p = new Pools();  // never destroyed: indexes may outlive static objects
+    return *p;
+}
+
+// One per device.
 BlockPool &pool_of(int device)
 {
-    static std::mutex mu;
-    static std::map<int, BlockPool *> *pools = new std::map<int, BlockPool *>();
-    std::lock_guard<std::mutex> lock(mu);
-    BlockPool *&p = (*pools)[device];
+    std::lock_guard<std::mutex> lock(pools().mu);
+    BlockPool *&p = pools().of[device];
     if (!p) p = new BlockPool();
     return *p;
 }
@@ -90,64 +105,86 @@ void give_back(BlockPool &b, size_t bytes)
         b.kept.erase(it);
     }
 }
+
+// hipMalloc; where memory is short, once more with what the pool kept given back.
+hipError_t alloc_or_give_back(BlockPool &b, void **p, size_t bytes)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e != hipErrorOutOfMemory || b.kept.empty()) return e;
+    (void)hipGetLastError();
+    give_back(b, 0);
+    return hipMalloc(p, bytes);
+}
 }  // namespace
 
-hipError_t device_alloc(void **p, size_t bytes, size_t *capacity, int *device)
-{
+hipError_t device_alloc(void **p, size_t bytes, size_t *capacity, int *device) noexcept
+try {
     *p = nullptr;
     hipError_t e = hipGetDevice(device);
     if (e != hipSuccess) return e;
-    if (bytes < kPoolMin) {
-        *capacity = bytes;
-        return hipMalloc(p, bytes);
-    }
-    *capacity = size_class(bytes);
     BlockPool &b = pool_of(*device);
     std::lock_guard<std::mutex> lock(b.mu);
-    const auto it = b.kept.find(*capacity);
+    *capacity = bytes < kPoolMin ? bytes : size_class(bytes);
+    const auto it = pooled(*capacity) ? b.kept.find(*capacity) : b.kept.end();
     if (it != b.kept.end()) {
         *p = it->second;
         b.kept_bytes -= it->first;
         b.kept.erase(it);
-    } else if ((e = hipMalloc(p, *capacity)) != hipSuccess) {
-        if (b.kept.empty() || e != hipErrorOutOfMemory) return e;
-        (void)hipGetLastError();
-        give_back(b, 0);
-        if ((e = hipMalloc(p, *capacity)) != hipSuccess) return e;
+    } else {
+        e = alloc_or_give_back(b, p, *capacity);
+        if (e == hipErrorOutOfMemory && *capacity > bytes) {  // the last resort: not a byte more
+            (void)hipGetLastError();
+            *capacity = bytes;
+            e = hipMalloc(p, bytes);
+        }
+        if (e != hipSuccess) return e;
     }
-    b.used_bytes += *capacity;
+    if (pooled(*capacity)) b.used_bytes += *capacity;
     return hipSuccess;
+} catch (...) {
+    return hipErrorOutOfMemory;  // of the host
 }
 
-void device_free(void *p, size_t capacity, int device)
+void device_free(void *p, size_t capacity, int device) noexcept
 {
-    if (capacity < kPoolMin) {
+    if (!pooled(capacity)) {
         (void)hipFree(p);
         return;
     }
-    BlockPool &b = pool_of(device);
     int current = device;
     const bool here = hipGetDevice(&current) == hipSuccess &&
                       (current == device || hipSetDevice(device) == hipSuccess);
     const bool idle = here && hipDeviceSynchronize() == hipSuccess;
-    {
+    bool keep = false;
+    try {
+        BlockPool &b = pool_of(device);
         std::lock_guard<std::mutex> lock(b.mu);
         b.used_bytes -= capacity;
         if (!b.most) {
             size_t free_bytes = 0, total = 0;
             if (!here || hipMemGetInfo(&free_bytes, &total) != hipSuccess) total = 0;
-            b.most = total / 16;
+            b.most = total / kPoolShare;
         }
         const size_t room = std::min(b.used_bytes, b.most);
         if (idle && capacity <= room) {
             b.kept.emplace(capacity, p);
+            keep = true;
             b.kept_bytes += capacity;
-        } else {
-            (void)hipFree(p);
         }
         give_back(b, room);
+    } catch (...) {  // no host memory for the entry: the driver gets the block
     }
+    if (!keep) (void)hipFree(p);
     if (here && current != device) (void)hipSetDevice(current);
+}
+
+void device_give_back()
+{
+    std::lock_guard<std::mutex> lock(pools().mu);
+    for (auto &p : pools().of) {
+        std::lock_guard<std::mutex> held(p.second->mu);
+        give_back(*p.second, 0);
+    }
 }
 
 // ------------------------------------------------------------------ profiling
@@ -1231,6 +1268,16 @@ sindi_status sindi_build(const sindi_csr *corpus, const sindi_build_params *para
 }
 
 void sindi_index_free(sindi_index *idx) { delete idx; }
+
+sindi_status sindi_release_memory(void)
+{
+    try {
+        device_give_back();
+        return SINDI_OK;
+    } catch (...) {
+        return fail(SINDI_E_INTERNAL, "sindi_release_memory: unexpected exception");
+    }
+}
 
 sindi_status sindi_index_get_info(const sindi_index *ix, sindi_index_info *o)
 {

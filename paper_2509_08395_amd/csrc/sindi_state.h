@@ -53,13 +53,15 @@ void parallel_for(int64_t n, F fn)
 // Device memory of the library.  Blocks of a MiB and more are rounded up to a size class (at most
 // 1/16 more) and, when released, kept for the next allocation of their class: at most as many
 // bytes as the library still has in use on the device (so the last index to go gives everything
-// back) and 1/16 of its memory; an allocation that fails gives all of it back first.  Rebuilding
-// an index beside the one it replaces then reuses the memory of the last one: taking it from the
-// driver each time ran into the clearing of freed memory (1M documents: 6 ms a build, every so
-// often 16 to 38 ms, in spells of hundreds of builds).  Safe with threads; a release waits for
-// the device, as hipFree does, so no stream still uses a kept block.
-hipError_t device_alloc(void **p, size_t bytes, size_t *capacity, int *device);
-void device_free(void *p, size_t capacity, int device);
+// back) and 1/128 of its memory.  An allocation that fails gives all of it back and tries again (then
+// without the rounding), and so does sindi_release_memory.  Rebuilding an index beside the one it
+// replaces then reuses the memory of the last one: taking it from the driver each time ran into the
+// clearing of freed memory (1M documents: 6 ms a build, every so often 16 to 38 ms, in spells of
+// hundreds of builds).  Safe with threads; a release waits for the device, as hipFree does, so no
+// stream still uses a kept block.
+hipError_t device_alloc(void **p, size_t bytes, size_t *capacity, int *device) noexcept;
+void device_free(void *p, size_t capacity, int device) noexcept;
+void device_give_back();  // every kept block of every device
 
 // Grow-only device buffer.
 struct DBuf {

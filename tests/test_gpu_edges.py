@@ -399,3 +399,48 @@ def test_pools_of_positives_zeros_and_negatives(sindi, nd, cand_cap, signed):
         ref = _ranked(dense.T[terms], k)
         got = idx.search_coarse(sindi.DeviceCsr.from_host(q), k, cand_cap=cand_cap)
         assert np.array_equal(_np(got[0]), ref[0]) and np.array_equal(_np(got[1]), ref[1])
+
+
+# ------------------------------------------------------------------ memory kept between builds
+def test_memory_kept_between_builds_is_bounded_and_released(sindi):
+    """What the library keeps idle: no more than the live indexes hold, nothing once it is told to
+    release it or the last index is gone."""
+    nd, vocab, n = 400_000, 2_000, 40
+    g = torch.Generator("cuda").manual_seed(18)
+    ids = (torch.rand((nd, vocab // n), device="cuda", generator=g) * n).int()
+    ids += torch.arange(vocab // n, device="cuda", dtype=torch.int32) * n
+    values = torch.rand(ids.numel(), device="cuda", generator=g) + 0.1
+    corpus = sindi.DeviceCsr(torch.arange(nd + 1, device="cuda") * ids.shape[1], ids.reshape(-1), values, vocab)
+    del ids
+
+    def build():
+        return sindi.Index(corpus, alpha=0.6, window=100_000, value_dtype="f16", gpu_build=True)
+
+    def held():  # by the library: torch allocates nothing in between
+        torch.cuda.synchronize()
+        return free0 - torch.cuda.mem_get_info()[0]
+
+    build().close()  # code objects and the like are loaded
+    sindi.release_memory()
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    slack = 4 << 20  # below any of the large arrays
+    a = build()
+    size = a.info()["device_bytes"]
+    assert size > 16 * slack
+    sindi.release_memory()  # the build's scratch
+    alone = held()
+    assert size - slack < alone < size * 17 // 16 + slack
+    for _ in range(3):
+        b = build()
+        a.close()
+        a = b
+        assert held() <= 2 * alone + slack
+    assert held() >= alone + slack  # something is kept for the next build
+    sindi.release_memory()
+    assert abs(held() - alone) < slack
+    b = build()
+    a.close()
+    assert held() <= 2 * alone + slack
+    b.close()
+    assert held() < slack
