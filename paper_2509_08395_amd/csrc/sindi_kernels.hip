@@ -1589,13 +1589,14 @@ __device__ __forceinline__ void accumulate1_item(int64_t ti, int32_t s0, int32_t
     }
 }
 
-// One workgroup per item.
+// One workgroup per item: grid (items of a tile, tiles over two dimensions).
 template <int VT, bool SAMPLE>
 __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_accumulate1(AccArgs)
 {
     const acc_args_t g = acc_args();
-    const int64_t ti = blockIdx.x / (uint32_t)g->items.groups;
-    const int32_t s0 = (int32_t)(blockIdx.x % (uint32_t)g->items.groups) * g->items.run;
+    const int64_t ti = (int64_t)blockIdx.z * gridDim.y + blockIdx.y;
+    if (ti >= g->items.tiles) return;  // the whole workgroup
+    const int32_t s0 = (int32_t)blockIdx.x * g->items.run;
     accumulate1_item<VT, SAMPLE>(ti, s0, min(s0 + g->items.run, g->slots.n), true, [] {});
 }
 
@@ -2447,14 +2448,13 @@ hipError_t run_accumulate(const DevIndex &ix, const DevQueries &q, const DevCoar
                                dim3(kAccThreads), lds, s, args);
             return hipGetLastError();
         }
-        if (items.n > INT32_MAX) {  // beyond a grid: the longest items
-            items.run = kWave;
-            items.groups = (slots.n + items.run - 1) / items.run;
-            items.n = n_iter * items.groups;
-            if (items.n > INT32_MAX) return hipErrorInvalidValue;
-        }
-        hipLaunchKernelGGL((k_accumulate1<VT, SAMPLE>), dim3((unsigned)items.n), dim3(kAccThreads), lds,
-                           s, args);
+        // A grid dimension holds less than 2^32 threads, and one that exceeds that is cut off without
+        // an error (8.4 million items of 512 threads), the second and third 65,535 workgroups.
+        if ((int64_t)items.groups * kAccThreads > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
+        const int64_t rows = std::min<int64_t>(n_iter, 65535);
+        hipLaunchKernelGGL((k_accumulate1<VT, SAMPLE>),
+                           dim3((unsigned)items.groups, (unsigned)rows, (unsigned)((n_iter + rows - 1) / rows)),
+                           dim3(kAccThreads), lds, s, args);
     } else {
         const int64_t n_batches = (slots.n + B - 1) / B;
         // Contiguous tile ranges per workgroup (see the kernel); the range length

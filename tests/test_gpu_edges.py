@@ -444,3 +444,16 @@ def test_memory_kept_between_builds_is_bounded_and_released(sindi):
     assert held() <= 2 * alone + slack
     b.close()
     assert held() < slack
+
+
+# ------------------------------------------------------------------ large grids
+@pytest.mark.parametrize("nd, nq, tile", [(100_000, 1_400, 16), (140_001, 3, 2)])
+def test_items_beyond_one_grid_dimension(sindi, nd, nq, tile):
+    """One workgroup per item, more items than threads of one grid dimension can count and more
+    tiles than its second holds: every item is scored, as from the queues."""
+    corpus = synth.generate(nd, 300, nnz=("poisson", 6.0), seed=19)
+    q = sindi.DeviceCsr.from_host(synth.generate(nq, 300, nnz=("poisson", 4.0), seed=20, stream=1))
+    idx = sindi.Index(corpus, alpha=1.0, window=nd, tile=tile)
+    ref = idx.search(q, 10, gamma=100)
+    got = idx.search(q, 10, gamma=100, schedule=1, tile_run=1)
+    assert torch.equal(ref[0], got[0]) and torch.equal(ref[1], got[1])
