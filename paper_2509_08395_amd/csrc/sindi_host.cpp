@@ -1050,8 +1050,9 @@ sindi_status run_search(const sindi_index *ix, Scratch &sc, const Plan &plan, co
     };
     // Device queries are validated before anything reaches the caller's outputs.  A call of few
     // entries does not wait for that: the entries bound its longest row, and its kernels write
-    // nothing where the flags are set.
-    const bool unchecked = device_queries && ix->n_docs > 0 &&
+    // nothing where the flags are set.  (Merged batches size their lists in LDS by the longest row,
+    // and beside the tiles' score rows there is no room for a looser bound.)
+    const bool unchecked = device_queries && ix->n_docs > 0 && pl.batch == 1 &&
                            dq.nnz <= (nq == 1 ? kUncheckedOne : kUncheckedNnz);
     if (device_queries && !unchecked) {
         int32_t e2[2] = {0, 0};

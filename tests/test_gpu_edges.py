@@ -457,3 +457,16 @@ def test_items_beyond_one_grid_dimension(sindi, nd, nq, tile):
     ref = idx.search(q, 10, gamma=100)
     got = idx.search(q, 10, gamma=100, schedule=1, tile_run=1)
     assert torch.equal(ref[0], got[0]) and torch.equal(ref[1], got[1])
+
+
+@pytest.mark.parametrize("tile, batch", [(3_836, 8), (8_700, 4)])
+@pytest.mark.parametrize("lens", [[25, 9, 12, 9], [20]])
+def test_merged_batches_of_few_entries_beside_full_tiles(sindi, tile, batch, lens):
+    """Merged batches whose score rows leave the lists room for short queries only: calls of few
+    entries in all are taken where each of their rows fits, as calls of many are."""
+    rng = np.random.default_rng(21)
+    corpus = synth.generate(3 * tile, 500, nnz=("poisson", 5.0), seed=22)
+    idx = sindi.Index(corpus, alpha=1.0, window=tile, tile=tile)
+    q = sindi.DeviceCsr.from_host(_rows(rng, lens, 500))
+    ref, got = idx.search(q, 10, gamma=100), idx.search(q, 10, gamma=100, batch=batch)
+    assert torch.equal(ref[0], got[0]) and torch.equal(ref[1], got[1])
