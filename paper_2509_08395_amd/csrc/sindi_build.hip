@@ -926,17 +926,17 @@ hipError_t build_prune_long(const int64_t *ptr, const int32_t *idx, const float 
 }
 
 // Parts per tile: a CU holds one fill workgroup, so the fill takes as many rounds as its workgroups
-// (tiles, parts, term passes) fill the 256 CUs, each a part long plus setting up its cursors (0.003 of
+// (tiles, parts, term passes) fill the device's CUs, each a part long plus setting up its cursors (0.003 of
 // a tile's time); the count that makes this least, of at least 256 documents of a full tile.
-// 80 tiles: 16 parts (10 parts, four rounds with the last nearly empty: 1.40 ms).
-int32_t build_parts(int64_t n_tiles, int64_t n_cols, int32_t tile_max)
+// 80 tiles, 256 CUs: 16 parts (10 parts, four rounds with the last nearly empty: 1.40 ms).
+int32_t build_parts(int64_t n_tiles, int64_t n_cols, int32_t tile_max, int32_t cus)
 {
     const int64_t wgs = std::max<int64_t>(1, n_tiles * ((n_cols + kFillTerms - 1) / kFillTerms));
     const int32_t most = (int32_t)std::max<int64_t>(1, std::min<int64_t>(16, tile_max / 256));
     int32_t best = 1;
     double least = 1e300;
     for (int32_t p = 1; p <= most; ++p) {
-        const double cost = (double)((wgs * p + 255) / 256) * (1.0 / p + 0.003);
+        const double cost = (double)((wgs * p + cus - 1) / cus) * (1.0 / p + 0.003);
         if (cost < 0.98 * least) {
             least = cost;
             best = p;

@@ -463,7 +463,9 @@ sindi_status build_device(const sindi_csr *c, const sindi_build_params *p, hipSt
     const int32_t *idx = ix->indices.as<int32_t>();
     const float *val = ix->values.as<float>();
     // the build's scratch as one allocation (each one more costs some 0.15 ms to make and free)
-    const int32_t parts = build_parts(n_tiles, nc, ix->tile_max);
+    int cus = 0;
+    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ix->device));
+    const int32_t parts = build_parts(n_tiles, nc, ix->tile_max, std::max(cus, 1));
     const size_t stride = (size_t)nc + 1;
     size_t scratch = 0;
     auto piece = [&](size_t bytes) {

@@ -189,7 +189,7 @@ hipError_t build_prune_long(const int64_t *ptr, const int32_t *idx, const float 
 // Parts that separate workgroups count and fill of every tile; part_cnt (build_part_bytes): the
 // parts' counts per term, then (after build_list_offsets, which also writes the
 // lists' lengths cnt) the postings of the parts before.
-int32_t build_parts(int64_t n_tiles, int64_t n_cols, int32_t tile_max);
+int32_t build_parts(int64_t n_tiles, int64_t n_cols, int32_t tile_max, int32_t cus);
 size_t build_part_bytes(int64_t n_tiles, int32_t parts, int64_t n_cols);
 hipError_t build_count_lists(const int64_t *ptr, const int32_t *idx, const float *val,
                              const uint8_t *keep, int64_t n_rows, int64_t n_cols,
