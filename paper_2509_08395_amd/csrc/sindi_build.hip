@@ -557,8 +557,9 @@ __global__ __launch_bounds__(kOffsetThreads) void k_list_offsets(uint16_t *part_
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     if (p0 + i >= parts) break;
-                    *reinterpret_cast<uint4 *>(pc + (size_t)(p0 + i) * part_stride(n_cols) + j0) =
-                        make_uint4(n[0] | n[1] << 16, n[2] | n[3] << 16, n[4] | n[5] << 16, n[6] | n[7] << 16);
+                    if (parts > 1)  // (a lone part starts at the lists' first postings)
+                        *reinterpret_cast<uint4 *>(pc + (size_t)(p0 + i) * part_stride(n_cols) + j0) =
+                            make_uint4(n[0] | n[1] << 16, n[2] | n[3] << 16, n[4] | n[5] << 16, n[6] | n[7] << 16);
                     const uint32_t w[4] = {k[i].x, k[i].y, k[i].z, k[i].w};
 #pragma unroll
                     for (int u = 0; u < kOffsetPer; ++u) n[u] += (w[u / 2] >> (16 * (u & 1))) & 0xFFFFu;
@@ -636,7 +637,7 @@ __global__ __launch_bounds__(kFillThreads) void k_fill_lists(
     if (j0 >= n_cols) return;  // the whole workgroup
     const uint32_t *g = goff + (size_t)t * (size_t)(n_cols + 1);
     const uint16_t *before = part_cnt + (size_t)blockIdx.x * part_stride(n_cols) + (size_t)j0;
-    for (int64_t j = tid; j < j1 - j0; j += kFillThreads) word[j] = before[j];
+    for (int64_t j = tid; j < j1 - j0; j += kFillThreads) word[j] = parts > 1 ? before[j] : 0u;
     const int64_t tile0 = tile_doc[t], P0 = tile_post[t];
     int64_t d, d1;
     part_docs(tile_doc, t, (int32_t)(blockIdx.x % (uint32_t)parts), parts, d, d1);
