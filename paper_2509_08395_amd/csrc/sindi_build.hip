@@ -783,13 +783,16 @@ __global__ void k_fill_pads(const uint32_t *goff, const uint32_t *cnt, const int
 // and a bin holds ceil(count / bins) of them at most.  A chunk of one group (one lane) keeps its
 // order, and pads stay at the list's end.  A wave takes 64 lists of tile blockIdx.x at a time
 // (their offsets loaded together, a list per lane) and reorders those of two or more groups one
-// after another.  The lists of a wave lie the grid's number of waves apart: the long lists of a
-// vocabulary ordered by frequency sit side by side, and a wave that took 64 neighbours walked
-// some 700 chunks alone (1M documents 1.80 ms, interleaved 0.52 ms).
+// after another.  They come in runs of 2^lg_run neighbours, the grid's number of waves apart: the
+// long lists of a vocabulary ordered by frequency sit side by side, and a wave that took 64
+// neighbours walked some 700 chunks alone (1M documents 1.80 ms, runs of one 0.52 ms).  Longer runs
+// keep the lanes' offsets in fewer sectors, which counts where the tiles are small and many
+// (deal_run).
 __global__ __launch_bounds__(kDealThreads) void k_deal_chunks(const uint32_t *goff,
                                                               const int64_t *tile_post,
-                                                              int64_t n_cols, int32_t vbytes,
-                                                              uint16_t *post_doc, void *post_val)
+                                                              int64_t n_cols, int32_t lg_run,
+                                                              int32_t vbytes, uint16_t *post_doc,
+                                                              void *post_val)
 {
     constexpr int NW = kDealThreads / kWave;
     __shared__ uint32_t s_doc[NW][4 * kChunk], s_val[NW][4 * kChunk];
@@ -798,10 +801,11 @@ __global__ __launch_bounds__(kDealThreads) void k_deal_chunks(const uint32_t *go
     const int r = lane & 31, h = lane >> 5;
     const int64_t tile_first = tile_post[t];
     const int64_t waves = (int64_t)gridDim.y * NW;
-    for (int64_t j0 = (int64_t)blockIdx.y * NW + w; j0 < n_cols; j0 += waves * kWave) {
+    for (int64_t run = (int64_t)blockIdx.y * NW + w; run << lg_run < n_cols; run += waves * (kWave >> lg_run)) {
         uint32_t gs_l = 0, pad_l = 0, ng_l = 0;
-        if (j0 + lane * waves < n_cols) {
-            const size_t o = (size_t)t * (size_t)(n_cols + 1) + (size_t)(j0 + lane * waves);
+        const int64_t j = ((run + (lane >> lg_run) * waves) << lg_run) + (lane & ((1 << lg_run) - 1));
+        if (j < n_cols) {
+            const size_t o = (size_t)t * (size_t)(n_cols + 1) + (size_t)j;
             const uint32_t g = goff[o];
             gs_l = g & kGoffMask;
             pad_l = g >> 30;
@@ -1027,16 +1031,28 @@ hipError_t build_fill_pads(const uint32_t *goff, const uint32_t *cnt, const int6
     return hipGetLastError();
 }
 
+// Neighbouring lists (2^x of them, at most 8) that a wave of the bank-order pass takes: as many as
+// hold 64 chunks at most in a full tile.  In us, runs of 1 and 8: 500,000 documents in tiles of 20
+// 4296 1371, of 100 847 451, of 300 377 305; 1M documents, 250K terms, tiles of 500 1472 979, of
+// 2,000 450 352, of 12,500 164 320 (a wave then walks the eight longest lists alone).
+static int32_t deal_run(int32_t tile_max)
+{
+    const int32_t chunks = (tile_max + 4 * kChunk - 1) / (4 * kChunk);
+    int32_t lg = 3;
+    while (lg > 0 && chunks << lg > 64) --lg;
+    return lg;
+}
+
 hipError_t build_deal_chunks(const uint32_t *goff, const int64_t *tile_post, int64_t n_tiles,
-                             int64_t n_cols, int32_t vbytes, uint16_t *post_doc, void *post_val,
-                             hipStream_t s)
+                             int64_t n_cols, int32_t tile_max, int32_t vbytes, uint16_t *post_doc,
+                             void *post_val, hipStream_t s)
 {
     if (n_tiles == 0 || n_cols == 0) return hipSuccess;
     if (n_tiles > 0x7FFFFFFF) return hipErrorInvalidValue;
     // 64 lists per wave
     const int64_t cols = std::min<int64_t>(65535, (n_cols + (int64_t)kDealThreads - 1) / kDealThreads);
     hipLaunchKernelGGL(k_deal_chunks, dim3((unsigned)n_tiles, (unsigned)cols), dim3(kDealThreads), 0,
-                       s, goff, tile_post, n_cols, vbytes, post_doc, post_val);
+                       s, goff, tile_post, n_cols, deal_run(tile_max), vbytes, post_doc, post_val);
     return hipGetLastError();
 }
 

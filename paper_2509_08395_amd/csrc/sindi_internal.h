@@ -210,8 +210,8 @@ hipError_t build_fill_pads(const uint32_t *goff, const uint32_t *cnt, const int6
 // the lists are filled) so that the postings one scoring instruction adds per 32-lane half fall
 // in distinct LDS banks where the chunk allows; pads stay in place.  vbytes: 4 or 2.
 hipError_t build_deal_chunks(const uint32_t *goff, const int64_t *tile_post, int64_t n_tiles,
-                             int64_t n_cols, int32_t vbytes, uint16_t *post_doc, void *post_val,
-                             hipStream_t s);
+                             int64_t n_cols, int32_t tile_max, int32_t vbytes, uint16_t *post_doc,
+                             void *post_val, hipStream_t s);
 
 // Pair scores and their gradients; max_qnnz: the longest query row (sizes the query tables).
 hipError_t launch_score_forward(const DevIndex &ix, const DevQueries &q, const int64_t *cand,
