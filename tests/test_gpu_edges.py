@@ -4,6 +4,7 @@ import pytest
 
 import oracle
 import synth
+from parity import check_bank_order
 
 pytestmark = pytest.mark.gpu
 
@@ -242,6 +243,16 @@ def test_device_build_parts(sindi, nd, vocab, tile):
                         gpu_build=g).export(raw=True) for g in (False, True))
     for name in a:
         assert np.array_equal(a[name], b[name]), name
+
+
+@pytest.mark.parametrize("tile", [12_500, 8_192, 8_193, 4_096, 2_048, 300])
+@pytest.mark.parametrize("vocab", [7, 65, 1_027])
+def test_bank_order_of_every_run(sindi, tile, vocab):
+    """Waves of one to eight neighbouring lists (tiles on both sides of the rule's steps,
+    vocabularies off every run and wave): every chunk in LDS-bank order."""
+    corpus = synth.random_csr(np.random.default_rng(23), 13_001, vocab, min(12, vocab))
+    idx = sindi.Index(corpus, alpha=1.0, window=13_001, tile=tile, value_dtype="f16", gpu_build=True)
+    check_bank_order(idx.export(raw=True), idx.export())
 
 
 def test_rebuilt_indexes_reuse_and_return_memory(sindi):
