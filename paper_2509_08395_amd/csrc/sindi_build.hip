@@ -1031,15 +1031,17 @@ hipError_t build_fill_pads(const uint32_t *goff, const uint32_t *cnt, const int6
     return hipGetLastError();
 }
 
-// Neighbouring lists (2^x of them, at most 8) that a wave of the bank-order pass takes: as many as
-// hold 64 chunks at most in a full tile.  In us, runs of 1 and 8: 500,000 documents in tiles of 20
-// 4296 1371, of 100 847 451, of 300 377 305; 1M documents, 250K terms, tiles of 500 1472 979, of
-// 2,000 450 352, of 12,500 164 320 (a wave then walks the eight longest lists alone).
-static int32_t deal_run(int32_t tile_max)
+// Neighbouring lists (2^x of them, at most 8) that a wave of the bank-order pass takes.  A run costs
+// the chain of its longest lists, some 0.8 us for each chunk after the first list's, and saves sectors
+// of all lists' offsets, some 2.6 us per million lists: the longest run whose chunks are fewer than
+// one per 2^19 lists.  In us, runs of 1 and 8: 500,000 documents in tiles of 20 4296 1371, of 100 847
+// 451, of 300 377 305; 1M documents, 250K terms, tiles of 500 1472 979, of 2,000 450 352, of 12,500 164
+// 320; a build of 2,000 documents in one tile 475 519.
+static int32_t deal_run(int64_t n_tiles, int64_t n_cols, int32_t tile_max)
 {
-    const int32_t chunks = (tile_max + 4 * kChunk - 1) / (4 * kChunk);
+    const int64_t chunks = (tile_max + 4 * kChunk - 1) / (4 * kChunk);
     int32_t lg = 3;
-    while (lg > 0 && chunks << lg > 64) --lg;
+    while (lg > 0 && (((int64_t)1 << lg) - 1) * chunks > (n_tiles * n_cols) >> 19) --lg;
     return lg;
 }
 
@@ -1052,7 +1054,7 @@ hipError_t build_deal_chunks(const uint32_t *goff, const int64_t *tile_post, int
     // 64 lists per wave
     const int64_t cols = std::min<int64_t>(65535, (n_cols + (int64_t)kDealThreads - 1) / kDealThreads);
     hipLaunchKernelGGL(k_deal_chunks, dim3((unsigned)n_tiles, (unsigned)cols), dim3(kDealThreads), 0,
-                       s, goff, tile_post, n_cols, deal_run(tile_max), vbytes, post_doc, post_val);
+                       s, goff, tile_post, n_cols, deal_run(n_tiles, n_cols, tile_max), vbytes, post_doc, post_val);
     return hipGetLastError();
 }
 

@@ -245,13 +245,21 @@ def test_device_build_parts(sindi, nd, vocab, tile):
         assert np.array_equal(a[name], b[name]), name
 
 
-@pytest.mark.parametrize("tile", [12_500, 8_192, 8_193, 4_096, 2_048, 300])
-@pytest.mark.parametrize("vocab", [7, 65, 1_027])
-def test_bank_order_of_every_run(sindi, tile, vocab):
-    """Waves of one to eight neighbouring lists (tiles on both sides of the rule's steps,
-    vocabularies off every run and wave): every chunk in LDS-bank order."""
-    corpus = synth.random_csr(np.random.default_rng(23), 13_001, vocab, min(12, vocab))
-    idx = sindi.Index(corpus, alpha=1.0, window=13_001, tile=tile, value_dtype="f16", gpu_build=True)
+@pytest.mark.parametrize("vocab, tile", [(1_027, 5_000), (262_149, 5_000), (262_143, 250), (524_289, 250),
+                                         (524_293, 125)])
+def test_bank_order_of_every_run(sindi, vocab, tile):
+    """Waves of one to eight neighbouring lists (terms times tiles on both sides of the rule's
+    steps, vocabularies off every run and wave): every chunk in LDS-bank order."""
+    nd = 1_001
+    rng = np.random.default_rng(23)
+    lists = rng.choice(vocab, 150, replace=False)  # long ones, the first and the last terms among them
+    lists[:3] = 0, vocab - 2, vocab - 1
+    lists = np.unique(np.concatenate([lists, lists[3:] // 8 * 8 + 7])).astype(np.int32)
+    lists = lists[lists < vocab]
+    rows = [lists[rng.random(lists.size) < 0.3] for _ in range(nd)]
+    indptr = np.concatenate([[0], np.cumsum([r.size for r in rows])])
+    corpus = synth.Csr(indptr, np.concatenate(rows), rng.lognormal(0, 0.8, indptr[-1]).astype(np.float32), vocab)
+    idx = sindi.Index(corpus, alpha=1.0, window=nd, tile=tile, value_dtype="f16", gpu_build=True)
     check_bank_order(idx.export(raw=True), idx.export())
 
 
