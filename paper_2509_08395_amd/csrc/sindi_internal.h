@@ -56,12 +56,13 @@ struct DevCoarse {
 };
 
 constexpr int kAccThreads = 512;       // accumulate kernel workgroup
-constexpr int kQueues = 8;             // work queues of a scoring launch: one per XCD
+constexpr int kQueues = 8;             // work queues of a scoring launch: one per XCD of a whole MI355X
+                                       // (fewer XCDs share them: same items, less kept in each L2)
 constexpr int kQueueStep = 16;         // 8-byte words from one queue's counter to the next: 128-byte lines
 constexpr size_t kQueueBytes = 2 * kQueues * kQueueStep * sizeof(unsigned long long);  // sample, score
 constexpr int kFinThreads = 256;       // rerank, top-k and pair-score kernels
 constexpr int kGammaMax = 4096;        // largest reorder pool
-constexpr int kQueryHash = 8192;       // rerank hash slots (query nnz <= kQueryHash / 2)
+constexpr int kQueryHash = 8192;       // entries of the largest query table; rows hold at most half
 constexpr int kEntryBlock = 512;       // (query, term) entries merged per pass in the accumulate kernel
 constexpr int kChunk = 64;             // 4-posting groups per list chunk (one per lane)
 constexpr uint32_t kGoffMask = 0x3FFFFFFFu;
@@ -145,7 +146,8 @@ hipError_t launch_query_prep(const DevQueries &q, int64_t n_cols, double beta, D
 // theta (and sum_min, the least sum that reaches it): null keeps every document.  per_item: the
 // plan's item_run.  queue: null launches one workgroup per item; otherwise (one query per
 // workgroup only) one persistent launch of the device's resident workgroups takes the items
-// from the 8-byte counter *queue, which must be zero when the launch starts.
+// by kQueues counters, kQueueStep 8-byte words apart from queue on (kQueueBytes / 2 in all), which
+// must be zero when the launch starts.
 hipError_t launch_accumulate(const DevIndex &ix, const DevQueries &q, const DevCoarse &c,
                              int batch, bool sample, const DevSlots &slots,
                              int32_t n_sample_tiles, float *maxima, const float *theta,
@@ -166,8 +168,8 @@ hipError_t launch_report(const DevRetry &r, hipStream_t s);
 // rerank table; a longer row gets status kSlotRetry).  theta: the thresholds
 // the candidates were emitted with (null: every document was emitted); a
 // threshold <= 0 means the zero sums were left out and are supplied here.
-// With rerank, pool is scratch of n_slots * need keys (select, then rerank
-// with one wave per entry, then sort).
+// With rerank, pool is scratch of n_slots * need keys (select, then rerank,
+// four entries per wave at a time, then select and sort).
 hipError_t launch_finalize(const DevIndex &ix, const DevQueries &q, const DevSlots &slots,
                            const uint32_t *count, const uint64_t *cand,
                            const float *theta, int64_t cap, int32_t need, int32_t k, bool rerank,

@@ -61,3 +61,12 @@ def test_coarse_terms_counted_are_the_beta_mass_prefix():
         keep = oracle.mass_prune(q, beta).astype(bool)
         assert np.array_equal(np.diff(c.indptr), np.bincount(rows[keep], minlength=q.n_rows))
         assert np.array_equal(c.indices, q.indices[keep])
+
+
+def test_committed_counter_summary_lies_between_the_lists_and_every_query_s_lists():
+    """Beyond-L2 bytes of one scoring launch, whatever order its items take: at least the stored
+    lists once (274,527,988 slots of 2 B document and 2 B value), at most every query's lists
+    (657 GB) and the small arrays beside them."""
+    traffic = bench.measured_traffic(DEFAULT)
+    assert traffic is not None
+    assert 274_527_988 * 4 <= traffic < 6.6e11
