@@ -127,7 +127,8 @@ typedef struct {
     int32_t tile_max;              /* largest tile, documents                  */
     int32_t value_dtype;
     double alpha;
-    int64_t device_bytes;          /* HBM held by the index                    */
+    int64_t device_bytes;          /* HBM of the index's arrays (the library takes up
+                                      to 1/16 more, in whole size classes)     */
     int64_t n_slots;               /* posting slots stored: n_postings plus the
                                       pad entries that align every list to 4   */
     int32_t prune, vn;             /* as built                                 */
